@@ -691,7 +691,8 @@ extern "C" gs_status gs_inject(gs_ctx *ctx, int32_t gap, int32_t species, int64_
     xd = (const double *)tmp;
     vd = (const double *)((char *)tmp + (size_t)n * 8);
   }
-  hipError_t e = launch_inject(ctx->dp, gap, species, n, xd, vd, ctx->next_id[gap], ctx->fp64, ctx->stream);
+  hipError_t e = launch_inject(ctx->dp, gap, species, n, xd, vd, ctx->next_id[gap], ctx->hc[gap].N,
+                               ctx->ncu, ctx->fp64, ctx->stream);
   ctx->next_id[gap] += n;
   if (tmp) {
     (void)hipStreamSynchronize(ctx->stream);
@@ -722,7 +723,8 @@ extern "C" gs_status gs_inject_noalloc(gs_ctx *ctx, int32_t gap, int32_t species
   double *vs = xs + n;
   HIPCHK(ctx, hipMemcpyAsync(xs, x, (size_t)n * 8, hipMemcpyHostToDevice, ctx->stream));
   HIPCHK(ctx, hipMemcpyAsync(vs, v, (size_t)n * 8, hipMemcpyHostToDevice, ctx->stream));
-  hipError_t e = launch_inject(ctx->dp, gap, species, n, xs, vs, ctx->next_id[gap], ctx->fp64, ctx->stream);
+  hipError_t e = launch_inject(ctx->dp, gap, species, n, xs, vs, ctx->next_id[gap], ctx->hc[gap].N,
+                               ctx->ncu, ctx->fp64, ctx->stream);
   ctx->next_id[gap] += n;
   if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "inject launch: %s", hipGetErrorString(e));
   // synchronises: the staging array is free again when the call returns

@@ -229,7 +229,7 @@ hipError_t launch_sort(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t
 // secondary emission of every gap's queued events, many workgroups (after a push)
 hipError_t launch_emit(const DevPtrs &p, int G, int fp64, int grid, hipStream_t s, KTime t = {});
 hipError_t launch_inject(const DevPtrs &p, int gap, int species, long long n, const double *x_dev,
-                         const double *v_dev, long long id0, int fp64, hipStream_t s);
+                         const double *v_dev, long long id0, int N, int ncu, int fp64, hipStream_t s);
 hipError_t launch_phi(const DevPtrs &p, int gap, hipStream_t s);
 // time-step check: largest |u| per species (bit patterns of non-negative
 // floats, max-reduced as unsigned integers) and electrons per cell of one gap

@@ -19,6 +19,7 @@
 #include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gs_internal.h"
@@ -2701,6 +2702,38 @@ __global__ __launch_bounds__(FW) void k_fill_move(DevPtrs p, int G) {
 // ---------------------------------------------------------------------------
 // injection of caller particles (SI) into one gap
 // ---------------------------------------------------------------------------
+// Caller particle i to a slot of its region: false when its position is bad or
+// the region is full (flagged); else its cell j and the fixed-point weights of
+// the cell's two nodes.
+template <class P>
+__device__ inline bool inject_one(const DevPtrs &p, const GapConst &c, int gap, int species, int sel, double xs,
+                                  double vs, uint32_t id, unsigned long long slot, int &j, long long &w0,
+                                  long long &w1) {
+  if (!(xs >= 0.0 && xs <= c.d)) {
+    atomicOr(&p.err[0], ERR_BADINJECT);
+    return false;
+  }
+  if (slot >= (unsigned long long)c.cap[species]) {
+    atomicOr(&p.err[0], ERR_CAPACITY);
+    atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)gap);
+    return false;
+  }
+  const P xi = (P)(xs / c.dx);
+  const P u = (P)((vs * c.dt) / c.dx);
+  const size_t k = (size_t)c.pbase[species] + slot;
+  ((P *)p.X[sel])[k] = xi;
+  ((P *)p.U[sel])[k] = u;
+  p.ID[sel][k] = id;
+  j = (int)xi;
+  if (j > c.N - 1) j = c.N - 1;
+  const P f = xi - (P)j;
+  w1 = (long long)Prec<P>::wq(f);
+  w0 = Prec<P>::W - w1;
+  return true;
+}
+
+// Few particles: one per thread, a slot reservation per wave, the weights
+// added to the gap's node row directly.
 template <class P>
 __global__ void k_inject(DevPtrs p, int gap, int species, long long n, const double *x,
                          const double *v, long long id0) {
@@ -2708,7 +2741,6 @@ __global__ void k_inject(DevPtrs p, int gap, int species, long long n, const dou
   const int sel = (int)(*p.epoch & 1);
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const bool valid = i < n;
-  // one slot reservation per wave
   const unsigned long long mask = __ballot(valid);
   if (mask == 0ull) return;
   const int lane = threadIdx.x & 63;
@@ -2723,30 +2755,76 @@ __global__ void k_inject(DevPtrs p, int gap, int species, long long n, const dou
     atomicAdd((unsigned long long *)&p.gs[gap].next_id, (unsigned long long)n);
   }
   const unsigned long long slot = base + (unsigned long long)__popcll(mask & ((1ull << lane) - 1ull));
-  const double xs = x[i];
-  if (!(xs >= 0.0 && xs <= c.d)) {
-    atomicOr(&p.err[0], ERR_BADINJECT);
-    return;
-  }
-  if (slot >= (unsigned long long)c.cap[species]) {
-    atomicOr(&p.err[0], ERR_CAPACITY);
-    atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)gap);
-    return;
-  }
-  const P xi = (P)(xs / c.dx);
-  const P u = (P)((v[i] * c.dt) / c.dx);
-  const size_t k = (size_t)c.pbase[species] + slot;
-  ((P *)p.X[sel])[k] = xi;
-  ((P *)p.U[sel])[k] = u;
-  p.ID[sel][k] = (uint32_t)(id0 + i);
-  int j = (int)xi;
-  if (j > c.N - 1) j = c.N - 1;
-  const P f = xi - (P)j;
-  const long long w1 = Prec<P>::wq(f);
-  const long long w0 = Prec<P>::W - w1;
+  int j;
+  long long w0, w1;
+  if (!inject_one<P>(p, c, gap, species, sel, x[i], v[i], (uint32_t)(id0 + i), slot, j, w0, w1)) return;
   unsigned long long *gacc = p.acc + c.nbase;
   atomicAdd(&gacc[j], (unsigned long long)(c.Z[species] * w0));
   atomicAdd(&gacc[j + 1], (unsigned long long)(c.Z[species] * w1));
+}
+
+// Many particles: each workgroup takes one contiguous run of them, reserves
+// its slots with one atomic and sums the weights per node in LDS before they
+// go to the gap's node row.  Bound by HBM (16 B read, 12 B written per binary32
+// particle); what bounded the direct additions was their two global atomics
+// per particle.
+constexpr int IBS = 1024;    // threads
+constexpr int INJ_RUN = 4;   // least particles per node and workgroup (see inject_t)
+constexpr int IU = 4;        // particles per thread whose loads are in flight together
+template <class P>
+__global__ __launch_bounds__(IBS) void k_inject_run(DevPtrs p, int gap, int species, long long n, const double *x,
+                                                    const double *v, long long id0, long long per) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  unsigned long long *acc = (unsigned long long *)lds_raw;  // [N + 1]
+  __shared__ unsigned long long s_base;
+  const GapConst &c = p.gc[gap];
+  const int sel = (int)(*p.epoch & 1);
+  const int tid = threadIdx.x;
+  const long long i0 = (long long)blockIdx.x * per, i1 = min(n, i0 + per);
+  if (i0 >= i1) return;  // (the whole workgroup)
+  if (tid == 0) {
+    s_base = atomicAdd(&p.next_count[gap * 2 + species], (unsigned long long)(i1 - i0));
+    if (blockIdx.x == 0) {
+      atomicAdd((unsigned long long *)&p.gs[gap].live[species], (unsigned long long)n);
+      atomicAdd((unsigned long long *)&p.gs[gap].next_id, (unsigned long long)n);
+    }
+  }
+  const int nn = c.N + 1;
+  for (int j = tid; j < nn; j += IBS) acc[j] = 0ull;
+  __syncthreads();
+  const unsigned long long base = s_base;
+  for (long long ib = i0 + tid; ib < i1; ib += IU * IBS) {
+    double xs[IU], vs[IU];
+#pragma unroll
+    for (int q = 0; q < IU; ++q) {
+      const long long i = min(ib + q * IBS, i1 - 1);
+      xs[q] = x[i];
+      vs[q] = v[i];
+    }
+#pragma unroll
+    for (int q = 0; q < IU; ++q) {
+      const long long i = ib + q * IBS;
+      int j;
+      long long w0, w1;
+      if (i < i1 && inject_one<P>(p, c, gap, species, sel, xs[q], vs[q], (uint32_t)(id0 + i),
+                                  base + (unsigned long long)(i - i0), j, w0, w1)) {
+        atomicAdd(&acc[j], (unsigned long long)w0);
+        atomicAdd(&acc[j + 1], (unsigned long long)w1);
+      }
+    }
+  }
+  __syncthreads();
+  // each workgroup starts at its own node: those flushing together add to
+  // different addresses
+  unsigned long long *gacc = p.acc + c.nbase;
+  const long long Z = (long long)c.Z[species];
+  const int rot = (int)(((long long)blockIdx.x * 977) % nn);
+  for (int q = tid; q < nn; q += IBS) {
+    int j = q + rot;
+    j = j >= nn ? j - nn : j;
+    const unsigned long long w = acc[j];
+    if (w != 0ull) atomicAdd(&gacc[j], (unsigned long long)(Z * (long long)w));
+  }
 }
 
 // phi_i = dx sum_{k >= i} E_{k+1/2}, phi_N = 0 (one gap, one workgroup)
@@ -2952,16 +3030,41 @@ hipError_t launch_emit(const DevPtrs &p, int G, int fp64, int grid, hipStream_t 
               : launch_k(k_emit<float>, dim3(grid), dim3(EBS), lds, s, t.a, t.b, p, G);
 }
 
-hipError_t launch_inject(const DevPtrs &p, int gap, int species, long long n, const double *x,
-                         const double *v, long long id0, int fp64, hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const int bs = 256;
-  const unsigned int grid = (unsigned int)((n + bs - 1) / bs);
-  if (fp64)
-    hipLaunchKernelGGL(k_inject<double>, dim3(grid), dim3(bs), 0, s, p, gap, species, n, x, v, id0);
-  else
-    hipLaunchKernelGGL(k_inject<float>, dim3(grid), dim3(bs), 0, s, p, gap, species, n, x, v, id0);
+template <class P>
+static hipError_t inject_t(const DevPtrs &p, int gap, int species, long long n, const double *x, const double *v,
+                           long long id0, int N, int ncu, hipStream_t s) {
+  // runs of at least INJ_RUN particles per node, so that a run's flush (N + 1
+  // atomics at most) stays small beside the 2 x run atomics it replaces; below
+  // two such runs the direct kernel
+  const long long runs = n / (INJ_RUN * (long long)(N + 1));
+  if (runs < 2) {
+    const int bs = 256;
+    hipLaunchKernelGGL(k_inject<P>, dim3((unsigned int)((n + bs - 1) / bs)), dim3(bs), 0, s, p, gap, species, n, x, v,
+                       id0);
+    return hipGetLastError();
+  }
+  const size_t lds = (size_t)(N + 1) * 8;
+  static size_t attr_set = 65536;
+  if (lds > attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_inject_run<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = lds;
+  }
+  // a workgroup's LDS lets two share a CU up to 8191 cells
+  const long long most = (long long)std::max(ncu, 1) * (lds <= 65536 ? 2 : 1);
+  const long long grid = std::min(runs, most);
+  const long long per = ((n + grid - 1) / grid + 63) / 64 * 64;
+  hipLaunchKernelGGL(k_inject_run<P>, dim3((unsigned int)grid), dim3(IBS), lds, s, p, gap, species, n, x, v, id0,
+                     per);
   return hipGetLastError();
+}
+
+hipError_t launch_inject(const DevPtrs &p, int gap, int species, long long n, const double *x, const double *v,
+                         long long id0, int N, int ncu, int fp64, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  return fp64 ? inject_t<double>(p, gap, species, n, x, v, id0, N, ncu, s)
+              : inject_t<float>(p, gap, species, n, x, v, id0, N, ncu, s);
 }
 
 hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, unsigned long long *umax,
