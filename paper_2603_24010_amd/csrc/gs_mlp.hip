@@ -1,11 +1,8 @@
 // Training and batch evaluation of the Newton guess network on the GPU.
 //
 // Training is plain mini-batch gradient descent with Adam (Kingma and Ba,
-// 2015) on the mean squared error, in binary32: forward and backward are
-// strided GEMMs on the matrix cores with fused epilogues (bias, GELU, GELU'),
-// the weight gradients split over the batch and summed in a fixed order, bias
-// gradients are column sums; every reduction has a fixed order, so a run is
-// bitwise repeatable.  Batch evaluation uses the same device routine as the
+// 2015) on the mean squared error, in binary32 on the matrix cores; every
+// reduction has a fixed order, so a run is bitwise repeatable.  Batch evaluation uses the same device routine as the
 // strict step (bfloat16 weights, binary32 sums).
 #include <hip/hip_runtime.h>
 
@@ -19,220 +16,319 @@
 namespace gs {
 
 // ---------------------------------------------------------------------------
-// C[m][n] = epilogue(sum_k A(m,k) B(k,n)),  A(m,k) = A[m sam + k sak],
-// B(k,n) = B[k sbk + n sbn], C row-major with leading dimension ldc.
-// On the matrix cores in binary32 (v_mfma_f32_16x16x4_f32: binary32 products,
-// binary32 sums): 64 x 64 output tiles, 256 threads, each wave a 32 x 32
-// quadrant as 2 x 2 blocks of 16 x 16; K in steps of 16 through LDS, the next
-// step's operands loaded into registers while the current one is multiplied.
-// blockIdx.z takes a slice of kslice of the K range (split-K): slice z writes
-// C + z * slice_stride, and the slices are then summed in order z = 0, 1, ...
-// (k_sum_slices).  Every sum has a fixed order, so a run is bitwise
-// repeatable.
-// Lane l of a wave gives the 16 x 4 A block's element (l % 16, l / 16) and the
-// 4 x 16 B block's (l / 16, l % 16); its accumulator r holds D(4 (l / 16) + r,
-// l % 16).
+// One optimiser step is two kernels.  k_train_rows takes a tile of batch rows
+// through the whole network and back, the tile's activations in LDS from the
+// gather to the last layer's derivative, and leaves what the weight gradients
+// contract over (inputs, activations, derivatives) in the workspace.
+// k_train_update sums one 16 x 16 block of a weight gradient over the batch per
+// workgroup and applies Adam to it.  What bounds a step at the usual batches is
+// latency: 14.6 GFLOP in 64 steps of batch 1024 is 1.5 us of matrix work a step.
+// At batch 1024 (64 row tiles, 160 blocks) the two kernels take 19.7 and 8.3 us
+// and a step 30.4 us, launches included; one kernel per GEMM, column sum and
+// reduction (22 launches) took 157 us.
+//
+// All products run on the matrix cores in binary32 (v_mfma_f32_16x16x4_f32:
+// binary32 products and sums).  Lane l gives A(l % 16, l / 16) and B(l / 16, l
+// % 16); its accumulator r holds D(4 (l / 16) + r, l % 16).  The order of a
+// sum over k is free but fixed: where k runs along memory, the four MFMAs of a
+// 16-wide step take k = 4 (l / 16) + j, j = 0..3, so that a lane reads four
+// consecutive values.
 // ---------------------------------------------------------------------------
-enum { EP_STORE = 0, EP_BIAS_GELU = 1, EP_BIAS = 2, EP_GELU_GRAD = 3 };
-
-constexpr int GT = 64, GK = 16;
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-__device__ inline float gelu_grad_f32(float z) {
+__device__ inline float gelu_both(float z, float *grad) {
   const float Phi = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-  return Phi + z * (0.39894228040143268f * expf(-0.5f * z * z));
+  *grad = Phi + z * (0.39894228040143268f * expf(-0.5f * z * z));
+  return gelu_f32(z);
 }
 
-template <int EP>
-__global__ __launch_bounds__(256) void k_gemm(int M, int N, int K, int kslice, const float *A, long sam, long sak,
-                                              const float *B, long sbk, long sbn, float *C, long ldc,
-                                              long slice_stride, const float *bias, float *Zout, const float *Zin) {
-  __shared__ float As[GK][GT + 4];
-  __shared__ float Bs[GK][GT + 4];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
-  const int k_lo = blockIdx.z * kslice, k_hi = min(K, k_lo + kslice);
-  const int wm = (wv >> 1) * 32, wn = (wv & 1) * 32;  // this wave's quadrant
-  C += (long)blockIdx.z * slice_stride;
-  // staging: element e = tid + 256 q of the 16 x 64 tile, q = 0..3
-  float ra[4], rb[4];
-  auto load = [&](int k0) {
+// four consecutive floats from 4-byte aligned memory (the caller's arrays)
+__device__ inline v4f ld4(const float *a) {
+  v4f v;
+  __builtin_memcpy(&v, a, 16);
+  return v;
+}
+
+constexpr int TRW = 8;              // waves of k_train_rows: one 16-wide column block each
+constexpr int TRT = TRW * 64;       // its threads
+constexpr int TLD = MLP_H + 4;      // row stride of the LDS tiles (spreads rows over the banks)
+constexpr int TRM = 16;             // batch rows per row block
+constexpr int TRAIN_MB1_MAX = 4096; // largest batch with one row block per workgroup
+static_assert(TRW * 16 == MLP_H, "a wave per column block");
+
+// what k_train_rows leaves for the weight gradients (rows of the batch)
+struct TrainRows {
+  float *x, *a1, *a2, *a3;   // inputs and activations: [B][48], [B][128] x 3
+  float *d1, *d2, *d3, *dy;  // derivatives by the pre-activations: [B][128] x 3, [B][3]
+  float *loss;               // sum of squared errors per workgroup
+  unsigned int *bad;
+};
+
+template <int MB>
+constexpr size_t train_rows_lds() {
+  return ((size_t)MB * TRM * (5 * TLD + 3 * MLP_OUT)) * 4;
+}
+
+// W (row-major [128][K], K a multiple of 16) for one column block of the
+// forward product: lane l's values of row n0 + l % 16
+template <int K>
+__device__ inline void load_fwd(const float *W, int n0, v4f *w) {
+  const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q, kk = e / GT, mm = e % GT;
-      const int k = k0 + kk, m = m0 + mm, n = n0 + mm;
-      ra[q] = (m < M && k < k_hi) ? A[(long)m * sam + (long)k * sak] : 0.0f;
-      rb[q] = (n < N && k < k_hi) ? B[(long)k * sbk + (long)n * sbn] : 0.0f;
+  for (int k = 0; k < K / 16; ++k) w[k] = ld4(W + (size_t)(n0 + c) * K + 16 * k + 4 * q);
+}
+
+// the same for the backward product: lane l's values of column k0 + l % 16
+__device__ inline void load_bwd(const float *W, int k0, v4f *w) {
+  const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int n = 0; n < MLP_H / 16; ++n)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w[n][j] = W[(size_t)(16 * n + 4 * q + j) * MLP_H + k0 + c];
+}
+
+// acc[m] = rows of block m of the LDS tile A times the loaded block
+template <int MB, int K>
+__device__ inline void mul_block(const float *A, const v4f *w, v4f *acc) {
+  const int c = threadIdx.x & 15, q = (threadIdx.x >> 4) & 3;
+#pragma unroll
+  for (int m = 0; m < MB; ++m) acc[m] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int k = 0; k < K / 16; ++k) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m) {
+      const v4f a = *(const v4f *)(A + (m * TRM + c) * TLD + 16 * k + 4 * q);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], w[k][j], acc[m], 0, 0, 0);
     }
-  };
-  v4f acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-  if (k_lo < k_hi) load(k_lo);
-  for (int k0 = k_lo; k0 < k_hi; k0 += GK) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = tid + 256 * q;
-      As[e / GT][e % GT] = ra[q];
-      Bs[e / GT][e % GT] = rb[q];
-    }
-    __syncthreads();
-    if (k0 + GK < k_hi) load(k0 + GK);
-#pragma unroll
-    for (int kk = 0; kk < GK; kk += 4) {
-      const int kr = kk + (lane >> 4), c = lane & 15;
-      const float a0 = As[kr][wm + c], a1 = As[kr][wm + 16 + c];
-      const float b0 = Bs[kr][wn + c], b1 = Bs[kr][wn + 16 + c];
-      acc[0][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b0, acc[0][0], 0, 0, 0);
-      acc[0][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0, b1, acc[0][1], 0, 0, 0);
-      acc[1][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b0, acc[1][0], 0, 0, 0);
-      acc[1][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1, b1, acc[1][1], 0, 0, 0);
-    }
-    __syncthreads();
   }
+}
+
+// MB row blocks of 16 per workgroup
+template <int MB>
+__global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const float *t, long long n,
+                                                       const int32_t *order, long long off, int B, const float *th,
+                                                       TrainRows o) {
+  constexpr int R = MB * TRM;
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  float *A0 = (float *)lds_raw;        // [R][TLD] x 2: a layer's input, its output
+  float *A1 = A0 + R * TLD;
+  float *G1 = A1 + R * TLD;            // [R][TLD] x 3: GELU' of the pre-activations
+  float *G2 = G1 + R * TLD, *G3 = G2 + R * TLD;
+  float *sdy = G3 + R * TLD;           // [R][3]
+  float *st = sdy + R * MLP_OUT;       // [R][3] targets
+  float *se = st + R * MLP_OUT;        // [R][3] squared errors
+  const int tid = threadIdx.x, wv = tid >> 6, c = tid & 15, q = (tid >> 4) & 3;
+  const int n0 = wv * 16;
+  const int r0 = blockIdx.x * R;
+  const float *W1 = th + MLP_OFF_W1, *W2 = th + MLP_OFF_W2, *W3 = th + MLP_OFF_W3, *W4 = th + MLP_OFF_W4;
+  v4f w1[MLP_IN / 16], wa[MLP_H / 16], wb[MLP_H / 16];
+  load_fwd<MLP_IN>(W1, n0, w1);
+  load_fwd<MLP_H>(W2, n0, wa);
+  // the batch's rows (past its end the last one, whose derivative is zeroed);
+  // an index outside [0, n) is replaced by 0 and counted
+  for (int e = tid; e < R * (MLP_IN + MLP_OUT); e += TRT) {
+    const int r = e / (MLP_IN + MLP_OUT), f = e % (MLP_IN + MLP_OUT);
+    const int b = min(r0 + r, B - 1);
+    long long i = order[off + b];
+    if (i < 0 || i >= n) {
+      if (f == 0 && r0 + r < B) atomicAdd(o.bad, 1u);
+      i = 0;
+    }
+    if (f < MLP_IN) {
+      const float v = x[i * MLP_IN + f];
+      A0[r * TLD + f] = v;
+      if (r0 + r < B) o.x[(size_t)b * MLP_IN + f] = v;
+    } else {
+      st[r * MLP_OUT + f - MLP_IN] = t[i * MLP_OUT + f - MLP_IN];
+    }
+  }
+  __syncthreads();
+  // a hidden layer's epilogue: bias, GELU to LDS and the workspace, GELU' to LDS
+  v4f acc[MB];
+  auto hidden = [&](const float *bias, float *out, float *g, float *global) {
+    const float bj = bias[n0 + c];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int m = 0; m < MB; ++m)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * (lane >> 4) + r, n = n0 + wn + 16 * j + (lane & 15);
-        if (m >= M || n >= N) continue;
-        const long o = (long)m * ldc + n;
-        float v = acc[i][j][r];
-        if (EP == EP_BIAS_GELU) {
-          const float z = v + bias[n];
-          Zout[o] = z;
-          v = gelu_f32(z);
-        } else if (EP == EP_BIAS) {
-          v += bias[n];
-        } else if (EP == EP_GELU_GRAD) {
-          v *= gelu_grad_f32(Zin[o]);
-        }
-        C[o] = v;
+      for (int i = 0; i < 4; ++i) {
+        const int r = m * TRM + 4 * q + i;
+        float gr;
+        const float v = gelu_both(acc[m][i] + bj, &gr);
+        out[r * TLD + n0 + c] = v;
+        g[r * TLD + n0 + c] = gr;
+        if (r0 + r < B) global[(size_t)(r0 + r) * MLP_H + n0 + c] = v;
       }
-}
-
-// C[i] = sum over z = 0..S-1 of P[z * stride + i], i < n, in that order
-__global__ void k_sum_slices(const float *P, int S, long stride, long n, float *C) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float s = 0.0f;
-  for (int z = 0; z < S; ++z) s += P[(long)z * stride + i];
-  C[i] = s;
-}
-
-template <int EP>
-static hipError_t gemm(hipStream_t s, int M, int N, int K, const float *A, long sam, long sak, const float *B,
-                       long sbk, long sbn, float *C, long ldc, const float *bias = nullptr,
-                       float *Zout = nullptr, const float *Zin = nullptr) {
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, 1);
-  hipLaunchKernelGGL(k_gemm<EP>, grid, dim3(256), 0, s, M, N, K, K, A, sam, sak, B, sbk, sbn, C, ldc, 0L, bias,
-                     Zout, Zin);
-  return hipGetLastError();
-}
-
-// Up to SPLITK_MAX slices of the K range (each a whole number of K steps),
-// for the weight gradients, whose K is the batch.
-constexpr int SPLITK_MAX = 16;
-
-static int splitk_slices(int K) {
-  const int steps = (K + GK - 1) / GK;
-  return steps < 4 ? 1 : (steps / 4 < SPLITK_MAX ? steps / 4 : SPLITK_MAX);
-}
-
-// C (M x N, contiguous rows) = A B with the K range split over slices, each
-// slice's partial in P, then summed in slice order into C
-static hipError_t gemm_splitk(hipStream_t s, int M, int N, int K, const float *A, long sam, long sak,
-                              const float *B, long sbk, long sbn, float *C, float *P) {
-  const int S = splitk_slices(K);
-  const int kslice = ((K + S - 1) / S + GK - 1) / GK * GK;
-  const int used = (K + kslice - 1) / kslice;
-  const long n = (long)M * N;
-  dim3 grid((N + GT - 1) / GT, (M + GT - 1) / GT, used);
-  hipLaunchKernelGGL(k_gemm<EP_STORE>, grid, dim3(256), 0, s, M, N, K, kslice, A, sam, sak, B, sbk, sbn, P,
-                     (long)N, n, nullptr, nullptr, nullptr);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_sum_slices, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, (const float *)P, used, n, n,
-                     C);
-  return hipGetLastError();
-}
-
-// batch rows selected by order[step * B + b]; an index outside [0, n) is
-// replaced by 0 and counted in *bad
-__global__ void k_gather(const float *x, const float *t, long long n, const int32_t *order, long long off, int B,
-                         float *xb, float *tb, unsigned int *bad) {
-  const int b = blockIdx.x;
-  long long i = order[off + b];
-  if (i < 0 || i >= n) {
-    if (threadIdx.x == 0) atomicAdd(bad, 1u);
-    i = 0;
-  }
-  for (int f = threadIdx.x; f < MLP_IN; f += blockDim.x) xb[(long)b * MLP_IN + f] = x[i * MLP_IN + f];
-  if (threadIdx.x < MLP_OUT) tb[(long)b * MLP_OUT + threadIdx.x] = t[i * MLP_OUT + threadIdx.x];
-}
-
-// loss = mean (y - t)^2 over B x 3 values; dy = 2 (y - t) / (3 B)
-__global__ __launch_bounds__(256) void k_loss(const float *y, const float *t, int B, float *dy, float *loss) {
-  __shared__ float red[256];
-  const int n = B * MLP_OUT;
-  const float inv = 1.0f / (float)n;
-  float s = 0.0f;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const float e = y[i] - t[i];
-    s += e * e;
-    dy[i] = 2.0f * e * inv;
-  }
-  red[threadIdx.x] = s;
+  };
+  mul_block<MB, MLP_IN>(A0, w1, acc);
+  load_fwd<MLP_H>(W3, n0, wb);
+  hidden(th + MLP_OFF_B1, A1, G1, o.a1);
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0 && loss) *loss = red[0] * inv;
-}
-
-// db[j] = sum_b dz[b][j]: 64 columns per workgroup and 16 row groups, group r
-// summing rows r, r + 16, ... in order (eight loads in flight), then the 16
-// partial sums of a column added in group order
-constexpr int CS_COLS = 64, CS_GROUPS = 16;
-__global__ __launch_bounds__(CS_COLS *CS_GROUPS) void k_colsum(const float *dz, int B, int N, float *db) {
-  __shared__ float part[CS_GROUPS][CS_COLS];
-  const int c = threadIdx.x % CS_COLS, r = threadIdx.x / CS_COLS;
-  const int j = blockIdx.x * CS_COLS + c;
-  const int jj = j < N ? j : N - 1;  // (columns past N read a valid one and are dropped)
-  float s = 0.0f;
-  int b = r;
-  for (; b + 7 * CS_GROUPS < B; b += 8 * CS_GROUPS) {
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = dz[(long)(b + q * CS_GROUPS) * N + jj];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) s += v[q];
-  }
-  for (; b < B; b += CS_GROUPS) s += dz[(long)b * N + jj];
-  part[r][c] = s;
+  mul_block<MB, MLP_H>(A1, wa, acc);
+  load_bwd(W3, n0, wa);
+  hidden(th + MLP_OFF_B2, A0, G2, o.a2);
   __syncthreads();
-  if (r == 0 && j < N) {
-    float t = 0.0f;
-    for (int q = 0; q < CS_GROUPS; ++q) t += part[q][c];
-    db[j] = t;
+  mul_block<MB, MLP_H>(A0, wb, acc);
+  load_bwd(W2, n0, wb);
+  hidden(th + MLP_OFF_B3, A1, G3, o.a3);
+  __syncthreads();
+  // the output layer: eight lanes per output, sixteen inputs each
+  const float inv = 1.0f / (float)(B * MLP_OUT);
+  for (int e = tid; e < R * MLP_OUT * 8; e += TRT) {
+    const int p = e & 7, r = (e >> 3) / MLP_OUT, u = (e >> 3) % MLP_OUT;
+    float s = 0.0f;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) s += A1[r * TLD + 16 * p + k] * W4[u * MLP_H + 16 * p + k];
+    s += __shfl_xor(s, 4, 64);
+    s += __shfl_xor(s, 2, 64);
+    s += __shfl_xor(s, 1, 64);
+    if (p == 0) {
+      const bool in = r0 + r < B;
+      const float d = in ? s + th[MLP_OFF_B4 + u] - st[r * MLP_OUT + u] : 0.0f;
+      se[r * MLP_OUT + u] = d * d;
+      sdy[r * MLP_OUT + u] = 2.0f * d * inv;
+      if (in) o.dy[(size_t)(r0 + r) * MLP_OUT + u] = 2.0f * d * inv;
+    }
   }
+  __syncthreads();
+  if (wv == 0) {
+    float s = 0.0f;
+    for (int e = tid; e < R * MLP_OUT; e += 64) s += se[e];
+#pragma unroll
+    for (int k = 32; k > 0; k >>= 1) s += __shfl_xor(s, k, 64);
+    if (tid == 0) o.loss[blockIdx.x] = s;
+  }
+  // back: d3 = (dy W4) GELU'(z3), then d2 and d1 through W3 and W2
+  for (int e = tid; e < R * MLP_H; e += TRT) {
+    const int r = e / MLP_H, k = e % MLP_H;
+    float s = 0.0f;
+#pragma unroll
+    for (int u = 0; u < MLP_OUT; ++u) s += sdy[r * MLP_OUT + u] * W4[u * MLP_H + k];
+    s *= G3[r * TLD + k];
+    A0[r * TLD + k] = s;
+    if (r0 + r < B) o.d3[(size_t)(r0 + r) * MLP_H + k] = s;
+  }
+  __syncthreads();
+  auto back = [&](float *out, const float *g, float *global) {
+#pragma unroll
+    for (int m = 0; m < MB; ++m)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = m * TRM + 4 * q + i;
+        const float v = acc[m][i] * g[r * TLD + n0 + c];
+        if (out) out[r * TLD + n0 + c] = v;
+        if (r0 + r < B) global[(size_t)(r0 + r) * MLP_H + n0 + c] = v;
+      }
+  };
+  mul_block<MB, MLP_H>(A0, wa, acc);
+  back(A1, G2, o.d2);
+  __syncthreads();
+  mul_block<MB, MLP_H>(A1, wb, acc);
+  back(nullptr, G1, o.d1);
 }
 
-__global__ void k_adam(float *th, float *m, float *v, const float *g, int np, float lr, float b1, float b2,
-                       float eps, float c1, float c2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= np) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.0f - b1) * gi;
-  const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
+// Adam on one parameter (Kingma and Ba, bias-corrected moments)
+struct AdamK {
+  float lr, b1, b2, eps, c1, c2;
+};
+__device__ inline void adam_one(float *th, float *m, float *v, int i, float g, const AdamK &k) {
+  const float mi = k.b1 * m[i] + (1.0f - k.b1) * g;
+  const float vi = k.b2 * v[i] + (1.0f - k.b2) * g * g;
   m[i] = mi;
   v[i] = vi;
-  th[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+  th[i] -= k.lr * (mi / k.c1) / (sqrtf(vi / k.c2) + k.eps);
+}
+
+// The weight-gradient blocks: 8 x 8 for W2 and W3, 8 x 3 for W1, 1 x 8 for W4.
+// A small block spreads the parameters over the most workgroups: at the usual
+// batches each has little to contract.
+constexpr int UB2 = 64, UB1 = 24, UB4 = 8, UBLOCKS = 2 * UB2 + UB1 + UB4;
+constexpr int UPW = 16;  // waves of k_train_update, each with a slice of the batch
+constexpr int UPT = UPW * 64;
+constexpr int UPU = 8;   // MFMAs of 4 batch rows whose loads are in flight together
+
+// dW[j][k] = sum_b d[b][j] a[b][k] for one block, summed over the waves' slices
+// in slice order, then Adam; the blocks of the first column also do the bias
+// (the same sum with a = 1).  The last step's gradient goes to grad when set.
+// Workgroup 0 adds up the batch loss.
+__global__ __launch_bounds__(UPT) void k_train_update(TrainRows o, int B, int ntiles, float *th, float *m, float *v,
+                                                      AdamK ak, float *grad, float *loss) {
+  __shared__ float part[UPW][16 * 16];
+  __shared__ float partb[UPW][16];
+  const int tid = threadIdx.x, wv = tid >> 6, c = tid & 15, q = (tid >> 4) & 3;
+  int bl = blockIdx.x;
+  const float *d, *a;
+  int ldd = MLP_H, lda = MLP_H, j0, k0, ow, ob, K = MLP_H, J = MLP_H;
+  if (bl < UB2) {
+    d = o.d3, a = o.a2, ow = MLP_OFF_W3, ob = MLP_OFF_B3, j0 = bl / 8 * 16, k0 = bl % 8 * 16;
+  } else if ((bl -= UB2) < UB2) {
+    d = o.d2, a = o.a1, ow = MLP_OFF_W2, ob = MLP_OFF_B2, j0 = bl / 8 * 16, k0 = bl % 8 * 16;
+  } else if ((bl -= UB2) < UB1) {
+    d = o.d1, a = o.x, ow = MLP_OFF_W1, ob = MLP_OFF_B1, j0 = bl / 3 * 16, k0 = bl % 3 * 16, K = lda = MLP_IN;
+  } else {
+    bl -= UB1;
+    d = o.dy, a = o.a3, ow = MLP_OFF_W4, ob = MLP_OFF_B4, j0 = 0, k0 = bl * 16, J = ldd = MLP_OUT;
+  }
+  // this wave's rows: a whole number of MFMA steps of four
+  const int per = ((B + UPW - 1) / UPW + 3) / 4 * 4;
+  const int b0 = min(wv * per, B), b1 = min(B, b0 + per);
+  const float *dl = d + min(j0 + c, J - 1), *al = a + k0 + c;
+  const bool jin = j0 + c < J;
+  v4f acc = {0.0f, 0.0f, 0.0f, 0.0f}, accb = {0.0f, 0.0f, 0.0f, 0.0f};
+  for (int b = b0; b < b1; b += 4 * UPU) {
+    float dv[UPU], av[UPU];
+#pragma unroll
+    for (int i = 0; i < UPU; ++i) {
+      const int r = min(b + 4 * i + q, B - 1);
+      dv[i] = dl[(size_t)r * ldd];
+      av[i] = al[(size_t)r * lda];
+    }
+#pragma unroll
+    for (int i = 0; i < UPU; ++i) {
+      const float dd = jin && b + 4 * i + q < b1 ? dv[i] : 0.0f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(dd, av[i], acc, 0, 0, 0);
+      if (k0 == 0) accb = __builtin_amdgcn_mfma_f32_16x16x4f32(dd, 1.0f, accb, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    part[wv][(4 * q + i) * 16 + c] = acc[i];
+    if (c == 0) partb[wv][4 * q + i] = accb[i];
+  }
+  __syncthreads();
+  if (tid < 256) {
+    const int j = j0 + tid / 16, k = k0 + tid % 16;
+    if (j < J) {
+      float g = 0.0f;
+#pragma unroll
+      for (int w = 0; w < UPW; ++w) g += part[w][tid];
+      const int i = ow + j * K + k;
+      adam_one(th, m, v, i, g, ak);
+      if (grad) grad[i] = g;
+    }
+  } else if (tid < 256 + 16 && k0 == 0) {
+    const int j = j0 + tid - 256;
+    if (j < J) {
+      float g = 0.0f;
+#pragma unroll
+      for (int w = 0; w < UPW; ++w) g += partb[w][tid - 256];
+      adam_one(th, m, v, ob + j, g, ak);
+      if (grad) grad[ob + j] = g;
+    }
+  }
+  if (blockIdx.x == 0 && loss) {
+    __syncthreads();
+    float *red = &part[0][0];  // [UPT]
+    float s = 0.0f;
+    for (int e = tid; e < ntiles; e += UPT) s += o.loss[e];
+    red[tid] = s;
+    __syncthreads();
+    for (int k = UPT / 2; k > 0; k >>= 1) {
+      if (tid < k) red[tid] += red[tid + k];
+      __syncthreads();
+    }
+    if (tid == 0) *loss = red[0] * (1.0f / (float)(B * MLP_OUT));
+  }
 }
 
 __global__ __launch_bounds__(256) void k_mlp_forward(const uint16_t *W, const float *x, float *y) {
@@ -254,89 +350,51 @@ hipError_t launch_mlp_forward(const uint16_t *W, const float *x, long long n, fl
   return hipSuccess;
 }
 
-// workspace layout (floats) for batch B
-struct TrainWs {
-  float *xb, *tb, *z1, *a1, *z2, *a2, *z3, *a3, *y, *dy, *d0, *d1, *grad, *part;
-  unsigned int *bad;
-};
-
-// the split-K partials of the largest weight gradient (H x H)
-constexpr size_t PART_FLOATS = (size_t)SPLITK_MAX * MLP_H * MLP_H;
-
-static size_t ws_floats(int B) {
-  return (size_t)B * (MLP_IN + 2 * MLP_OUT + 6 * MLP_H + MLP_OUT + 2 * MLP_H) + MLP_NPARAM + PART_FLOATS + 64 * 16;
-}
-
-static TrainWs ws_map(void *work, int B) {
-  TrainWs w;
+// the workspace of a batch of B rows; returns its floats (work may be null)
+static size_t ws_map(void *work, int B, TrainRows *o) {
   float *f = (float *)work;
+  size_t used = 0;
   auto take = [&](size_t n) {
-    float *r = f;
-    f += (n + 63) / 64 * 64;
+    float *r = f ? f + used : nullptr;
+    used += (n + 63) / 64 * 64;
     return r;
   };
-  w.bad = (unsigned int *)take(64);
-  w.xb = take((size_t)B * MLP_IN);
-  w.tb = take((size_t)B * MLP_OUT);
-  w.z1 = take((size_t)B * MLP_H);
-  w.a1 = take((size_t)B * MLP_H);
-  w.z2 = take((size_t)B * MLP_H);
-  w.a2 = take((size_t)B * MLP_H);
-  w.z3 = take((size_t)B * MLP_H);
-  w.a3 = take((size_t)B * MLP_H);
-  w.y = take((size_t)B * MLP_OUT);
-  w.dy = take((size_t)B * MLP_OUT);
-  w.d0 = take((size_t)B * MLP_H);
-  w.d1 = take((size_t)B * MLP_H);
-  w.grad = take(MLP_NPARAM);
-  w.part = take(PART_FLOATS);
-  return w;
+  o->bad = (unsigned int *)take(64);
+  o->x = take((size_t)B * MLP_IN);
+  for (float **p : {&o->a1, &o->a2, &o->a3, &o->d1, &o->d2, &o->d3}) *p = take((size_t)B * MLP_H);
+  o->dy = take((size_t)B * MLP_OUT);
+  o->loss = take((size_t)(B + TRM - 1) / TRM);
+  return used;
+}
+
+template <int MB>
+static hipError_t train_rows(const float *x, const float *t, long long n, const int32_t *order, long long off, int B,
+                             const float *th, const TrainRows &o, hipStream_t s, int *ntiles) {
+  constexpr size_t lds = train_rows_lds<MB>();
+  if (lds > 65536) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_train_rows<MB>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  *ntiles = (B + MB * TRM - 1) / (MB * TRM);
+  hipLaunchKernelGGL(k_train_rows<MB>, dim3(*ntiles), dim3(TRT), lds, s, x, t, n, order, off, B, th, o);
+  return hipGetLastError();
 }
 
 // one optimiser step on the batch at order[off .. off + B)
-static hipError_t train_step(const float *x, const float *t, long long n, const int32_t *order, long long off,
-                             int B, float *th, float *m, float *v, long long step, float lr, float b1, float b2,
-                             float eps, float *loss, const TrainWs &w, hipStream_t s) {
-  hipError_t e;
-#define CK(x)                      \
-  do {                             \
-    if ((e = (x)) != hipSuccess) \
-      return e;                    \
-  } while (0)
-  hipLaunchKernelGGL(k_gather, dim3(B), dim3(64), 0, s, x, t, n, order, off, B, w.xb, w.tb, w.bad);
-  CK(hipGetLastError());
-  const float *W1 = th + MLP_OFF_W1, *W2 = th + MLP_OFF_W2, *W3 = th + MLP_OFF_W3, *W4 = th + MLP_OFF_W4;
-  float *g = w.grad;
-  const int H = MLP_H, I = MLP_IN, O = MLP_OUT;
-  // forward: z = a W^T + b, a' = GELU(z)
-  CK(gemm<EP_BIAS_GELU>(s, B, H, I, w.xb, I, 1, W1, 1, I, w.a1, H, th + MLP_OFF_B1, w.z1));
-  CK(gemm<EP_BIAS_GELU>(s, B, H, H, w.a1, H, 1, W2, 1, H, w.a2, H, th + MLP_OFF_B2, w.z2));
-  CK(gemm<EP_BIAS_GELU>(s, B, H, H, w.a2, H, 1, W3, 1, H, w.a3, H, th + MLP_OFF_B3, w.z3));
-  CK(gemm<EP_BIAS>(s, B, O, H, w.a3, H, 1, W4, 1, H, w.y, O, th + MLP_OFF_B4));
-  hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, s, w.y, w.tb, B, w.dy, loss);
-  CK(hipGetLastError());
-  // backward: dW = dz^T a_prev, db = column sums of dz, dz_prev = (dz W) * GELU'(z_prev)
-  CK(gemm_splitk(s, O, H, B, w.dy, 1, O, w.a3, H, 1, g + MLP_OFF_W4, w.part));
-  hipLaunchKernelGGL(k_colsum, dim3(1), dim3(CS_COLS * CS_GROUPS), 0, s, w.dy, B, O, g + MLP_OFF_B4);
-  CK(hipGetLastError());
-  CK(gemm<EP_GELU_GRAD>(s, B, H, O, w.dy, O, 1, W4, H, 1, w.d0, H, nullptr, nullptr, w.z3));
-  CK(gemm_splitk(s, H, H, B, w.d0, 1, H, w.a2, H, 1, g + MLP_OFF_W3, w.part));
-  hipLaunchKernelGGL(k_colsum, dim3(H / CS_COLS), dim3(CS_COLS * CS_GROUPS), 0, s, w.d0, B, H, g + MLP_OFF_B3);
-  CK(hipGetLastError());
-  CK(gemm<EP_GELU_GRAD>(s, B, H, H, w.d0, H, 1, W3, H, 1, w.d1, H, nullptr, nullptr, w.z2));
-  CK(gemm_splitk(s, H, H, B, w.d1, 1, H, w.a1, H, 1, g + MLP_OFF_W2, w.part));
-  hipLaunchKernelGGL(k_colsum, dim3(H / CS_COLS), dim3(CS_COLS * CS_GROUPS), 0, s, w.d1, B, H, g + MLP_OFF_B2);
-  CK(hipGetLastError());
-  CK(gemm<EP_GELU_GRAD>(s, B, H, H, w.d1, H, 1, W2, H, 1, w.d0, H, nullptr, nullptr, w.z1));
-  CK(gemm_splitk(s, H, I, B, w.d0, 1, H, w.xb, I, 1, g + MLP_OFF_W1, w.part));
-  hipLaunchKernelGGL(k_colsum, dim3(H / CS_COLS), dim3(CS_COLS * CS_GROUPS), 0, s, w.d0, B, H, g + MLP_OFF_B1);
-  CK(hipGetLastError());
+static hipError_t train_step(const float *x, const float *t, long long n, const int32_t *order, long long off, int B,
+                             float *th, float *m, float *v, long long step, float lr, float b1, float b2, float eps,
+                             float *loss, float *grad, const TrainRows &o, hipStream_t s) {
+  // one row block per workgroup while that leaves CUs idle, else two, which
+  // read the weights half as often
+  int ntiles = 0;
+  hipError_t e = B <= TRAIN_MB1_MAX ? train_rows<1>(x, t, n, order, off, B, th, o, s, &ntiles)
+                                    : train_rows<2>(x, t, n, order, off, B, th, o, s, &ntiles);
+  if (e != hipSuccess) return e;
   const double c1 = 1.0 - std::pow((double)b1, (double)step), c2 = 1.0 - std::pow((double)b2, (double)step);
-  hipLaunchKernelGGL(k_adam, dim3((MLP_NPARAM + 255) / 256), dim3(256), 0, s, th, m, v, (const float *)g,
-                     MLP_NPARAM, lr, b1, b2, eps, (float)c1, (float)c2);
-  CK(hipGetLastError());
-#undef CK
-  return hipSuccess;
+  const AdamK ak{lr, b1, b2, eps, (float)c1, (float)c2};
+  hipLaunchKernelGGL(k_train_update, dim3(UBLOCKS), dim3(UPT), 0, s, o, B, ntiles, th, m, v, ak, grad, loss);
+  return hipGetLastError();
 }
 
 }  // namespace gs
@@ -345,7 +403,8 @@ using namespace gs;
 
 extern "C" size_t gs_mlp_train_workspace(int32_t batch) {
   if (batch < 1) return 0;
-  return ws_floats(batch) * sizeof(float);
+  TrainRows o;
+  return ws_map(nullptr, batch, &o) * sizeof(float);
 }
 
 extern "C" gs_status gs_mlp_train(const float *x, const float *t, int64_t n, const int32_t *order, int64_t n_order,
@@ -358,17 +417,16 @@ extern "C" gs_status gs_mlp_train(const float *x, const float *t, int64_t n, con
     return GS_EINVAL;
   if (work_bytes < gs_mlp_train_workspace(batch)) return GS_EINVAL;
   hipStream_t s = (hipStream_t)hip_stream;
-  const TrainWs w = ws_map(work, batch);
+  TrainRows w;
+  (void)ws_map(work, batch, &w);
   if (hipMemsetAsync(w.bad, 0, 4, s) != hipSuccess) return GS_EDEVICE;
   const long long steps = n_order / batch;
   for (long long k = 0; k < steps; ++k) {
     if (train_step(x, t, n, order, k * batch, batch, theta, adam_m, adam_v, step0 + k + 1, (float)lr,
-                   (float)beta1, (float)beta2, (float)eps, loss ? loss + k : nullptr, w, s) != hipSuccess)
+                   (float)beta1, (float)beta2, (float)eps, loss ? loss + k : nullptr,
+                   k == steps - 1 ? grad_last : nullptr, w, s) != hipSuccess)
       return GS_EDEVICE;
   }
-  if (grad_last && steps > 0 &&
-      hipMemcpyAsync(grad_last, w.grad, sizeof(float) * MLP_NPARAM, hipMemcpyDeviceToDevice, s) != hipSuccess)
-    return GS_EDEVICE;
   unsigned int bad = 0;
   if (hipMemcpyAsync(&bad, w.bad, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return GS_EDEVICE;
   if (hipStreamSynchronize(s) != hipSuccess) return GS_EDEVICE;
