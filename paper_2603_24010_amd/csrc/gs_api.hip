@@ -1397,7 +1397,7 @@ extern "C" gs_status gs_mlp_forward(gs_ctx *ctx, const float *x, int64_t n, floa
   if (!ctx->mlp_w) return fail(ctx, GS_ESTATE, "no guess network weights (gs_mlp_set_weights)");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(ctx, GS_EINVAL, "bad x, y or n");
   if (n == 0) return GS_OK;
-  hipError_t e = launch_mlp_forward(ctx->mlp_w, x, n, y, ctx->stream);
+  hipError_t e = launch_mlp_forward(ctx->mlp_w, x, n, y, std::max(ctx->ncu, 1), ctx->stream);
   if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "guess network launch: %s", hipGetErrorString(e));
   return GS_OK;
 }

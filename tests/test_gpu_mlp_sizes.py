@@ -59,3 +59,45 @@ def test_bad_sample_indices_are_reported():
         order[19] = bad
         with pytest.raises(gs.GapsimError):
             gs.mlp_train(x, t, order, 20, th, torch.zeros_like(th), torch.zeros_like(th))
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 1024, 1025, 1055, 1057, 16385, 50_001])
+def test_forward_at_tile_edges(n):
+    from paper_2603_24010_amd import gapsim as gs
+    from paper_2603_24010_amd import workloads as W
+    rng = np.random.default_rng(n)
+    theta = rng.normal(0.0, 0.12, oracle.MLP_NPARAM).astype(np.float32)
+    sim = gs.GapSim(W.config2(64), particle_fp=32, capacity=(64, 64))
+    sim.mlp_set_weights(theta, np.concatenate([np.zeros(48), np.ones(48), np.zeros(3), np.ones(3)]))
+    x = rng.normal(0, 1.5, (n, 48)).astype(np.float32)
+    # (outside the caller's rows nothing is read or written)
+    y = sim.mlp_forward(_view(x, n % 4)).cpu().numpy()
+    yo = oracle.mlp_forward(oracle.round_bf16(theta).astype(np.float64), x.astype(np.float64))
+    assert np.abs(y - yo).max() <= 1e-5 * np.abs(yo).max()
+    sim.close()
+
+
+def test_forward_rows_stay_apart():
+    """A row of infinities, NaN or the largest values touches no other row, and gives
+    no finite answer where the row kernel gives none."""
+    from paper_2603_24010_amd import gapsim as gs
+    from paper_2603_24010_amd import workloads as W
+    rng = np.random.default_rng(3)
+    theta = rng.normal(0.0, 0.12, oracle.MLP_NPARAM).astype(np.float32)
+    sim = gs.GapSim(W.config2(64), particle_fp=32, capacity=(64, 64))
+    sim.mlp_set_weights(theta, np.concatenate([np.zeros(48), np.ones(48), np.zeros(3), np.ones(3)]))
+    x = rng.normal(0, 1.5, (4000, 48)).astype(np.float32)
+    clean = sim.mlp_forward(_view(x, 0)).cpu().numpy()
+    odd = {5: np.inf, 70: -np.inf, 133: np.nan, 1000: np.finfo(np.float32).max, 3999: 1e-42}
+    z = x.copy()
+    for r, v in odd.items():
+        z[r, r % 48] = v
+    y = sim.mlp_forward(_view(z, 0)).cpu().numpy()
+    rows = np.array(sorted(odd))
+    same = np.setdiff1d(np.arange(4000), rows)
+    np.testing.assert_array_equal(y[same], clean[same])
+    few = sim.mlp_forward(_view(z[rows], 0)).cpu().numpy()
+    np.testing.assert_array_equal(np.isfinite(y[rows]), np.isfinite(few))
+    ok = np.isfinite(few)
+    np.testing.assert_allclose(y[rows][ok], few[ok], rtol=1e-5)
+    sim.close()
