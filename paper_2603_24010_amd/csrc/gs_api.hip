@@ -259,6 +259,8 @@ static gs_status build_const(gs_ctx *ctx, int g, const gs_gap_params &p, GapCons
   c.cgap = p.eps0 * p.area / p.d;
   c.c_par = p.c_par;
   c.s0 = p.weight * p.q_unit;
+  c.rdx = 1.0 / c.dx;
+  c.reps0 = 1.0 / c.eps0;
   for (int s = 0; s < 2; ++s) {
     // velocity change (cells per step) per V/m: Z q dt^2 / (m dx)
     c.alpha[s] = ((double)p.Z[s] * p.q_unit) * p.dt * p.dt / (p.mass[s] * c.dx);

@@ -8,6 +8,15 @@
 
 namespace gs {
 
+// Workgroup barrier for LDS only: __syncthreads also waits for every global load
+// and store the wave has under way (their data would be visible to the other
+// waves), which costs a round trip per barrier where none of it is exchanged.
+__device__ inline void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 constexpr int MAXM = GS_MAX_MESH;
 constexpr uint32_t NO_ID = 0xFFFFFFFFu;
 // fixed-point charge weights: a macroparticle is 2^F units
@@ -42,6 +51,7 @@ struct GapConst {
                       // (room for ceil(N / SORT_BIN_MIN) bins per species)
   uint64_t seed;
   double d, dx, A, eps0, dt, cgap, c_par;
+  double rdx, reps0;   // 1 / dx, 1 / eps0
   double s0;           // sheet charge per unit of Z: weight * q_unit [C/m^2]
   double alpha[2];     // Z q dt^2 / (m dx): velocity change in cells/step per V/m
   double mass[2], ev;

@@ -152,26 +152,34 @@ __device__ inline double block_exclusive_scan_w(double v, double *wsum, double *
 }
 
 // block_exclusive_scan_w of v, and in the same two barriers the block sum of w
+// (NW waves: the waves' sums are all read before the first is added)
+template <int NW>
 __device__ inline double block_exclusive_scan_sum_w(double v, double w, double *wsum, double *wsum2, double *total,
                                                     double *wtotal) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const double incl = wave_incl_scan_d(v);
   const double wincl = wave_incl_scan_d(w);
   if (lane == 63) {
     wsum[wv] = incl;
     wsum2[wv] = wincl;
   }
-  __syncthreads();
+  lds_barrier();
+  double a[NW], b[NW];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    a[q] = wsum[q];
+    b[q] = wsum2[q];
+  }
   double before = 0.0, all = 0.0, wall = 0.0;
-  for (int q = 0; q < nw; ++q) {
-    const double a = wsum[q];
-    if (q < wv) before += a;
-    all += a;
-    wall += wsum2[q];
+#pragma unroll
+  for (int q = 0; q < NW; ++q) {
+    before = q < wv ? before + a[q] : before;
+    all += a[q];
+    wall += b[q];
   }
   *total = all;
   *wtotal = wall;
-  __syncthreads();
+  lds_barrier();
   return before + incl - v;
 }
 
@@ -196,7 +204,7 @@ __device__ inline int block_exclusive_scan_i(int v, int *wsum, int *total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const int incl = wave_incl_scan(v);
   if (lane == 63) wsum[w] = incl;
-  __syncthreads();
+  lds_barrier();
   int before = 0, all = 0;
   for (int q = 0; q < nw; ++q) {
     const int a = wsum[q];
@@ -204,7 +212,7 @@ __device__ inline int block_exclusive_scan_i(int v, int *wsum, int *total) {
     all += a;
   }
   *total = all;
-  __syncthreads();
+  lds_barrier();
   return before + incl - v;
 }
 
@@ -354,265 +362,365 @@ constexpr int FDB = 256;   // k_fdens / k_ftable threads, four nodes each
 // Up to FIELD1_NMAX cells one workgroup per gap does all of it (k_field1): a
 // kernel costs some microseconds of its own here, and at 4096 cells the one
 // workgroup's serial path is shorter than three kernels'.  Its S_k live in LDS
-// (padded), and each thread forms at most FNQ nodes.
+// (padded).
 constexpr int FIELD1_NMAX = 8192;
-constexpr int FNQ = (FIELD1_NMAX + 1 + FBS - 1) / FBS;
-__device__ inline double node_rho(double s0, double dx, unsigned long long a, int j, int N, int fp64) {
+// a / b with r = 1 / b: two Newton corrections of a r give the correctly rounded
+// quotient (in the normal range) in five operations, a fifth of the general
+// division's
+__device__ inline double div_by(double a, double b, double r) {
+  double q = a * r;
+  q = __builtin_fma(__builtin_fma(-q, b, a), r, q);
+  return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+
+__device__ inline double node_rho(double s0, double dx, double rdx, unsigned long long a, int j, int N, int fp64) {
   const double scale = fp64 ? 5.684341886080801486968994140625e-14 /* 2^-44 */
                             : 5.9604644775390625e-08 /* 2^-24 */;
-  double r = s0 * ((double)(long long)a * scale) / dx;
+  double r = div_by(s0 * ((double)(long long)a * scale), dx, rdx);
   if (j == 0 || j == N) r *= 2.0;
   return r;
 }
 
-// Circuit, surface charge and electrode potential of level n (thread 0, on LDS
-// copies of the gap's constants and state).  P = (dx/eps0) sum_k S_k is the
-// potential the space charge alone gives the electrode.
-__device__ void solve_level(const DevPtrs &p, int g, const GapConst &c, GapState &st, double P,
-                            int mode, int guess, double tol, int maxit, double *sigma_out,
-                            double *wk, const unsigned long long *tl, const double *mlp_u,
-                            const unsigned long long *next_count, long long nb) {
+// Circuit, surface charge and electrode potential of level n, on LDS copies of
+// the gap's constants and state, in three parts so that little of it waits for
+// the space charge.  P = (dx/eps0) sum_k S_k is the potential the space charge
+// alone gives the electrode.
+//   level_begin  one wave, while the others form the density and its prefix
+//                sums: everything that does not depend on P
+//   level_solve  every thread: potential and surface charge from P
+//   level_counts, level_end
+//                the wave of level_begin, while the others write the field: the
+//                state after the level
+// Loops are one lane each; every sum keeps the order of the loop equations.
+// (As one thread's work between the prefix sums and the table, the level took
+// 2.4-2.7 us of the kernel's 8-10.)
+struct Level {
+  double qconv, qstar;                 // qstar: weak only
+  double K, G, c0, den;                // strict: phi0 = (c0 + P) / den, Q_circ = K - G phi0
+  double sigma;                        // weak: the surface charge needs no P
+  double h[MAXM], y[MAXM];
+  double u[MAXM + 1], r[MAXM + 1], rg[MAXM + 1], ue[MAXM + 1], rc[MAXM];  // Newton
+  double phi0;                         // Newton's electrode potential
+  int iters, fb;
+  double r0n, rn;
+};
+
+// LDS written by some lanes of a wave, read by others of it
+__device__ inline void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The beam schedule's entry for the level about to be solved (of no meaning past
+// the schedule's end; the schedule array holds at least one entry), read from a
+// clamped index, through one the compiler takes for a per-lane one: a uniform
+// load would become a scalar one, which every later wait on LDS would also wait
+// for.
+__device__ inline long long level_sched(const DevPtrs &p, const GapConst &c, const GapState &st) {
+  const long long n = st.level + 1;
+  int lane0 = 0;
+  asm volatile("" : "+v"(lane0));
+  const long long ix = c.sched_len > 0 ? c.sched_base + min(n, c.sched_len - 1) : 0;
+  return (long long)p.sched[ix + lane0];
+}
+
+__device__ void level_begin(const DevPtrs &p, int g, const GapConst &c, GapState &st, int mode, Level &lv,
+                            const unsigned long long *tl) {
+  const int lane = threadIdx.x & 63;
   const int M = c.M, gm = c.g;
   const double A = c.A, eps0 = c.eps0;
   const long long n = st.level + 1;
   const double t = (double)n * c.dt;
+  // an external circuit engine's gap voltage for this level (pinned host memory)
+  const double v_ext = mode == 2 ? p.ext_v[g] : 0.0;
+  if (lane < M) lv.h[lane] = 15.0 * st.dq[0][lane] - 7.0 * st.dq[1][lane] + st.dq[2][lane];
   // convection charge of the push that led to this level (Sec. 2.4.1); tl is
   // the gap's tally, already staged in LDS
-  long long ab[4], em[2], inj, pushed;
-  for (int i = 0; i < 4; ++i) ab[i] = (long long)tl[T_ABS + i];
-  em[0] = (long long)tl[T_EMIT];
-  em[1] = (long long)tl[T_EMIT + 1];
-  inj = (long long)tl[T_INJ];
-  pushed = (long long)tl[T_PUSHED];
   const double qsh_i = A * (c.s0 * (double)c.Z[1]);
   const double qsh_e = A * (c.s0 * (double)c.Z[0]);
   double qconv = 0.0;
-  qconv += qsh_i * (double)ab[1 * 2 + 0];
-  qconv += qsh_e * (double)ab[0 * 2 + 0];
-  qconv -= qsh_e * (double)em[0];
-  for (int i = 0; i < 4; ++i) {
-    st.abs_last[i] = ab[i];
-    st.abs_cum[i] += ab[i];
-  }
-  for (int i = 0; i < 2; ++i) {
-    st.emit_last[i] = em[i];
-    st.emit_cum[i] += em[i];
-  }
-  st.inj_last = inj;
-  st.inj_cum += inj;
-  st.pushed_last = pushed;
-  st.pushed_cum += pushed;
-  st.live[0] += em[0] + em[1] - ab[0] - ab[1];
-  st.live[1] += inj - ab[2] - ab[3];
-
-  // (no sine on this serial path when there is no AC source: dc + 0 sin = dc)
+  qconv += qsh_i * (double)(long long)tl[T_ABS + 1 * 2 + 0];
+  qconv += qsh_e * (double)(long long)tl[T_ABS + 0 * 2 + 0];
+  qconv -= qsh_e * (double)(long long)tl[T_EMIT];
+  // (no sine on this path when there is no AC source: dc + 0 sin = dc)
   const double Vs = c.src_amp != 0.0 ? c.src_dc + c.src_amp * sin(c.src_w * t + c.src_phase) : c.src_dc;
-  // small work vectors live in LDS: indexed by the run-time mesh count they would
-  // otherwise go to scratch memory
-  double *h = wk, *q = wk + MAXM, *Dn = wk + 2 * MAXM, *y = wk + 3 * MAXM;
-  double *u = wk + 4 * MAXM, *r = u + (MAXM + 1), *ue = r + (MAXM + 1), *rc = ue + (MAXM + 1);
-  for (int j = 0; j < M; ++j) h[j] = 15.0 * st.dq[0][j] - 7.0 * st.dq[1][j] + st.dq[2][j];
-  double sigma, qcirc, qstar, phi0;
-  if (mode == 0) {
-    // strict: D = y - z phi0, Q_gap = K - G phi0 (eq. Q4_phi_relation, eq. K_def)
-    for (int i = 0; i < M; ++i) {
-      double a = c.sb[i] * Vs;
-      for (int j = 0; j < M; ++j)
-        a += c.sL[i * MAXM + j] * h[j] + c.sR[i * MAXM + j] * st.dq[0][j] -
-             c.sS[i * MAXM + j] * st.qprev[j];
-      y[i] = a;
-    }
-    const double K = st.qprev[gm] + y[gm];
-    const double G = c.sz[gm] + c.c_par;
-    // eq. Poisson_BC2 closed over the interior rows:
-    // phi0 = (d/eps0) sigma + P with sigma = sigma* - G phi0 / A
-    const double sig_star = st.sigma_prev + (qconv + K - st.qcirc_prev) / A;
-    phi0 = ((c.d / eps0) * sig_star + P) / (1.0 + G * c.d / (eps0 * A));
-    int iters = -1, fb = 0;
-    double r0n = 0.0, rn = 0.0;
-    if (guess == GS_GUESS_DIRECT) {
-      // the direct solve starts from nothing; report the extrapolation
-      for (int i = 0; i <= M; ++i) st.guess[i] = 3.0 * st.uh[0][i] - 3.0 * st.uh[1][i] + st.uh[2][i];
+  wave_lds_sync();
+  if (mode != 2 && lane < M) {
+    const double *mb = mode == 0 ? c.sb : c.wb, *mL = mode == 0 ? c.sL : c.wL;
+    const double *mR = mode == 0 ? c.sR : c.wR, *mS = mode == 0 ? c.sS : c.wS;
+    double a = mb[lane] * Vs;
+    for (int j = 0; j < M; ++j)
+      a += mL[lane * MAXM + j] * lv.h[j] + mR[lane * MAXM + j] * st.dq[0][j] - mS[lane * MAXM + j] * st.qprev[j];
+    lv.y[lane] = a;
+  }
+  wave_lds_sync();
+  if (lane == 0) {
+    lv.qconv = qconv;
+    if (mode == 0) {
+      // strict: D = y - z phi0, Q_gap = K - G phi0 (eq. Q4_phi_relation, eq. K_def)
+      const double K = st.qprev[gm] + lv.y[gm];
+      const double G = c.sz[gm] + c.c_par;
+      // eq. Poisson_BC2 closed over the interior rows:
+      // phi0 = (d/eps0) sigma + P with sigma = sigma* - G phi0 / A
+      const double sig_star = st.sigma_prev + (qconv + K - st.qcirc_prev) / A;
+      lv.K = K;
+      lv.G = G;
+      lv.c0 = (c.d / eps0) * sig_star;
+      lv.den = 1.0 + G * c.d / (eps0 * A);
     } else {
-      // Newton on u = (V, I_0..I_{M-1}); the residual is affine in u
-      const int nu = M + 1;
-      auto residual = [&](const double *uu, double *rr) {
-        // BDF2 increments from the currents: I = (3 D - D1) / (2 dt)
-        for (int j = 0; j < M; ++j) rc[j] = (2.0 * c.dt * uu[1 + j] + st.dq[0][j]) / 3.0 - y[j];
-        // loop equations in volts: T' D - C' + g V = T' (D - y) + g V
-        for (int i = 0; i < M; ++i) {
-          double a = (i == gm) ? uu[0] : 0.0;
-          for (int j = 0; j < M; ++j) a += c.Tp[i * MAXM + j] * rc[j];
-          rr[1 + i] = a / c.v_ref;
-        }
-        // closure: V equals the electrode potential the field gives
-        const double qgap = st.qprev[gm] + (rc[gm] + y[gm]) - c.c_par * uu[0];
-        const double sg = st.sigma_prev + (qconv + qgap - st.qcirc_prev) / A;
-        rr[0] = (uu[0] - ((c.d / eps0) * sg + P)) / c.v_ref;
-      };
-      auto norm = [&](const double *rr) {
-        double m = 0.0;
-        for (int i = 0; i < nu; ++i) m = fmax(m, fabs(rr[i]));
-        return m;
-      };
-      // plain guess: quadratic extrapolation of the last three levels
-      for (int i = 0; i < nu; ++i) ue[i] = 3.0 * st.uh[0][i] - 3.0 * st.uh[1][i] + st.uh[2][i];
-      residual(ue, r);
-      const double rext = norm(r);
-      bool use_mlp = false;
-      if (guess == GS_GUESS_MLP && mlp_u) {
-        for (int i = 0; i < nu; ++i) u[i] = mlp_u[i];
-        for (int i = 0; i < 3; ++i) st.mlp_prop[i] = mlp_u[i];
-        residual(u, r);
-        const double rm = norm(r);
-        use_mlp = (rm == rm) && (rm <= rext);
-        if (!use_mlp) fb = 1;
-      }
-      if (!use_mlp) {
-        for (int i = 0; i < nu; ++i) u[i] = ue[i];
-        residual(u, r);
-      }
-      for (int i = 0; i < nu; ++i) st.guess[i] = u[i];
-      r0n = norm(r);
-      rn = r0n;
-      iters = 0;
-      // stop when the residual is within the tolerance, or when an update no
-      // longer moves any component by more than a few units in its last place
-      // (large loop currents can leave the representable u nearest the
-      // solution with a scaled residual above the tolerance)
-      bool at_roundoff = false;
-      while (!(rn <= tol) && !at_roundoff && iters < maxit) {
-        at_roundoff = true;
-        for (int i = 0; i < nu; ++i) {
-          double a = 0.0;
-          for (int j = 0; j < nu; ++j) a += c.Jinv[i * (MAXM + 1) + j] * r[j];
-          ue[i] = u[i] - a;
-          if (!(fabs(a) <= 8.0 * 2.220446049250313e-16 * fabs(u[i]))) at_roundoff = false;
-        }
-        for (int i = 0; i < nu; ++i) u[i] = ue[i];
-        residual(u, r);
-        rn = norm(r);
-        iters += 1;
-      }
-      if (!(rn <= tol) && !at_roundoff) atomicOr(p.err, ERR_NOCONV);
-      phi0 = u[0];
+      // weak: the circuit alone with the gap as a capacitor, then the field; or
+      // an external engine's gap voltage V* for this level, Q_circ* = C_gap V*
+      // (Sec. 2.4.3)
+      double vstar = v_ext;
+      if (mode == 1) vstar = (st.qprev[gm] + lv.y[gm]) / (c.cgap + c.c_par);
+      lv.qstar = c.cgap * vstar;
+      lv.sigma = st.sigma_prev + (qconv + lv.qstar - st.qcirc_prev) / A;
     }
-    qcirc = K - G * phi0;
-    qstar = qcirc;
-    sigma = st.sigma_prev + (qconv + qcirc - st.qcirc_prev) / A;  // eq. sigma_update
-    for (int j = 0; j < M; ++j) {
-      Dn[j] = y[j] - c.sz[j] * phi0;
-      q[j] = st.qprev[j] + Dn[j];
+  }
+}
+
+// Newton on u = (V, I_0..I_{M-1}) for the strict level (the wave of
+// level_begin, a lane per component); the residual is affine in u
+__device__ void level_newton(const DevPtrs &p, const GapConst &c, GapState &st, Level &lv, double P, int guess,
+                             double tol, int maxit, const double *mlp_u) {
+  const int lane = threadIdx.x & 63;
+  const int M = c.M, gm = c.g, nu = M + 1;
+  const double A = c.A, eps0 = c.eps0;
+  double *u = lv.u, *r = lv.r, *ue = lv.ue, *rc = lv.rc;
+  const double *y = lv.y;
+  auto residual = [&](const double *uu, double *rr) {
+    // BDF2 increments from the currents: I = (3 D - D1) / (2 dt)
+    if (lane < M) rc[lane] = (2.0 * c.dt * uu[1 + lane] + st.dq[0][lane]) / 3.0 - y[lane];
+    wave_lds_sync();
+    if (lane < M) {
+      // loop equations in volts: T' D - C' + g V = T' (D - y) + g V
+      const int i = lane;
+      double a = (i == gm) ? uu[0] : 0.0;
+      for (int j = 0; j < M; ++j) a += c.Tp[i * MAXM + j] * rc[j];
+      rr[1 + i] = a / c.v_ref;
+    } else if (lane == M) {
+      // closure: V equals the electrode potential the field gives
+      const double qgap = st.qprev[gm] + (rc[gm] + y[gm]) - c.c_par * uu[0];
+      const double sg = st.sigma_prev + (lv.qconv + qgap - st.qcirc_prev) / A;
+      rr[0] = (uu[0] - ((c.d / eps0) * sg + P)) / c.v_ref;
     }
-    st.newton_last = iters;
-    st.newton_fb_last = fb;
-    if (iters >= 0) {
-      st.newton_total += iters;
-      st.newton_fallbacks += fb;
-      st.newton_max = max(st.newton_max, iters);
-      st.newton_levels += 1;
+    wave_lds_sync();
+  };
+  auto norm = [&](const double *rr) {  // (the same in every lane)
+    double m = 0.0;
+    for (int i = 0; i < nu; ++i) m = fmax(m, fabs(rr[i]));
+    return m;
+  };
+  // plain guess: quadratic extrapolation of the last three levels
+  if (lane < nu) ue[lane] = 3.0 * st.uh[0][lane] - 3.0 * st.uh[1][lane] + st.uh[2][lane];
+  wave_lds_sync();
+  residual(ue, r);
+  double rn = norm(r);
+  int fb = 0;
+  const double *from = ue;
+  if (guess == GS_GUESS_MLP && mlp_u) {
+    if (lane < 3) st.mlp_prop[lane] = mlp_u[lane];
+    residual(mlp_u, lv.rg);
+    const double rm = norm(lv.rg);
+    if ((rm == rm) && (rm <= rn)) {
+      from = mlp_u;
+      rn = rm;
+      if (lane < nu) r[lane] = lv.rg[lane];
+    } else {
+      fb = 1;
     }
-    st.newton_r0 = r0n;
-    st.newton_r = rn;
-  } else if (mode == 2) {
-    // weak with an external circuit engine: its gap voltage V* for this level
-    // gives Q_circ* = C_gap V* (Sec. 2.4.3); the library's own loops are not
-    // advanced, only the gap mesh follows the re-imposed charge
-    qstar = c.cgap * p.ext_v[g];
-    sigma = st.sigma_prev + (qconv + qstar - st.qcirc_prev) / A;
-    phi0 = (c.d / eps0) * sigma + P;
-    for (int j = 0; j < M; ++j) {
-      q[j] = st.qprev[j];
-      Dn[j] = 0.0;
+  }
+  if (lane < nu) {
+    const double v = from[lane];
+    u[lane] = v;
+    st.guess[lane] = v;
+  }
+  wave_lds_sync();
+  const double r0n = rn;
+  int iters = 0;
+  // stop when the residual is within the tolerance, or when an update no
+  // longer moves any component by more than a few units in its last place
+  // (large loop currents can leave the representable u nearest the
+  // solution with a scaled residual above the tolerance)
+  bool at_roundoff = false;
+  while (!(rn <= tol) && !at_roundoff && iters < maxit) {
+    bool moved = false;
+    if (lane < nu) {
+      double a = 0.0;
+      for (int j = 0; j < nu; ++j) a += c.Jinv[lane * (MAXM + 1) + j] * r[j];
+      const double v = u[lane];
+      moved = !(fabs(a) <= 8.0 * 2.220446049250313e-16 * fabs(v));
+      u[lane] = v - a;
     }
-    q[gm] = (c.cgap + c.c_par) * phi0;
-    Dn[gm] = q[gm] - st.qprev[gm];
-    qcirc = c.cgap * phi0;
-    p.ext_phi[g] = phi0;  // for the engine's next call, read once this kernel is done
-    st.newton_last = -1;
-    st.newton_fb_last = 0;
+    at_roundoff = __ballot(moved) == 0ull;
+    wave_lds_sync();
+    residual(u, r);
+    rn = norm(r);
+    iters += 1;
+  }
+  if (lane == 0) {
+    if (!(rn <= tol) && !at_roundoff) atomicOr(p.err, ERR_NOCONV);
+    lv.phi0 = u[0];
+    lv.iters = iters;
+    lv.fb = fb;
+    lv.r0n = r0n;
+    lv.rn = rn;
+  }
+}
+
+// (newton: the potential is level_newton's)
+__device__ inline void level_solve(const GapConst &c, const GapState &st, const Level &lv, double P, int mode,
+                                   bool newton, double *phi0, double *sigma, double *qcirc) {
+  if (mode == 0) {
+    *phi0 = newton ? lv.phi0 : (lv.c0 + P) / lv.den;
+    *qcirc = lv.K - lv.G * *phi0;
+    *sigma = st.sigma_prev + (lv.qconv + *qcirc - st.qcirc_prev) / c.A;  // eq. sigma_update
   } else {
-    // weak: the circuit alone with the gap as a capacitor, then the field
-    for (int i = 0; i < M; ++i) {
-      double a = c.wb[i] * Vs;
-      for (int j = 0; j < M; ++j)
-        a += c.wL[i * MAXM + j] * h[j] + c.wR[i * MAXM + j] * st.dq[0][j] -
-             c.wS[i * MAXM + j] * st.qprev[j];
-      y[i] = a;
-    }
-    for (int j = 0; j < M; ++j) {
-      q[j] = st.qprev[j] + y[j];
-      Dn[j] = y[j];
-    }
-    const double vstar = q[gm] / (c.cgap + c.c_par);
-    qstar = c.cgap * vstar;
-    sigma = st.sigma_prev + (qconv + qstar - st.qcirc_prev) / A;
-    phi0 = (c.d / eps0) * sigma + P;
-    // re-impose the gap charge the field implies; the increment history stays
-    q[gm] = (c.cgap + c.c_par) * phi0;
-    qcirc = c.cgap * phi0;
-    st.newton_last = -1;
-    st.newton_fb_last = 0;
+    *sigma = lv.sigma;
+    *phi0 = (c.d / c.eps0) * *sigma + P;
+    // the gap charge the field implies is re-imposed
+    *qcirc = c.cgap * *phi0;
   }
-  for (int j = 0; j < M; ++j) {
-    st.I[j] = (3.0 * Dn[j] - st.dq[0][j]) / (2.0 * c.dt);
-    st.q[j] = q[j];
-    st.dq[2][j] = st.dq[1][j];
-    st.dq[1][j] = st.dq[0][j];
-    st.dq[0][j] = Dn[j];
-    st.qprev[j] = q[j];
+}
+
+// The counts of the push that led to this level, and what the coming one sweeps
+// and injects (the wave of level_begin, while the others write the field).
+__device__ void level_counts(const DevPtrs &p, int g, const GapConst &c, GapState &st, const unsigned long long *tl,
+                             const unsigned long long *next_count, long long sched) {
+  const int lane = threadIdx.x & 63;
+  const long long n = st.level + 1;
+  const long long ab[4] = {(long long)tl[T_ABS], (long long)tl[T_ABS + 1], (long long)tl[T_ABS + 2],
+                           (long long)tl[T_ABS + 3]};
+  const long long em[2] = {(long long)tl[T_EMIT], (long long)tl[T_EMIT + 1]};
+  if (lane < 4) {
+    const long long v = (long long)tl[T_ABS + lane];
+    st.abs_last[lane] = v;
+    st.abs_cum[lane] += v;
   }
-  for (int i = 0; i <= M; ++i) {
-    st.uh[2][i] = st.uh[1][i];
-    st.uh[1][i] = st.uh[0][i];
+  if (lane < 2) {
+    const long long v = (long long)tl[T_EMIT + lane];
+    st.emit_last[lane] = v;
+    st.emit_cum[lane] += v;
+    // slots the coming push sweeps (append counters can run past the capacity
+    // after an overflow, which was flagged when it happened; never sweep past
+    // the region)
+    st.count[lane] = min((long long)next_count[lane], c.cap[lane]);
   }
-  st.uh[0][0] = phi0;
-  for (int j = 0; j < M; ++j) st.uh[0][1 + j] = st.I[j];
-  {
-    // the guess network's history: this level's voltage, first two loop
-    // currents, surface charge and the absorbed / emitted charge behind Q_conv
+  if (lane == 0) {
+    const long long inj = (long long)tl[T_INJ], pushed = (long long)tl[T_PUSHED];
+    st.inj_last = inj;
+    st.inj_cum += inj;
+    st.pushed_last = pushed;
+    st.pushed_cum += pushed;
+    st.live[0] += em[0] + em[1] - ab[0] - ab[1];
+    st.live[1] += inj - ab[2] - ab[3];
+    // the step's beam gets the slots right after the swept ones (its ids and
+    // slots are fixed before the push)
+    const long long nb = n < c.sched_len ? sched : c.beam_n;
+    st.beam_now = nb;
+    p.next_count[g * 2 + 1] = (unsigned long long)(min((long long)next_count[1], c.cap[1]) + nb);
+    p.ev_count[g] = 0ull;
+    p.ev_done[g] = 0ull;
+    st.beam_id0 = st.next_id;
+    st.next_id += nb;
+    // the guess network's history: the absorbed and emitted charge behind Q_conv
+    const double qsh_i = c.A * (c.s0 * (double)c.Z[1]);
+    const double qsh_e = c.A * (c.s0 * (double)c.Z[0]);
     const int hh = st.hist_head;
-    st.hist[hh][0] = phi0;
-    st.hist[hh][1] = st.I[0];
-    st.hist[hh][2] = M > 1 ? st.I[1] : 0.0;
-    st.hist[hh][3] = sigma;
     st.hist[hh][4] = qsh_i * (double)ab[1 * 2 + 0] + qsh_e * (double)ab[0 * 2 + 0];
     st.hist[hh][5] = qsh_e * (double)em[0];
-    st.hist_head = (hh + 1) & 7;
   }
-  st.qcirc_step = qstar - st.qcirc_prev;
-  st.sigma_prev = sigma;
-  st.qcirc_prev = qcirc;
-  st.level = n;
-  st.t = t;
-  st.phi0 = phi0;
-  st.sigma = sigma;
-  st.qcirc = qcirc;
-  st.qcirc_star = qstar;
-  st.qconv = qconv;
-  // particles the coming push sweeps; the step's beam gets the slots right after
-  // them (its ids and slots are fixed before the push)
-  // (append counters can run past the capacity after an overflow, which was
-  // flagged when it happened; never sweep past the region)
-  // (next_count: the append counters as the push and the emission left them;
-  // nb: the beam of the step that solves level n, its schedule entry or else
-  // the fixed count; both read at the field kernel's start)
-  for (int s = 0; s < 2; ++s) st.count[s] = min((long long)next_count[s], c.cap[s]);
-  st.beam_now = nb;
-  p.next_count[g * 2 + 1] = (unsigned long long)(st.count[1] + nb);
-  p.ev_count[g] = 0ull;
-  p.ev_done[g] = 0ull;
-  st.beam_id0 = st.next_id;
-  st.next_id += nb;
-  *sigma_out = sigma;
+}
+
+__device__ void level_end(const DevPtrs &p, int g, const GapConst &c, GapState &st, const Level &lv, int mode,
+                          bool newton, double phi0, double sigma, double qcirc, double q_space) {
+  const int lane = threadIdx.x & 63;
+  const int M = c.M, gm = c.g;
+  if (lane < M) {
+    const int j = lane;
+    double D, q;
+    if (mode == 0) {
+      D = lv.y[j] - c.sz[j] * phi0;
+      q = st.qprev[j] + D;
+    } else if (mode == 1) {
+      // (the increment history stays when the gap charge is re-imposed)
+      D = lv.y[j];
+      q = j == gm ? (c.cgap + c.c_par) * phi0 : st.qprev[j] + D;
+    } else {
+      // the engine holds the circuit: only the gap mesh follows the charge
+      q = j == gm ? (c.cgap + c.c_par) * phi0 : st.qprev[j];
+      D = j == gm ? q - st.qprev[j] : 0.0;
+    }
+    const double I = (3.0 * D - st.dq[0][j]) / (2.0 * c.dt);
+    st.I[j] = I;
+    st.q[j] = q;
+    st.dq[2][j] = st.dq[1][j];
+    st.dq[1][j] = st.dq[0][j];
+    st.dq[0][j] = D;
+    st.qprev[j] = q;
+    if (mode == 0 && !newton)  // the direct solve starts from nothing: report the extrapolation
+      st.guess[1 + j] = 3.0 * st.uh[0][1 + j] - 3.0 * st.uh[1][1 + j] + st.uh[2][1 + j];
+    st.uh[2][1 + j] = st.uh[1][1 + j];
+    st.uh[1][1 + j] = st.uh[0][1 + j];
+    st.uh[0][1 + j] = I;
+    if (j < 2) st.hist[st.hist_head][1 + j] = I;
+  }
+  wave_lds_sync();
+  if (lane == 0) {
+    if (mode == 0 && !newton) st.guess[0] = 3.0 * st.uh[0][0] - 3.0 * st.uh[1][0] + st.uh[2][0];
+    st.uh[2][0] = st.uh[1][0];
+    st.uh[1][0] = st.uh[0][0];
+    st.uh[0][0] = phi0;
+    st.newton_last = newton ? lv.iters : -1;
+    st.newton_fb_last = newton ? lv.fb : 0;
+    if (mode == 0) {
+      if (newton) {
+        st.newton_total += lv.iters;
+        st.newton_fallbacks += lv.fb;
+        st.newton_max = max(st.newton_max, lv.iters);
+        st.newton_levels += 1;
+      }
+      st.newton_r0 = newton ? lv.r0n : 0.0;
+      st.newton_r = newton ? lv.rn : 0.0;
+    }
+    // the guess network's history: this level's voltage and surface charge (its
+    // first two loop currents above, the charges behind Q_conv in level_begin)
+    const int hh = st.hist_head;
+    st.hist[hh][0] = phi0;
+    if (M < 2) st.hist[hh][2] = 0.0;
+    st.hist[hh][3] = sigma;
+    st.hist_head = (hh + 1) & 7;
+    const double qstar = mode == 0 ? qcirc : lv.qstar;
+    st.qcirc_step = qstar - st.qcirc_prev;
+    st.sigma_prev = sigma;
+    st.qcirc_prev = qcirc;
+    const long long n = st.level + 1;
+    st.level = n;
+    st.t = (double)n * c.dt;
+    st.phi0 = phi0;
+    st.sigma = sigma;
+    st.qcirc = qcirc;
+    st.qcirc_star = qstar;
+    st.qconv = lv.qconv;
+    st.q_space = q_space;
+    if (mode == 2) p.ext_phi[g] = phi0;  // for the engine's next call, read once this kernel is done
+  }
 }
 
 // k_field1: level n of one gap per workgroup, for grids up to FIELD1_NMAX
 // cells: the nodal density (the accumulator cleared for the next push), the
 // prefix sums S_k, the circuit and the surface charge, the half-grid field and
 // the push's gather table.
-__global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, double tol,
-                                                int maxit, int fp64) {
+// BS threads hold NQ nodes each: the fewest waves that keep a thread's share
+// small.  Bound by latency: every wave repeats the scan's sums over the waves, and
+// the waves of a SIMD take turns at them (for 600 cells, 16 waves took 1.7 us over
+// the scan, four take 0.6); the barriers wait for LDS alone, as waiting for the
+// density's stores cost another 0.5 us.
+// MLP: strict steps that start Newton from the guess network (a variant of its
+// own, so that the weights' loads stand in no branch, where they would be waited
+// for)
+template <int BS, int NQ, bool MLP>
+__global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, double tol, int maxit, int fp64) {
   const int g = blockIdx.x, tid = threadIdx.x;
   extern __shared__ __align__(16) double Sk[];  // S_k, one per cell (padded, see the prefix sums)
   // the gap's constants, state and last push's tallies, staged as one block
@@ -627,60 +735,64 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
   GapConst &sc = stg.c;
   GapState &ss = stg.s;
   unsigned long long *s_tally = stg.tally;
-  __shared__ double wsum[FBS / 64], wsum2[FBS / 64];
-  __shared__ double s_sigma, s_rhoN;
-  __shared__ double s_work[8 * MAXM + 8];
+  __shared__ double wsum[BS / 64], wsum2[BS / 64];
+  __shared__ double s_rhoN;
+  __shared__ Level s_lv;
   __shared__ float s_x[MLP_IN], s_h0[MLP_H], s_h1[MLP_H], s_y[MLP_OUT];
   __shared__ double s_ue[MAXM + 1], s_mu[MAXM + 1];
-  // the first FBS x AV0 nodes of the push's charge accumulator, loaded before
-  // anything else (nothing in this kernel writes them before the density pass),
-  // from clamped indices and masked afterwards: a guarded load would be waited
-  // for before the next is issued
+  // the nodes of the push's charge accumulator, loaded before anything else
+  // (nothing in this kernel writes them before the density pass), from clamped
+  // indices: a guarded load would be waited for before the next is issued
   // (secondary emission is complete when this kernel runs: the emission kernel
   // ran after the push)
-  constexpr int AV0 = 5;
-  unsigned long long av0[AV0];
+  unsigned long long av[NQ];
   {
     const int n0 = p.gc[g].N;
     const unsigned long long *a0 = p.acc + p.gc[g].nbase;
 #pragma unroll
-    for (int q = 0; q < AV0; ++q) av0[q] = a0[min(tid + q * FBS, n0)];
-#pragma unroll
-    for (int q = 0; q < AV0; ++q)
-      if (tid + q * FBS > n0) av0[q] = 0ull;
+    for (int q = 0; q < NQ; ++q) av[q] = a0[min(tid + q * BS, n0)];
   }
   // the coming push's tile pool starts empty
   if (g == 0 && tid == 0) *p.steal = 0u;
-  // stage the gap's constants, state and last push's tallies: word tid of
-  // their concatenation per thread, one load and one LDS store with no branch;
-  // the tallies are cleared at the kernel's end
+  // stage the gap's constants, state and last push's tallies: the words of
+  // their concatenation, a few per thread, loaded with no branch; the tallies
+  // are cleared at the kernel's end
   {
     constexpr int NC = (int)(sizeof(GapConst) / 8), NS = (int)(sizeof(GapState) / 8);
     constexpr int NW = (int)(sizeof(Staged) / 8);
-    static_assert(sizeof(Staged) == sizeof(GapConst) + sizeof(GapState) + 8 * (T_N + 2) && NW <= FBS,
-                  "one staged word per thread");
-    const unsigned long long *src =
-        tid < NC ? (const unsigned long long *)&p.gc[g] + tid
-        : tid < NC + NS ? (const unsigned long long *)&p.gs[g] + (tid - NC)
-        : tid < NC + NS + T_N ? p.tally + (size_t)g * T_N + (tid - NC - NS)
-                              : p.next_count + (size_t)g * 2 + min(tid - NC - NS - T_N, 1);
-    const unsigned long long v = *src;
-    if (tid < NW) ((unsigned long long *)&stg)[tid] = v;
+    static_assert(sizeof(Staged) == sizeof(GapConst) + sizeof(GapState) + 8 * (T_N + 2), "no padding");
+    constexpr int WPT = (NW + BS - 1) / BS;
+    unsigned long long v[WPT];
+#pragma unroll
+    for (int q = 0; q < WPT; ++q) {
+      const int w = tid + q * BS;
+      const unsigned long long *src =
+          w < NC ? (const unsigned long long *)&p.gc[g] + w
+          : w < NC + NS ? (const unsigned long long *)&p.gs[g] + (w - NC)
+          : w < NC + NS + T_N ? p.tally + (size_t)g * T_N + (w - NC - NS)
+                              : p.next_count + (size_t)g * 2 + min(w - NC - NS - T_N, 1);
+      v[q] = *src;
+    }
+#pragma unroll
+    for (int q = 0; q < WPT; ++q)
+      if (tid + q * BS < NW) ((unsigned long long *)&stg)[tid + q * BS] = v[q];
   }
-  __syncthreads();
-  long long nbeam;
-  {
-    const long long n = ss.level + 1;
-    int lane0 = 0;
-    asm volatile("" : "+v"(lane0));
-    const long long ix = sc.sched_len > 0 ? sc.sched_base + min(n, sc.sched_len - 1) : 0;
-    const long long v = (long long)p.sched[ix + lane0];
-    nbeam = n < sc.sched_len ? v : sc.beam_n;
+  // (the guess network's weights on their way before the first barrier)
+  constexpr bool want_mlp = MLP;
+  MlpWeights<BS> mw;
+  if (MLP) mw.load(p.mlp_w);
+  lds_barrier();
+  // the level's part that does not wait for the space charge: the last wave (on
+  // grids that leave it nodes to do, it does those after the others)
+  const bool circuit_wave = tid >= BS - 64;
+  long long sched = 0;
+  if (circuit_wave) {
+    sched = level_sched(p, sc, ss);  // (used at the level's end)
+    level_begin(p, g, sc, ss, mode, s_lv, s_tally);
   }
 
   // 0. strict coupling: the guess network's input (the last 8 levels from the
   //    history ring), recorded for training and/or evaluated for the guess
-  const bool want_mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
   const bool want_rec = mode == 0 && p.rec_x != nullptr;
   const long long rec_idx = (ss.level + 1 - p.rec_level0) * (long long)gridDim.x + g;
   const bool rec_here = want_rec && rec_idx >= 0 && rec_idx < p.rec_cap;
@@ -706,7 +818,7 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
     if (tid == 0)
       for (int i = 0; i <= sc.M; ++i) s_ue[i] = 3.0 * ss.uh[0][i] - 3.0 * ss.uh[1][i] + ss.uh[2][i];
     if (want_mlp) {
-      mlp_eval_block(p.mlp_w, s_x, s_h0, s_h1, s_y);
+      mw.eval(s_x, s_h0, s_h1, s_y);
       if (tid == 0)
         for (int i = 0; i < MLP_OUT; ++i)
           s_mu[i] = s_ue[i] + p.mlp_norm[2 * MLP_IN + i] + p.mlp_norm[2 * MLP_IN + MLP_OUT + i] * (double)s_y[i];
@@ -714,35 +826,22 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
   }
 
   const int N = sc.N;
-  const double dx = sc.dx, eps0 = sc.eps0, s0 = sc.s0;
+  const double dx = sc.dx, eps0 = sc.eps0, s0 = sc.s0, rdx = sc.rdx, reps0 = sc.reps0;
   unsigned long long *acc = p.acc + sc.nbase;
   double *rho = p.rho64 + sc.nbase;
   double *E = p.E64 + sc.nbase;
 
   // 1. nodal density of level n (to global rho and, as the cell terms of the
   //    prefix sums, to LDS); the accumulator is cleared for the next push.
-  //    The rest of the thread's nodes are loaded before any clearing store:
-  //    loads and stores share one counter, so a load issued after a store would
-  //    wait for it too.
-  const int ch = (N + FBS - 1) / FBS;  // cells per thread in the prefix sums below
-  // floor(k / ch) = (k * ceil(2^32 / ch)) >> 32 for every k here (k <= 16384 + FBS)
-  const unsigned long long chm = (4294967296ull + (unsigned long long)ch - 1ull) / (unsigned long long)ch;
-  auto pad = [&](int k) { return k + (int)(((unsigned long long)k * chm) >> 32); };
-  // (the nodes past the first FBS x AV0 only when the grid has them: the
-  // condition is the workgroup's, and a load nobody needs still costs a round
-  // trip)
-  unsigned long long av[FNQ];
+  const int ch = (N + BS - 1) / BS;  // cells per thread in the prefix sums below
+  // floor(k / ch) = (k * ceil(2^32 / ch)) >> 32 for every k here (k <= 8192 + BS)
+  const unsigned int chm = ch == 1 ? 0u : (unsigned int)((4294967296ull + (unsigned long long)ch - 1ull) / (unsigned long long)ch);
+  auto pad = [&](int k) { return k + (ch == 1 ? k : (int)__umulhi((unsigned int)k, chm)); };
 #pragma unroll
-  for (int q = 0; q < AV0; ++q) av[q] = av0[q];
-  if (N >= AV0 * FBS) {
-#pragma unroll
-    for (int q = AV0; q < FNQ; ++q) av[q] = acc[min(tid + q * FBS, N)];
-  }
-#pragma unroll
-  for (int q = 0; q < FNQ; ++q) {
-    const int k = tid + q * FBS;
+  for (int q = 0; q < NQ; ++q) {
+    const int k = tid + q * BS;
     if (k > N) break;
-    const double r = node_rho(s0, dx, av[q], k, N, fp64);
+    const double r = node_rho(s0, dx, rdx, av[q], k, N, fp64);
     rho[k] = r;
     acc[k] = 0ull;
     if (k < N)
@@ -750,7 +849,7 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
     else
       s_rhoN = r;
   }
-  __syncthreads();
+  lds_barrier();
   // prefix sums S_k = dx rho_0/2 + dx sum_{1..k} rho_j over contiguous chunks
   // of ch cells per thread (cell k at LDS index k + k / ch: a chunk's stride
   // of ch + 1 doubles spreads a wave's lanes over the LDS banks, where a
@@ -759,48 +858,53 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
   // k0 + i of thread tid sits at LDS index k0 + i + tid)
   const int k0 = min(tid * ch, N), k1 = min(k0 + ch, N);
   const int nk = k1 - k0;
-  double cv[FNQ];
+  double cv[NQ];
 #pragma unroll
-  for (int i = 0; i < FNQ; ++i) cv[i] = i < nk ? Sk[k0 + i + tid] : 0.0;
+  for (int i = 0; i < NQ; ++i) cv[i] = i < nk ? Sk[k0 + i + tid] : 0.0;
   // with sum_k S_k = sum_j c_j (N - j) (c_j the cell terms) taken in the same
   // reduction as the scan's wave totals
   double loc = 0.0, wloc = 0.0;
 #pragma unroll
-  for (int i = 0; i < FNQ; ++i)
+  for (int i = 0; i < NQ; ++i)
     if (i < nk) {
       loc += cv[i];
       wloc += cv[i] * (double)(N - (k0 + i));
     }
   double tot, sumS;
-  double run = block_exclusive_scan_sum_w(loc, wloc, wsum, wsum2, &tot, &sumS);
+  double run = block_exclusive_scan_sum_w<BS / 64>(loc, wloc, wsum, wsum2, &tot, &sumS);
 #pragma unroll
-  for (int i = 0; i < FNQ; ++i)
+  for (int i = 0; i < NQ; ++i)
     if (i < nk) {
       run += cv[i];
       Sk[k0 + i + tid] = run;
     }
   const double P = sumS * dx / eps0;
 
-  // 2. circuit and surface charge
-  if (tid == 0) {
-    double sg;
+  // 2. circuit and surface charge (the scan's barriers have published level_begin)
+  const bool newton = mode == 0 && guess != GS_GUESS_DIRECT;
+  if (newton) {
+    if (circuit_wave) level_newton(p, sc, ss, s_lv, P, guess, tol, maxit, want_mlp ? s_mu : nullptr);
+    lds_barrier();
+  }
+  double phi0, sigma, qcirc;
+  level_solve(sc, ss, s_lv, P, mode, newton, &phi0, &sigma, &qcirc);
+  const double rhoN = s_rhoN;
+  // (level_end rewrites what level_solve reads)
+  lds_barrier();
+  if (circuit_wave) {
+    level_counts(p, g, sc, ss, s_tally, stg.next_count, sched);
     // space charge: the cell terms (rho_0 at half weight) plus the half cell at node N
-    ss.q_space = sc.A * (tot + 0.5 * dx * s_rhoN);
-    solve_level(p, g, sc, ss, P, mode, guess, tol, maxit, &sg, s_work, s_tally, want_mlp ? s_mu : nullptr,
-                stg.next_count, nbeam);
-    s_sigma = sg;
-    if (rec_here)
+    level_end(p, g, sc, ss, s_lv, mode, newton, phi0, sigma, qcirc, sc.A * (tot + 0.5 * dx * rhoN));
+    wave_lds_sync();
+    if (rec_here && tid == BS - 64)
       for (int i = 0; i < MLP_OUT; ++i)
         p.rec_y[rec_idx * MLP_OUT + i] = i <= sc.M ? (float)(ss.uh[0][i] - s_ue[i]) : 0.0f;
   }
-  __syncthreads();
 
   // 3. half-grid field E_{k+1/2} = (sigma + S_k) / eps0 and the gather table
-  const double sigma = s_sigma;
-  const double rhoN = s_rhoN;
   const size_t eb = (size_t)sc.ebase;
-  for (int k = tid; k < N; k += FBS) {
-    const double e = (sigma + Sk[pad(k)]) / eps0;
+  for (int k = circuit_wave ? N : tid; k < N; k += BS - 64) {
+    const double e = div_by(sigma + Sk[pad(k)], eps0, reps0);
     E[k] = e;
     if (fp64)
       ((double *)p.ehat)[eb + k + 1] = e;
@@ -822,11 +926,11 @@ __global__ __launch_bounds__(FBS) void k_field1(DevPtrs p, int mode, int guess, 
     else
       ((float *)p.ehat)[eb] = (float)e0;
   }
-  __syncthreads();
+  lds_barrier();
   {
     const unsigned long long *a = (const unsigned long long *)&ss;
     unsigned long long *b = (unsigned long long *)&p.gs[g];
-    for (int i = tid; i < (int)(sizeof(GapState) / 8); i += FBS) b[i] = a[i];
+    for (int i = tid; i < (int)(sizeof(GapState) / 8); i += BS) b[i] = a[i];
   }
   if (tid < T_N) p.tally[(size_t)g * T_N + tid] = 0ull;
 }
@@ -847,7 +951,7 @@ __global__ __launch_bounds__(FDB) void k_fdens(DevPtrs p, int fp64) {
   unsigned long long *acc = p.acc + gc.nbase;
   double *rho = p.rho64 + gc.nbase;
   double *sl = p.fsl + gc.nbase;
-  const double dx = gc.dx, s0 = gc.s0;
+  const double dx = gc.dx, s0 = gc.s0, rdx = gc.rdx;
   // (loads from clamped indices, all issued before the first is used)
   unsigned long long a[4];
 #pragma unroll
@@ -857,7 +961,7 @@ __global__ __launch_bounds__(FDB) void k_fdens(DevPtrs p, int fp64) {
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int k = kb + i;
-    const double r = node_rho(s0, dx, a[i], k, N, fp64);
+    const double r = node_rho(s0, dx, rdx, a[i], k, N, fp64);
     cv[i] = k < N ? (k == 0 ? dx * r / 2.0 : dx * r) : 0.0;
     loc += cv[i];
     wloc += cv[i] * (double)(N - k);
@@ -867,7 +971,7 @@ __global__ __launch_bounds__(FDB) void k_fdens(DevPtrs p, int fp64) {
     }
   }
   double tot, wtot;
-  double run = block_exclusive_scan_sum_w(loc, wloc, wsum, wsum2, &tot, &wtot);
+  double run = block_exclusive_scan_sum_w<FDB / 64>(loc, wloc, wsum, wsum2, &tot, &wtot);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     run += cv[i];
@@ -899,7 +1003,7 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
   GapConst &sc = stg.c;
   GapState &ss = stg.s;
   unsigned long long *s_tally = stg.tally;
-  __shared__ double s_work[8 * MAXM + 8];
+  __shared__ Level s_lv;
   __shared__ float s_x[MLP_IN], s_h0[MLP_H], s_h1[MLP_H], s_y[MLP_OUT];
   __shared__ double s_ue[MAXM + 1], s_mu[MAXM + 1];
   // (secondary emission is complete when this kernel runs: the emission kernel
@@ -935,27 +1039,20 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
     const unsigned long long v = *src;
     if (tid < NW) ((unsigned long long *)&stg)[tid] = v;
   }
-  __syncthreads();
-  // the beam of the step that solves level n = level + 1: its schedule entry,
-  // else the fixed count
-  // (read from a clamped index and chosen afterwards, through an index the
-  // compiler takes for a per-lane one: a load on each side of the choice would
-  // become one flat load, and a uniform one a scalar load, either of which every
-  // later barrier's wait on LDS would also wait for; the schedule array holds
-  // at least one entry)
-  long long nbeam;
-  {
-    const long long n = ss.level + 1;
-    int lane0 = 0;
-    asm volatile("" : "+v"(lane0));
-    const long long ix = sc.sched_len > 0 ? sc.sched_base + min(n, sc.sched_len - 1) : 0;
-    const long long v = (long long)p.sched[ix + lane0];
-    nbeam = n < sc.sched_len ? v : sc.beam_n;
+  const bool want_mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
+  MlpWeights<FBS> mw;
+  if (want_mlp) mw.load(p.mlp_w);
+  lds_barrier();
+  // (the second wave, while the first sums the chunks)
+  const bool circuit_wave = tid >= 64 && tid < 128;
+  long long sched = 0;
+  if (circuit_wave) {
+    sched = level_sched(p, sc, ss);  // (used at the level's end)
+    level_begin(p, g, sc, ss, mode, s_lv, s_tally);
   }
 
   // 0. strict coupling: the guess network's input (the last 8 levels from the
   //    history ring), recorded for training and/or evaluated for the guess
-  const bool want_mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
   const bool want_rec = mode == 0 && p.rec_x != nullptr;
   const long long rec_idx = (ss.level + 1 - p.rec_level0) * (long long)gridDim.x + g;
   const bool rec_here = want_rec && rec_idx >= 0 && rec_idx < p.rec_cap;
@@ -981,19 +1078,14 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
     if (tid == 0)
       for (int i = 0; i <= sc.M; ++i) s_ue[i] = 3.0 * ss.uh[0][i] - 3.0 * ss.uh[1][i] + ss.uh[2][i];
     if (want_mlp) {
-      mlp_eval_block(p.mlp_w, s_x, s_h0, s_h1, s_y);
+      mw.eval(s_x, s_h0, s_h1, s_y);
       if (tid == 0)
         for (int i = 0; i < MLP_OUT; ++i)
           s_mu[i] = s_ue[i] + p.mlp_norm[2 * MLP_IN + i] + p.mlp_norm[2 * MLP_IN + MLP_OUT + i] * (double)s_y[i];
     }
   }
 
-  const int N = sc.N;
-  const double dx = sc.dx, eps0 = sc.eps0, s0 = sc.s0;
-  unsigned long long *acc = p.acc + sc.nbase;
-  double *rho = p.rho64 + sc.nbase;
-  double *E = p.E64 + sc.nbase;
-
+  __shared__ double s_tot, s_wsum, s_rhoN;
   // 1. the chunks' offsets O_c (exclusive prefix of their totals) for
   //    k_ftable, the total S_{N-1} and sum_k S_k = sum_k c_k (N - k)
   if (tid < 64) {
@@ -1008,27 +1100,40 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
     for (int o = 32; o > 0; o >>= 1) wsumall += __shfl_xor(wsumall, o, 64);
     const double tot = __shfl(run, 63, 64);
     if (tid < nch) p.foff[(size_t)g * NCHMAX + tid] = run - ptot;
-    // 2. circuit and surface charge
     if (tid == 0) {
-      const double dx = sc.dx, eps0 = sc.eps0;
-      const double P = wsumall * dx / eps0;
-      double sg;
-      // space charge: the cell terms (rho_0 at half weight) plus the half cell at node N
-      ss.q_space = sc.A * (tot + 0.5 * dx * rhoN);
-      solve_level(p, g, sc, ss, P, mode, guess, tol, maxit, &sg, s_work, s_tally, want_mlp ? s_mu : nullptr,
-                  stg.next_count, nbeam);
-      p.fsig[g] = sg;
-      const size_t eb = (size_t)sc.ebase;
-      if (fp64)
-        ((double *)p.ehat)[eb] = sg / eps0;
-      else
-        ((float *)p.ehat)[eb] = (float)(sg / eps0);
-      if (rec_here)
-        for (int i = 0; i < MLP_OUT; ++i)
-          p.rec_y[rec_idx * MLP_OUT + i] = i <= sc.M ? (float)(ss.uh[0][i] - s_ue[i]) : 0.0f;
+      s_tot = tot;
+      s_wsum = wsumall;
     }
   }
-  __syncthreads();
+  if (tid == 0) s_rhoN = rhoN;
+  lds_barrier();
+  // 2. circuit and surface charge
+  if (circuit_wave) {
+    const double dx = sc.dx, eps0 = sc.eps0;
+    const double P = s_wsum * dx / eps0;
+    const bool newton = mode == 0 && guess != GS_GUESS_DIRECT;
+    if (newton) level_newton(p, sc, ss, s_lv, P, guess, tol, maxit, want_mlp ? s_mu : nullptr);
+    wave_lds_sync();
+    double phi0, sigma, qcirc;
+    level_solve(sc, ss, s_lv, P, mode, newton, &phi0, &sigma, &qcirc);
+    wave_lds_sync();
+    if (tid == 64) {
+      p.fsig[g] = sigma;
+      const size_t eb = (size_t)sc.ebase;
+      if (fp64)
+        ((double *)p.ehat)[eb] = sigma / eps0;
+      else
+        ((float *)p.ehat)[eb] = (float)(sigma / eps0);
+    }
+    level_counts(p, g, sc, ss, s_tally, stg.next_count, sched);
+    // space charge: the cell terms (rho_0 at half weight) plus the half cell at node N
+    level_end(p, g, sc, ss, s_lv, mode, newton, phi0, sigma, qcirc, sc.A * (s_tot + 0.5 * dx * s_rhoN));
+    wave_lds_sync();
+    if (rec_here && tid == 64)
+      for (int i = 0; i < MLP_OUT; ++i)
+        p.rec_y[rec_idx * MLP_OUT + i] = i <= sc.M ? (float)(ss.uh[0][i] - s_ue[i]) : 0.0f;
+  }
+  lds_barrier();
   {
     const unsigned long long *a = (const unsigned long long *)&ss;
     unsigned long long *b = (unsigned long long *)&p.gs[g];
@@ -1059,7 +1164,7 @@ __global__ __launch_bounds__(FDB) void k_ftable(DevPtrs p, int fp64) {
   for (int i = 0; i < 4; ++i) {
     const int k = kb + i;
     if (k >= N) break;
-    const double e = (sigma + (off + L[i])) / eps0;
+    const double e = div_by(sigma + (off + L[i]), eps0, gc.reps0);
     E[k] = e;
     if (fp64)
       ((double *)p.ehat)[eb + k + 1] = e;
@@ -2915,21 +3020,40 @@ size_t push_lds_bytes(int nmax, int fp64, int G, int wide) {
   return off;
 }
 
+template <int BS, int NQ, bool MLP>
+static hipError_t field1_m(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit, int fp64, int nmax,
+                           hipStream_t s, KTime t) {
+  // S_k of every cell, padded by one double per chunk of the prefix sums
+  // (index k + k / ch < N + BS)
+  const size_t lds = ((size_t)nmax + (size_t)BS + 1) * 8;
+  static size_t attr_set = 32768;
+  if (lds > attr_set) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_field1<BS, NQ, MLP>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    attr_set = lds;
+  }
+  return launch_k(k_field1<BS, NQ, MLP>, dim3(G), dim3(BS), lds, s, t.a, t.b, p, mode, guess, tol, maxit, fp64);
+}
+
+template <int BS, int NQ>
+static hipError_t field1_t(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit, int fp64, int nmax,
+                           hipStream_t s, KTime t) {
+  const bool mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
+  return mlp ? field1_m<BS, NQ, true>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t)
+             : field1_m<BS, NQ, false>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+}
+
 hipError_t launch_field(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit,
                         int fp64, int nmax, hipStream_t s, KTime t) {
-  if (nmax <= FIELD1_NMAX) {
-    // S_k of every cell, padded by one double per chunk of the prefix sums
-    // (index k + k / ch < N + FBS)
-    const size_t lds = ((size_t)nmax + (size_t)FBS + 1) * 8;
-    static size_t attr_set = 32768;
-    if (lds > attr_set) {
-      hipError_t e = hipFuncSetAttribute((const void *)k_field1, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds);
-      if (e != hipSuccess) return e;
-      attr_set = lds;
-    }
-    return launch_k(k_field1, dim3(G), dim3(FBS), lds, s, t.a, t.b, p, mode, guess, tol, maxit, fp64);
-  }
+  // the fewest threads that keep a thread's nodes few, by the largest grid: at
+  // 600 cells 256 threads take 5.7 us where 1024 took 8.3, at 4096 cells 512 take
+  // 7.6 and 1024 8.9 (10 with the circuit between scan and table)
+  if (nmax < 3 * 256) return field1_t<256, 3>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  if (nmax < 6 * 256) return field1_t<256, 6>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  if (nmax < 5 * 512) return field1_t<512, 5>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  if (nmax < 9 * 512) return field1_t<512, 9>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  if (nmax <= FIELD1_NMAX) return field1_t<1024, 9>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
   // events (when timing) on the first and the last of the three launches
   const dim3 chunks((unsigned)(nmax / FCN + 1), (unsigned)G);
   hipError_t e = launch_k(k_fdens, chunks, dim3(FDB), 0, s, t.a, nullptr, p, fp64);

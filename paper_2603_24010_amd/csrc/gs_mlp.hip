@@ -143,7 +143,7 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
       st[r * MLP_OUT + f - MLP_IN] = t[i * MLP_OUT + f - MLP_IN];
     }
   }
-  __syncthreads();
+  lds_barrier();
   // a hidden layer's epilogue: bias, GELU to LDS and the workspace, GELU' to LDS
   v4f acc[MB];
   auto hidden = [&](const float *bias, float *out, float *g, float *global) {
@@ -163,15 +163,15 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
   mul_block<MB, MLP_IN>(A0, w1, acc);
   load_fwd<MLP_H>(W3, n0, wb);
   hidden(th + MLP_OFF_B1, A1, G1, o.a1);
-  __syncthreads();
+  lds_barrier();
   mul_block<MB, MLP_H>(A1, wa, acc);
   load_bwd(W3, n0, wa);
   hidden(th + MLP_OFF_B2, A0, G2, o.a2);
-  __syncthreads();
+  lds_barrier();
   mul_block<MB, MLP_H>(A0, wb, acc);
   load_bwd(W2, n0, wb);
   hidden(th + MLP_OFF_B3, A1, G3, o.a3);
-  __syncthreads();
+  lds_barrier();
   // the output layer: eight lanes per output, sixteen inputs each
   const float inv = 1.0f / (float)(B * MLP_OUT);
   for (int e = tid; e < R * MLP_OUT * 8; e += TRT) {
@@ -190,7 +190,7 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
       if (in) o.dy[(size_t)(r0 + r) * MLP_OUT + u] = 2.0f * d * inv;
     }
   }
-  __syncthreads();
+  lds_barrier();
   if (wv == 0) {
     float s = 0.0f;
     for (int e = tid; e < R * MLP_OUT; e += 64) s += se[e];
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
     A0[r * TLD + k] = s;
     if (r0 + r < B) o.d3[(size_t)(r0 + r) * MLP_H + k] = s;
   }
-  __syncthreads();
+  lds_barrier();
   auto back = [&](float *out, const float *g, float *global) {
 #pragma unroll
     for (int m = 0; m < MB; ++m)
@@ -222,7 +222,7 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
   };
   mul_block<MB, MLP_H>(A0, wa, acc);
   back(A1, G2, o.d2);
-  __syncthreads();
+  lds_barrier();
   mul_block<MB, MLP_H>(A1, wb, acc);
   back(nullptr, G1, o.d1);
 }
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(UPT) void k_train_update(TrainRows o, int B, int nt
     part[wv][(4 * q + i) * 16 + c] = acc[i];
     if (c == 0) partb[wv][4 * q + i] = accb[i];
   }
-  __syncthreads();
+  lds_barrier();
   if (tid < 256) {
     const int j = j0 + tid / 16, k = k0 + tid % 16;
     if (j < J) {
@@ -317,15 +317,15 @@ __global__ __launch_bounds__(UPT) void k_train_update(TrainRows o, int B, int nt
     }
   }
   if (blockIdx.x == 0 && loss) {
-    __syncthreads();
+    lds_barrier();
     float *red = &part[0][0];  // [UPT]
     float s = 0.0f;
     for (int e = tid; e < ntiles; e += UPT) s += o.loss[e];
     red[tid] = s;
-    __syncthreads();
+    lds_barrier();
     for (int k = UPT / 2; k > 0; k >>= 1) {
       if (tid < k) red[tid] += red[tid + k];
-      __syncthreads();
+      lds_barrier();
     }
     if (tid == 0) *loss = red[0] * (1.0f / (float)(B * MLP_OUT));
   }
@@ -351,8 +351,10 @@ __global__ __launch_bounds__(UPT) void k_train_update(TrainRows o, int B, int nt
 __global__ __launch_bounds__(256) void k_mlp_forward(const uint16_t *W, const float *x, float *y) {
   __shared__ float s_x[MLP_IN], s_h0[MLP_H], s_h1[MLP_H], s_y[MLP_OUT];
   const long b = blockIdx.x;
+  MlpWeights<256> mw;
+  mw.load(W);
   if (threadIdx.x < MLP_IN) s_x[threadIdx.x] = x[b * MLP_IN + threadIdx.x];
-  mlp_eval_block(W, s_x, s_h0, s_h1, s_y);
+  mw.eval(s_x, s_h0, s_h1, s_y);
   if (threadIdx.x < MLP_OUT) y[b * MLP_OUT + threadIdx.x] = s_y[threadIdx.x];
 }
 
@@ -465,14 +467,14 @@ __global__ __launch_bounds__(FTT, 4) void k_mlp_tiles(const uint16_t *W, const f
       for (int r = 0; r < 4; ++r) v[r] = gelu_f32(acc[m][r] + bias[r]);
       put(dst, 16 * m + c, o0 + 4 * q, v);
     }
-    __syncthreads();
+    lds_barrier();
   };
   float xv[4];
   if ((long long)blockIdx.x < tiles) load_x(blockIdx.x, xv);
   for (long long t = blockIdx.x; t < tiles; t += gridDim.x) {
     put(buf[0], tid >> 4, 4 * (tid & 15), xv);
     if (t + gridDim.x < tiles) load_x(t + gridDim.x, xv);
-    __syncthreads();
+    lds_barrier();
     tile_layer<2>(buf[0], w1, acc);
     hidden(buf[1], b1);
     tile_layer<4>(buf[1], w2, acc);
