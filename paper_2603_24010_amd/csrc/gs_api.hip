@@ -261,6 +261,10 @@ static gs_status build_const(gs_ctx *ctx, int g, const gs_gap_params &p, GapCons
   c.s0 = p.weight * p.q_unit;
   c.rdx = 1.0 / c.dx;
   c.reps0 = 1.0 / c.eps0;
+  c.rdt = 1.0 / c.dt;
+  c.rev = 1.0 / p.ev;
+  c.rE0 = 1.0 / p.see_E0_eV;
+  for (int s = 0; s < 2; ++s) c.rmass[s] = 1.0 / p.mass[s];
   for (int s = 0; s < 2; ++s) {
     // velocity change (cells per step) per V/m: Z q dt^2 / (m dx)
     c.alpha[s] = ((double)p.Z[s] * p.q_unit) * p.dt * p.dt / (p.mass[s] * c.dx);
@@ -485,6 +489,7 @@ static gs_status setup(gs_ctx *ctx) {
   ALLOC(d.push_done, unsigned int *, 33 * 128);
   ALLOC(d.gc, const GapConst *, sizeof(GapConst) * (size_t)G);
   ALLOC(d.gs, GapState *, sizeof(GapState) * (size_t)G);
+  ALLOC(d.head, PushHead *, sizeof(PushHead) * (size_t)G);
 #undef ALLOC
   d.mlp_w = nullptr;
   d.mlp_norm = nullptr;
@@ -529,6 +534,7 @@ static gs_status setup(gs_ctx *ctx) {
   ctx->lc.sort_bin = 0;
   ctx->lc.steal = 0;
   ctx->lc.stream = 0;
+  ctx->lc.min_wgs = 0;
   ctx->lc.masks = 0;
   ctx->lc.lists = 0;
   choose_launch(ctx);
@@ -554,6 +560,10 @@ static void choose_launch(gs_ctx *ctx) {
   const int per_cu_lds = (int)std::max<size_t>(1, lds_cap / lds);
   const int per_cu_thr = std::max(1, 2048 / ctx->lc.block);
   if (!ctx->grid_opt) ctx->lc.grid = std::max(1, ctx->ncu * std::min(per_cu_lds, per_cu_thr));
+  int64_t tiles = 0;
+  for (const GapConst &c : ctx->hc)
+    for (int s = 0; s < 2; ++s) tiles += c.cap[s] / ctx->lc.tile + 1;
+  ctx->lc.max_wgs = (int)std::min<int64_t>(tiles, 1 << 30);
 }
 
 static bool launch_fits(const gs_ctx *ctx) {
@@ -787,6 +797,7 @@ static hipError_t launch_push_emit(gs_ctx *ctx, hipStream_t s, bool timing, bool
   if (ctx->lc.sort_bin > 0) dp.ovf_wgs = 0;
   LaunchCfg lc = ctx->lc;
   lc.masks = masks && lc.sort_bin == 0;
+  lc.min_wgs = ctx->grid_opt ? lc.grid : ctx->ncu;
   const bool listed = ctx->list_hint && *ctx->list_hint != 0ull;
   lc.lists = ctx->emits && lc.sort_bin == 0 && lc.grid < 65536 && !listed;
   auto push = [&](KTime t) { return launch_push(dp, ctx->G, lc, s, t); };

@@ -51,7 +51,8 @@ struct GapConst {
                       // (room for ceil(N / SORT_BIN_MIN) bins per species)
   uint64_t seed;
   double d, dx, A, eps0, dt, cgap, c_par;
-  double rdx, reps0;   // 1 / dx, 1 / eps0
+  double rdx, reps0;   // reciprocals (see div_by): 1 / dx, 1 / eps0,
+  double rdt, rev, rE0, rmass[2];  // 1 / dt, 1 / ev, 1 / see_E0, 1 / mass
   double s0;           // sheet charge per unit of Z: weight * q_unit [C/m^2]
   double alpha[2];     // Z q dt^2 / (m dx): velocity change in cells/step per V/m
   double mass[2], ev;
@@ -115,10 +116,25 @@ struct Event {
   uint32_t wall;
 };
 
+// What a push reads of a gap before and while it streams the particles, written
+// by the field solve: constants and the step's counts in two cache lines, so
+// that a workgroup starts after one round trip instead of one per structure.
+struct PushHead {
+  int64_t count[2];   // slots to sweep, per species
+  int64_t beam_now, beam_id0, level;
+  int64_t pbase[2], nbase, ebase, evbase, evcap;
+  double alpha[2];
+  int32_t N, Z[2];
+  int32_t see;        // absorbed ions free electrons
+  int64_t pad;
+};
+static_assert(sizeof(PushHead) == 128, "two cache lines");
+
 // Context-wide device pointers handed to kernels.
 struct DevPtrs {
   const GapConst *gc;
   GapState *gs;
+  PushHead *head;                  // [G]
   // particle slots, two buffers selected by compaction epoch parity
   void *X[2], *U[2];
   uint32_t *ID[2];
@@ -208,6 +224,8 @@ struct LaunchCfg {
                      // that workgroups done with their own draw from (0: none)
   int stream;        // push particle stream: STREAM_RR round-robin tile order,
                      // STREAM_NT non-temporal binary32 loads and stores
+  int max_wgs;       // tiles of the regions' slots: more push blocks would find nothing to do
+  int min_wgs;       // a single gap's push may use as few workgroups as this (see k_push)
   int masks;         // per launch: the push writes the live masks of the words
                      // below each region's count, and the compaction that follows
                      // takes them instead of reading those positions

@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstddef>
 #include <type_traits>
 
 #include "gs_internal.h"
@@ -37,14 +38,13 @@ __device__ inline void philox4x64_10(uint64_t c[4], uint64_t k0, uint64_t k1) {
   // kernel's instruction footprint matters more than its speed
 #pragma unroll 1
   for (int r = 0; r < 10; ++r) {
-    const uint64_t lo0 = M0 * c[0], hi0 = __umul64hi(M0, c[0]);
-    const uint64_t lo1 = M1 * c[2], hi1 = __umul64hi(M1, c[2]);
-    const uint64_t n0 = hi1 ^ c[1] ^ k0;
-    const uint64_t n2 = hi0 ^ c[3] ^ k1;
+    const unsigned __int128 p0 = (unsigned __int128)M0 * c[0], p1 = (unsigned __int128)M1 * c[2];
+    const uint64_t n0 = (uint64_t)(p1 >> 64) ^ c[1] ^ k0;
+    const uint64_t n2 = (uint64_t)(p0 >> 64) ^ c[3] ^ k1;
     c[0] = n0;
-    c[1] = lo1;
+    c[1] = (uint64_t)p1;
     c[2] = n2;
-    c[3] = lo0;
+    c[3] = (uint64_t)p0;
     k0 += W0;
     k1 += W1;
   }
@@ -64,10 +64,21 @@ __device__ inline void rng_block(uint64_t seed, uint64_t a, uint64_t b, uint64_t
   philox4x64_10(out, seed, 0);
 }
 
+// a / b with r = 1 / b: two Newton corrections of a r give the correctly rounded
+// quotient (in the normal range) in five operations, a fifth of the general
+// division's
+__device__ inline double div_by(double a, double b, double r) {
+  double q = a * r;
+  q = __builtin_fma(__builtin_fma(-q, b, a), r, q);
+  return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+
 // (not inlined: the constants of the exponential would otherwise be held in
 // registers across the whole push kernel)
-__device__ __attribute__((noinline)) int poisson_inverse(double lam, double u, int kmax) {
-  double p = exp(-lam);
+__device__ __attribute__((noinline)) double exp_of(double x) { return exp(x); }
+
+// the Poisson count of mean lam by inversion; p = exp(-lam)
+__device__ inline int poisson_inverse(double lam, double p, double u, int kmax) {
   double F = p;
   int k = 0;
   while (u > F && k < kmax) {
@@ -195,8 +206,26 @@ __device__ inline double block_sum_w(double v, double *wsum) {
   return all;
 }
 
-// wave-wide inclusive prefix sum (64 lanes)
-__device__ inline int wave_incl_scan(int v);
+// wave-wide inclusive prefix sum (64 lanes), by the DPP moves of wave_incl_scan_d;
+// every lane of the wave calls it
+template <int CTRL, int ROW_MASK, int BANK_MASK>
+__device__ inline int dpp_i(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, BANK_MASK, true);
+}
+
+__device__ inline int wave_incl_scan(int v) {
+  int y = v + dpp_i<0x111, 0xf, 0xf>(v) + dpp_i<0x112, 0xf, 0xf>(v) + dpp_i<0x113, 0xf, 0xf>(v);
+  y += dpp_i<0x114, 0xf, 0xe>(y);
+  y += dpp_i<0x118, 0xf, 0xc>(y);
+  y += dpp_i<0x142, 0xa, 0xf>(y);
+  y += dpp_i<0x143, 0xc, 0xf>(y);
+  return y;
+}
+
+// the wave's sum, the same in every lane
+__device__ inline unsigned int wave_sum(unsigned int a) {
+  return (unsigned int)__builtin_amdgcn_readlane(wave_incl_scan((int)a), 63);
+}
 
 // block-wide exclusive scan of ints from wave scans: two barriers (wsum: one
 // slot per wave)
@@ -216,30 +245,99 @@ __device__ inline int block_exclusive_scan_i(int v, int *wsum, int *total) {
   return before + incl - v;
 }
 
-__device__ inline int wave_incl_scan(int v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(v, o, 64);
-    if (lane >= o) v += t;
-  }
-  return v;
+// A gap's constants and push head as constant memory (nothing writes them while a
+// push or an emission runs): read with scalar loads.  Through an ordinary pointer,
+// past the kernel's first store the compiler must take vector loads, whose data
+// comes back behind every particle store the wave has under way.
+typedef const __attribute__((address_space(4))) GapConst ConstGap;
+__device__ inline ConstGap &const_gap(const DevPtrs &p, int g) {
+  return *(ConstGap *)(unsigned long long)(p.gc + g);
+}
+typedef const __attribute__((address_space(4))) PushHead ConstHead;
+__device__ inline ConstHead &const_head(const DevPtrs &p, int g) {
+  return *(ConstHead *)(unsigned long long)(p.head + g);
 }
 
-__device__ inline unsigned int wave_sum(unsigned int a) {
+__device__ inline PushHead load_head(const DevPtrs &p, int g) {
+  const ConstHead &h = const_head(p, g);
+  PushHead o;
+  for (int s = 0; s < 2; ++s) {
+    o.count[s] = h.count[s];
+    o.pbase[s] = h.pbase[s];
+    o.alpha[s] = h.alpha[s];
+    o.Z[s] = h.Z[s];
+  }
+  o.beam_now = h.beam_now;
+  o.beam_id0 = h.beam_id0;
+  o.level = h.level;
+  o.nbase = h.nbase;
+  o.ebase = h.ebase;
+  o.evbase = h.evbase;
+  o.evcap = h.evcap;
+  o.N = h.N;
+  o.see = h.see;
+  return o;
+}
+
+// The push kernel's pointers (its first argument), read where a part of it begins.
+// Held as ordinary values they are loaded at the kernel's start, one after the
+// other, and spilled: more of them than scalar registers, over a microsecond.
+template <class T>
+__device__ __forceinline__ void as_global(T *&q) {
+  q = (T *)(__attribute__((address_space(1))) T *)(unsigned long long)q;
+}
+__device__ __forceinline__ DevPtrs push_args() {
+  typedef const __attribute__((address_space(4))) unsigned long long Word;
+  Word *a = (Word *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  static_assert(sizeof(DevPtrs) % 8 == 0, "whole words");
+  unsigned long long w[sizeof(DevPtrs) / 8];
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-  return a;
+  for (int i = 0; i < (int)(sizeof(DevPtrs) / 8); ++i) w[i] = a[i];
+  DevPtrs p;
+  __builtin_memcpy(&p, w, sizeof p);
+  // (a pointer that was read from memory is a flat one until told otherwise)
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    as_global(p.X[b]);
+    as_global(p.U[b]);
+    as_global(p.ID[b]);
+  }
+  as_global(p.gc);
+  as_global(p.gs);
+  as_global(p.head);
+  as_global(p.next_count);
+  as_global(p.tally);
+  as_global(p.acc);
+  as_global(p.ehat);
+  as_global(p.err);
+  as_global(p.steal);
+  as_global(p.push_done);
+  as_global(p.ev);
+  as_global(p.ev_count);
+  as_global(p.ev_done);
+  as_global(p.live);
+  as_global(p.list_seen);
+  as_global(p.ovf);
+  return p;
+}
+
+// one of a pair by a run-time species or buffer (an index into a local struct would put it
+// on the stack)
+template <class T>
+__device__ inline T of_species(const T (&v)[2], int s) {
+  return s ? v[1] : v[0];
 }
 
 // Secondary emission (Alg. 2), in two parts.  see_count: an absorbed ion's
 // energy E = m v^2 / 2 from its impact velocity, the mean yield (saturating
 // a (E/E0) / (1 + E/E0), or a times the fifth-order fit clipped at zero) and
 // the Poisson count by inversion, drawn from the stream keyed by (level, ion
-// id); blk keeps the block for the energies.
-__device__ inline int see_count(const GapConst &c, long long level, uint32_t ion_id, double u_imp, uint64_t blk[4]) {
-  const double v_ion = (u_imp * c.dx) / c.dt;
-  const double e_ion = 0.5 * c.mass[1] * v_ion * v_ion / c.ev;
+// id); blk keeps the stream's first block for the energies.
+// (What does not need the id comes first: the id's load is under way.)
+__device__ inline int see_count(ConstGap &c, long long level, uint32_t ion_id, double u_imp, uint64_t blk[4]) {
+  const double v_ion = div_by(u_imp * c.dx, c.dt, c.rdt);
+  const double e_ion = div_by(0.5 * c.mass[1] * v_ion * v_ion, c.ev, c.rev);
   double lam;
   if (c.see_yield == GS_YIELD_POLY) {
     const double x = (e_ion < c.see_pEmax ? e_ion : c.see_pEmax) / 1000.0;
@@ -248,12 +346,13 @@ __device__ inline int see_count(const GapConst &c, long long level, uint32_t ion
     for (int j = 4; j >= 0; --j) f = f * x + c.see_poly[j];
     lam = c.see_amp * (f > 0.0 ? f : 0.0);
   } else {
-    const double rr = e_ion / c.see_E0;
+    const double rr = div_by(e_ion, c.see_E0, c.rE0);
     lam = c.see_amp * rr / (1.0 + rr);
   }
   if (lam < 0.0) lam = 0.0;
+  const double p0 = exp_of(-lam);
   rng_block(c.seed, (uint64_t)level, (uint64_t)ion_id, 1, 0, blk);
-  return poisson_inverse(lam, unit_open(blk[0]), c.see_max);
+  return poisson_inverse(lam, p0, unit_open(blk[0]), c.see_max);
 }
 
 // An emitted electron's energy [eV] from its one or two uniform draws: fixed,
@@ -269,45 +368,84 @@ __device__ __attribute__((noinline)) double see_energy(int law, double E, double
   return E;
 }
 
-// see_write: the ion's nk electrons, energies fixed, exponential or lognormal
-// (from the ion's stream words 1, 2, .. in order: one per electron, two for the
-// lognormal's normal draw), placed on the wall node with the inward speed of
-// their energy, in slots base.. of the electron region; counts per wall added
-// to n[0], n[1].
+// see_write: the electrons of one wave's ions (nk for each lane's, excl of them
+// before it in the wave), energies fixed, exponential or lognormal (from the
+// ion's stream words 1, 2, .. in order: one per electron, two for the lognormal's
+// normal draw), placed on the wall node with the inward speed of their energy, in
+// slots slot0.. of the electron region; counts per wall to n[0], n[1] (the wave's).
+// A lane per electron, not per ion: the draws are a chain of a microsecond or more
+// each, and the electrons of one ion would queue on its lane.  Every lane of the
+// wave calls it.
 template <class P>
-__device__ inline void see_write(const DevPtrs &p, const GapConst &c, long long level, int g, int sel,
-                                 uint32_t ion_id, int wall, int nk, uint64_t blk[4], unsigned long long base,
-                                 unsigned int n[2]) {
-  P *X = (P *)p.X[sel] + c.pbase[0];
-  P *U = (P *)p.U[sel] + c.pbase[0];
-  uint32_t *ID = p.ID[sel] + c.pbase[0];
-  const P xw = wall == 0 ? (P)0 : (P)c.N;
+__device__ inline void see_write(const DevPtrs &p, ConstGap &c, long long level, int g, int sel,
+                                 uint32_t ion_id, int wall, int nk, const uint64_t blk0[4], int excl,
+                                 unsigned long long slot0, unsigned int n[2]) {
+  const int lane = threadIdx.x & 63;
+  const int incl = excl + nk;
+  const int total = __builtin_amdgcn_readlane(incl, 63);
+  n[0] = n[1] = 0u;
   // one copy of each draw and function (cold code: its size is what costs)
   const int nw = c.see_law == GS_SEE_LOGNORMAL ? 2 : 1;
-  int w = 1;  // word 0 of block 0 drew the count
-  for (int e = 0; e < nk; ++e) {
-    double u[2] = {0.5, 0.5};
 #pragma unroll 1
-    for (int t = 0; t < nw; ++t) {
-      if ((w & 3) == 0) rng_block(c.seed, (uint64_t)level, (uint64_t)ion_id, 1, (uint64_t)(w >> 2), blk);
-      const double uw = unit_open(blk[w & 3]);
-      u[0] = t == 0 ? uw : u[0];
-      u[1] = t == 1 ? uw : u[1];
-      w += 1;
+  for (int e0 = 0; e0 < total; e0 += 64) {
+    const int e = e0 + lane;
+    // the ion: as many lanes' inclusive counts are at most e as lanes come before it
+    int own = 0;
+#pragma unroll
+    for (int b = 32; b > 0; b >>= 1)
+      if (__shfl(incl, own + b - 1, 64) <= e) own += b;
+    own = own < 63 ? own : 63;
+    const uint32_t id = (uint32_t)__shfl((int)ion_id, own, 64);
+    const int wl = __shfl(wall, own, 64);
+    const int k = e - __shfl(excl, own, 64);
+    const bool in = e < total;
+    const unsigned long long sl = slot0 + (unsigned long long)e;
+    // the electron's words: of the ion's first block, at hand on its lane, or, for
+    // an ion's later electrons, of another (a block is 0.8 us on a wave)
+    const int w0 = 1 + nw * k;  // word 0 of block 0 drew the count
+    uint64_t word[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int w = w0 + t;
+      const uint64_t v1 = __shfl((unsigned long long)blk0[1], own, 64);
+      const uint64_t v2 = __shfl((unsigned long long)blk0[2], own, 64);
+      const uint64_t v3 = __shfl((unsigned long long)blk0[3], own, 64);
+      word[t] = w == 1 ? v1 : w == 2 ? v2 : v3;
     }
-    const double E_se = see_energy(c.see_law, c.see_E, c.see_mu, c.see_sig, u[0], u[1]);
-    const double v_se = sqrt(2.0 * E_se * c.ev / c.mass[0]);
-    const double v_si = wall == 0 ? v_se : -v_se;
-    const unsigned long long sl = base + (unsigned long long)e;
-    if (sl >= (unsigned long long)c.cap[0]) {
-      atomicOr(&p.err[0], ERR_CAPACITY);
-      atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)g);
-      continue;
+    if (in && w0 + nw > 4) {
+      uint64_t blk[4] = {0, 0, 0, 0};
+      int at = 0;
+#pragma unroll 1
+      for (int t = 0; t < nw; ++t) {
+        const int w = w0 + t;
+        if ((w >> 2) != at) {
+          at = w >> 2;
+          rng_block(c.seed, (uint64_t)level, (uint64_t)id, 1, (uint64_t)at, blk);
+        }
+        if (at > 0) {
+          const uint64_t v = (w & 2) ? ((w & 1) ? blk[3] : blk[2]) : ((w & 1) ? blk[1] : blk[0]);
+          word[0] = t == 0 ? v : word[0];
+          word[1] = t == 1 ? v : word[1];
+        }
+      }
     }
-    X[sl] = xw;
-    U[sl] = (P)((v_si * c.dt) / c.dx);
-    ID[sl] = NO_ID;
-    n[wall] += 1;
+    bool wrote = false;
+    if (in) {
+      const double E_se = see_energy(c.see_law, c.see_E, c.see_mu, c.see_sig, unit_open(word[0]), unit_open(word[1]));
+      const double v_se = sqrt(div_by(2.0 * E_se * c.ev, c.mass[0], c.rmass[0]));
+      const double v_si = wl == 0 ? v_se : -v_se;
+      if (sl >= (unsigned long long)c.cap[0]) {
+        atomicOr(&p.err[0], ERR_CAPACITY);
+        atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)g);
+      } else {
+        ((P *)of_species(p.X, sel) + c.pbase[0])[sl] = wl == 0 ? (P)0 : (P)c.N;
+        ((P *)of_species(p.U, sel) + c.pbase[0])[sl] = (P)div_by(v_si * c.dt, c.dx, c.rdx);
+        (of_species(p.ID, sel) + c.pbase[0])[sl] = NO_ID;
+        wrote = true;
+      }
+    }
+    n[0] += (unsigned int)__popcll(__ballot(wrote && wl == 0));
+    n[1] += (unsigned int)__popcll(__ballot(wrote && wl != 0));
   }
 }
 
@@ -316,7 +454,7 @@ __device__ inline void see_write(const DevPtrs &p, const GapConst &c, long long 
 // pass; emitted counts per wall added to emit_cnt (LDS).  Every thread of the
 // block calls it.
 template <class P>
-__device__ void see_emit(const DevPtrs &p, const GapConst &c, long long level, int g, int sel, const Event *evs,
+__device__ void see_emit(const DevPtrs &p, ConstGap &c, long long level, int g, int sel, const Event *evs,
                          int ne, int *wsum, unsigned long long *s_base, unsigned int *emit_cnt) {
   for (int r = 0; r < ne; r += blockDim.x) {
     const int k = r + threadIdx.x;
@@ -336,12 +474,12 @@ __device__ void see_emit(const DevPtrs &p, const GapConst &c, long long level, i
     __syncthreads();
     const unsigned long long base = *s_base;
     __syncthreads();
-    unsigned int n[2] = {0u, 0u};
-    see_write<P>(p, c, level, g, sel, ion_id, wall, nk, blk, base + (unsigned long long)excl, n);
-    const unsigned int a0 = wave_sum(n[0]), a1 = wave_sum(n[1]);
+    unsigned int n[2];
+    const int wex = __builtin_amdgcn_readlane(excl, 0);
+    see_write<P>(p, c, level, g, sel, ion_id, wall, nk, blk, excl - wex, base + (unsigned long long)wex, n);
     if ((threadIdx.x & 63) == 0) {
-      if (a0) atomicAdd(&emit_cnt[0], a0);
-      if (a1) atomicAdd(&emit_cnt[1], a1);
+      if (n[0]) atomicAdd(&emit_cnt[0], n[0]);
+      if (n[1]) atomicAdd(&emit_cnt[1], n[1]);
     }
   }
 }
@@ -364,15 +502,6 @@ constexpr int FDB = 256;   // k_fdens / k_ftable threads, four nodes each
 // workgroup's serial path is shorter than three kernels'.  Its S_k live in LDS
 // (padded).
 constexpr int FIELD1_NMAX = 8192;
-// a / b with r = 1 / b: two Newton corrections of a r give the correctly rounded
-// quotient (in the normal range) in five operations, a fifth of the general
-// division's
-__device__ inline double div_by(double a, double b, double r) {
-  double q = a * r;
-  q = __builtin_fma(__builtin_fma(-q, b, a), r, q);
-  return __builtin_fma(__builtin_fma(-q, b, a), r, q);
-}
-
 __device__ inline double node_rho(double s0, double dx, double rdx, unsigned long long a, int j, int N, int fp64) {
   const double scale = fp64 ? 5.684341886080801486968994140625e-14 /* 2^-44 */
                             : 5.9604644775390625e-08 /* 2^-24 */;
@@ -629,6 +758,35 @@ __device__ void level_counts(const DevPtrs &p, int g, const GapConst &c, GapStat
     const int hh = st.hist_head;
     st.hist[hh][4] = qsh_i * (double)ab[1 * 2 + 0] + qsh_e * (double)ab[0 * 2 + 0];
     st.hist[hh][5] = qsh_e * (double)em[0];
+  }
+}
+
+// word i of the coming push's head (after level_counts and level_end)
+__device__ inline void write_head(const DevPtrs &p, int g, const GapConst &c, const GapState &st, int i) {
+  PushHead *h = p.head + g;
+  switch (i) {
+    case 0: h->count[0] = st.count[0]; break;
+    case 1: h->count[1] = st.count[1]; break;
+    case 2: h->beam_now = st.beam_now; break;
+    case 3: h->beam_id0 = st.beam_id0; break;
+    case 4: h->level = st.level; break;
+    case 5: h->pbase[0] = c.pbase[0]; break;
+    case 6: h->pbase[1] = c.pbase[1]; break;
+    case 7: h->nbase = c.nbase; break;
+    case 8: h->ebase = c.ebase; break;
+    case 9: h->evbase = c.evbase; break;
+    case 10: h->evcap = c.evcap; break;
+    case 11: h->alpha[0] = c.alpha[0]; break;
+    case 12: h->alpha[1] = c.alpha[1]; break;
+    case 13:
+      h->N = c.N;
+      h->Z[0] = c.Z[0];
+      break;
+    case 14:
+      h->Z[1] = c.Z[1];
+      h->see = c.see_amp > 0.0 && c.Z[1] > 0 ? 1 : 0;
+      break;
+    default: break;
   }
 }
 
@@ -931,6 +1089,7 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
     const unsigned long long *a = (const unsigned long long *)&ss;
     unsigned long long *b = (unsigned long long *)&p.gs[g];
     for (int i = tid; i < (int)(sizeof(GapState) / 8); i += BS) b[i] = a[i];
+    if (tid < 15) write_head(p, g, sc, ss, tid);
   }
   if (tid < T_N) p.tally[(size_t)g * T_N + tid] = 0ull;
 }
@@ -1138,6 +1297,7 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
     const unsigned long long *a = (const unsigned long long *)&ss;
     unsigned long long *b = (unsigned long long *)&p.gs[g];
     for (int i = tid; i < (int)(sizeof(GapState) / 8); i += FBS) b[i] = a[i];
+    if (tid < 15) write_head(p, g, sc, ss, tid);
   }
   if (tid < T_N) p.tally[(size_t)g * T_N + tid] = 0ull;
 }
@@ -1330,7 +1490,8 @@ __device__ inline void acc_add<Carry32>(unsigned int *lds, unsigned long long *g
 template <class P>
 __device__ void emit_list(const DevPtrs &p, int g, int sel, long long r0, int nr, int *wsum,
                           unsigned long long *s_base, unsigned int *s_emit) {
-  const GapConst &c = p.gc[g];
+  g = __builtin_amdgcn_readfirstlane(g);
+  ConstGap &c = const_gap(p, g);
   const long long level = p.gs[g].level;
   if (threadIdx.x < 2) s_emit[threadIdx.x] = 0u;
   __syncthreads();
@@ -1353,6 +1514,7 @@ __device__ void emit_list(const DevPtrs &p, int g, int sel, long long r0, int nr
   __syncthreads();
 }
 
+constexpr int FLUSH_SHARE = 4;  // least slots per node and workgroup of a single gap (see k_push)
 constexpr int EVQ = 128;  // absorbed-ion events a push workgroup queues in LDS
 // (more go to the workgroup's overflow region of a global buffer; both are
 // emitted at the segment's flush, so a step's emission completes in its push)
@@ -1366,11 +1528,26 @@ struct PushShared {
   Event *evq;           // [EVQ]
   unsigned int *evq_n;
   int *wsum;            // [BS / 64] scan scratch
+  unsigned int *piece;  // the flush's next piece of nodes
+  unsigned int *ticket; // see push_ticket
+  int nact;             // workgroups of the launch that take part
   unsigned int *listed; // the workgroup put absorbed ions in a gap's list (set
                         // when a segment is closed: its queue count passed the
                         // LDS queue and the overflow region)
   int masks;            // the launch writes the live masks
 };
+
+// floor(k n / m) for 0 <= k <= m, n < 2^32: with 32-bit divisions below 2^16 shares
+// (a 64-bit division is some hundred instructions, half a microsecond of a
+// workgroup that has just started)
+__device__ inline unsigned int share_of(unsigned int n, unsigned int k, unsigned int m) {
+  if (n == m) return k;
+  if (m < 65536u) {
+    const unsigned int q = n / m, r = n - q * m;
+    return k * q + k * r / m;
+  }
+  return (unsigned int)(((unsigned long long)n * k) / m);
+}
 
 // push tiles of gap g: electrons, then ions (a gap with a beam has at least
 // one ion tile: the workgroups holding its ion tiles inject the beam)
@@ -1381,10 +1558,10 @@ __device__ inline int tiles_of(long long count, int tile) {
   return (int)(q + (c - q * t != 0u ? 1u : 0u));
 }
 
-__device__ inline void gap_tiles(const GapState &st, long long beam_n, int tile, int &te, int &ti) {
-  te = tiles_of(st.count[0], tile);
-  ti = tiles_of(st.count[1], tile);
-  if (beam_n > 0 && ti == 0) ti = 1;
+__device__ inline void gap_tiles(const PushHead &h, int tile, int &te, int &ti) {
+  te = tiles_of(h.count[0], tile);
+  ti = tiles_of(h.count[1], tile);
+  if (h.beam_now > 0 && ti == 0) ti = 1;
 }
 
 
@@ -1394,11 +1571,11 @@ __device__ inline void gap_tiles(const GapState &st, long long beam_n, int tile,
 // set aside by the field solve.  Their charge goes to the ion segment's LDS
 // accumulator.
 template <class P, class AC>
-__device__ void beam_inject(const DevPtrs &p, const GapConst &c, const GapState &st, int g, int sel, long long k0,
+__device__ void beam_inject(const DevPtrs &p, ConstGap &c, const PushHead &st, int g, int sel, long long k0,
                             long long k1, typename AC::cell *acc, unsigned int *n_inj) {
-  P *X = (P *)p.X[sel] + c.pbase[1];
-  P *U = (P *)p.U[sel] + c.pbase[1];
-  uint32_t *ID = p.ID[sel] + c.pbase[1];
+  P *X = (P *)of_species(p.X, sel) + c.pbase[1];
+  P *U = (P *)of_species(p.U, sel) + c.pbase[1];
+  uint32_t *ID = of_species(p.ID, sel) + c.pbase[1];
   unsigned long long *gacc = p.acc + c.nbase;
   const int N = c.N;
   const long long zhi = (long long)c.Z[1] * 4294967296ll;
@@ -1407,12 +1584,12 @@ __device__ void beam_inject(const DevPtrs &p, const GapConst &c, const GapState 
     uint64_t blk[4];
     rng_block(c.seed, (uint64_t)st.level, (uint64_t)k, 2, 0, blk);
     const double E = c.beam_Emin + (c.beam_Emax - c.beam_Emin) * unit_open(blk[0]);
-    const double v = sqrt(2.0 * E * c.ev / c.mass[1]);
+    const double v = sqrt(div_by(2.0 * E * c.ev, c.mass[1], c.rmass[1]));
     // depth below the entry electrode: within the layer, or within one step's flight
     const double depth = unit_open(blk[1]) * (c.beam_layer > 0.0 ? c.beam_layer : v * c.dt);
     const double x = c.beam_side == GS_BEAM_GROUND ? c.d - depth : depth;
-    const P xi = (P)(x / c.dx);
-    const double uv = (v * c.dt) / c.dx;
+    const P xi = (P)div_by(x, c.dx, c.rdx);
+    const double uv = div_by(v * c.dt, c.dx, c.rdx);
     const P u = (P)(c.beam_side == GS_BEAM_GROUND ? -uv : uv);
     const unsigned long long slot = (unsigned long long)st.count[1] + (unsigned long long)k;
     if (slot >= (unsigned long long)c.cap[1]) {
@@ -1436,110 +1613,192 @@ __device__ void beam_inject(const DevPtrs &p, const GapConst &c, const GapState 
   if ((threadIdx.x & 63) == 0 && a) atomicAdd(n_inj, a);
 }
 
-// Emission for the events [r0, r0 + blockDim) of a segment's queue (the LDS
-// queue, then the workgroup's overflow region): one per thread, counts drawn,
-// one slot reservation for the electrons, which are written; returns the
-// reservation's total.  The first round also flushes the node sums while its
-// reservation is in flight.
+// The gaps' lists of absorbed ions (the events past the workgroups' own
+// queues) are complete once every workgroup has pushed its particles.  Each
+// workgroup counts itself, when it begins its last flush, in the counter of its
+// group (blockIdx.x mod TICKET_GROUPS, a cache line each, so that a large grid
+// does not queue on one address); the high half counts those that added to a
+// list, after making their entries visible device-wide.  The workgroup that
+// completes a group adds the group to the top counter, and the one that completes
+// that is the last: when some workgroup added to a list, it emits the lists after
+// its flush, as k_emit would after the push.  It leaves every counter at zero for
+// the next launch, and the number of list events it emitted in the host word from
+// which the host chooses who emits the next push's lists.  (Fewer than 2^16
+// workgroups take part.)  push_ticket is one wave's, the counters' round trips
+// behind the other waves' flush; it leaves 0 in sh.ticket for a workgroup that is
+// not the last, else 1 + the number of workgroups that added to a list.  (Every
+// wave has passed a barrier with its list entries written.)
+constexpr int TICKET_LINE = 32;    // counter words per cache line
+constexpr int TICKET_GROUPS = 32;  // group counters (see the allocation of push_done)
 template <class P, class AC>
-__device__ inline int emit_round(const DevPtrs &p, const GapConst &c0, const GapState &st, int g, int s, int sel,
-                                 PushShared<P, AC> &sh, const Event *ovf, int ne, int r0,
-                                 unsigned long long *s_base) {
-  // the emission's constants are read here, not at the kernel's start (held
-  // in registers across the push they would spill)
-  // (the pointer is the workgroup's: moved to scalar registers half by half,
-  // which the empty asm then pins)
-  const unsigned long long cu = (unsigned long long)&c0;
-  const GapConst *cp = (const GapConst *)(((unsigned long long)(unsigned int)__builtin_amdgcn_readfirstlane(
-                                               (int)(cu >> 32)) << 32) |
-                                          (unsigned int)__builtin_amdgcn_readfirstlane((int)cu));
-  asm volatile("" : "+s"(cp));
-  const GapConst &c = *cp;
-  const int i = r0 + (int)threadIdx.x;
-  uint32_t ion_id = 0;
-  int wall = 0, nk = 0;
-  double u_imp = 0.0;
-  if (i < ne) {
-    const Event ev = i < EVQ ? sh.evq[i] : ovf[i - EVQ];
-    ion_id = p.ID[sel][c.pbase[1] + ev.ref];
-    wall = (int)ev.wall;
-    u_imp = ev.u;
+__device__ __forceinline__ void push_ticket(const DevPtrs &p, PushShared<P, AC> &sh, bool listed) {
+  if (listed) __threadfence();
+  if ((threadIdx.x & 63) == 0) {
+    unsigned int last = 0u;
+    const unsigned int n = (unsigned int)sh.nact;
+    constexpr unsigned int NG = (unsigned int)TICKET_GROUPS;
+    const unsigned int q = blockIdx.x % NG;
+    const unsigned int nq = (n - q + NG - 1u) / NG;  // workgroups in group q
+    const unsigned int add = listed ? 0x10001u : 1u;
+    const unsigned int gq = atomicAdd(&p.push_done[TICKET_LINE * (1u + q)], add) + add;
+    if ((gq & 0xFFFFu) == nq) {
+      if (gq >> 16) __threadfence();  // the group's list entries, on to the last one
+      const unsigned int add2 = 1u + ((gq >> 16) << 16);
+      const unsigned int t = atomicAdd(&p.push_done[0], add2) + add2;
+      if ((t & 0xFFFFu) == min(n, NG)) last = 1u + (t >> 16);
+    }
+    *sh.ticket = last;
   }
-  uint64_t blk[4] = {0, 0, 0, 0};
-  if (i < ne) nk = see_count(c, st.level, ion_id, u_imp, blk);
-  int btot = 0, excl = 0;
-  if (r0 < ne)
-    excl = block_exclusive_scan_i(nk, sh.wsum, &btot);
-  else
-    __syncthreads();
-  unsigned long long base = 0;
-  if (threadIdx.x == 0 && btot > 0) base = atomicAdd(&p.next_count[g * 2 + 0], (unsigned long long)btot);
-  if (r0 == 0) {
-    // node sums; each workgroup starts at its own node so that the workgroups
-    // flushing at the same time add to different addresses
-    unsigned long long *gacc = p.acc + c.nbase;
-    const long long Z = (long long)c.Z[s];
-    const int nn = c.N + 1;
-    const int rot = (int)(((long long)blockIdx.x * 977) % nn);
-    for (int q = threadIdx.x; q < nn; q += blockDim.x) {
+}
+
+// The segment's node sums to the gap's row, in pieces of 256 nodes that the waves
+// take as they get to it (a wave may still be emitting).  Each workgroup starts at
+// its own node so that the workgroups flushing at the same time add to different
+// addresses.
+template <class P, class AC>
+__device__ inline void flush_nodes(const DevPtrs &p, const PushHead &h, int s, PushShared<P, AC> &sh) {
+  unsigned long long *gacc = p.acc + h.nbase;
+  const long long Z = (long long)of_species(h.Z, s);
+  const int nn = h.N + 1;
+  const int lane = threadIdx.x & 63;
+  const int rot = (int)((blockIdx.x * 977u) % (unsigned int)nn);
+  for (;;) {
+    int q0 = 0;
+    if (lane == 0) q0 = (int)atomicAdd(sh.piece, 256u);
+    q0 = __builtin_amdgcn_readfirstlane(q0);
+    if (q0 >= nn) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int q = q0 + 64 * i + lane;
       int j = q + rot;
       j = j >= nn ? j - nn : j;
-      const unsigned long long v = (unsigned long long)sh.acc[j];
+      const unsigned long long v = q < nn ? (unsigned long long)sh.acc[j] : 0ull;
       if (v != 0ull) atomicAdd(&gacc[j], (unsigned long long)(Z * (long long)v));
     }
   }
-  if (btot > 0) {
-    if (threadIdx.x == 0) *s_base = base;
-    __syncthreads();
-    unsigned int n[2] = {0u, 0u};
-    if (nk > 0) see_write<P>(p, c, st.level, g, sel, ion_id, wall, nk, blk, *s_base + (unsigned long long)excl, n);
-    const unsigned int a0 = wave_sum(n[0]), a1 = wave_sum(n[1]);
-    if ((threadIdx.x & 63) == 0) {
-      if (a0) atomicAdd(&sh.tally[T_EMIT], a0);
-      if (a1) atomicAdd(&sh.tally[T_EMIT + 1], a1);
-    }
-    __syncthreads();
-  }
-  return btot;
 }
 
-// Close one (gap, species) segment: for the ion segment emit the secondary
-// electrons of the ions this workgroup absorbed, in rounds of one event per
-// thread (the first round also hands the node sums times the charge number to
-// the gap); then the emitted electrons' wall charge and the tallies.
+// an emitted electron carries its full weight on its wall node
+template <class P>
+__device__ inline void emitted_charge(const DevPtrs &p, const PushHead &h, unsigned int e0, unsigned int e1) {
+  unsigned long long *gacc = p.acc + h.nbase;
+  const long long ze = (long long)h.Z[0] * Prec<P>::W;
+  if (e0) atomicAdd(&gacc[0], (unsigned long long)(ze * (long long)e0));
+  if (e1) atomicAdd(&gacc[h.N], (unsigned long long)(ze * (long long)e1));
+}
+
+// A queued event's ion id, wall and Poisson count.
+__device__ inline int queued_count(const DevPtrs &p, ConstGap &c, const PushHead &h, int sel, const Event &ev,
+                                   uint32_t &ion_id, int &wall, uint64_t blk[4]) {
+  ion_id = of_species(p.ID, sel)[h.pbase[1] + ev.ref];
+  wall = (int)ev.wall;
+  return see_count(c, h.level, ion_id, ev.u, blk);
+}
+
+// Close one (gap, species) segment: the node sums times the charge number go to
+// the gap, for the ion segment the secondary electrons of the ions this workgroup
+// absorbed are emitted, and the tallies are added.  Up to a wave's worth of events
+// (most workgroups of a push) is the first wave's own work, from the ids to the
+// tallies, while the others flush the nodes; more are emitted in rounds of one
+// event per thread, with one slot reservation each (one address for the whole
+// device), in flight while the nodes are flushed.  On the workgroup's last segment
+// the last wave takes its ticket (see push_ticket).
 template <class P, class AC>
-__device__ void flush_seg(const DevPtrs &p, const GapConst &c, const GapState &st, int g, int s, int sel,
-                          PushShared<P, AC> &sh) {
+__device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P, AC> &sh,
+                          bool ticket) {
   __shared__ unsigned long long s_base;
-  __syncthreads();
+  lds_barrier();
+  const DevPtrs p = push_args();
   const int ovq = (long long)blockIdx.x < p.ovf_wgs ? (int)p.ovq : 0;
-  const int ne = s == 1 ? (int)min(*sh.evq_n, (unsigned int)(EVQ + ovq)) : 0;
-  if (s == 1 && threadIdx.x == 0 && *sh.evq_n > (unsigned int)(EVQ + ovq)) *sh.listed = 1u;
-  const Event *ovf = p.ovf + (size_t)blockIdx.x * (size_t)p.ovq;
-  // one inlined copy of the round (the kernel's instruction footprint matters)
-  int emitted = 0, r0 = 0;
-  do {
-    emitted += emit_round<P, AC>(p, c, st, g, s, sel, sh, ovf, ne, r0, &s_base);
-    r0 += blockDim.x;
-  } while (r0 < ne);
-  if (emitted > 0 && threadIdx.x == 0) {
-    // an emitted electron carries its full weight on its wall node
-    unsigned long long *gacc = p.acc + c.nbase;
-    const long long ze = (long long)c.Z[0] * Prec<P>::W;
-    const unsigned int e0 = sh.tally[T_EMIT], e1 = sh.tally[T_EMIT + 1];
-    if (e0) atomicAdd(&gacc[0], (unsigned long long)(ze * (long long)e0));
-    if (e1) atomicAdd(&gacc[c.N], (unsigned long long)(ze * (long long)e1));
+  const unsigned int queued = s == 1 ? *sh.evq_n : 0u;
+  const int ne = (int)min(queued, (unsigned int)(EVQ + ovq));
+  // (events past the LDS queue went through memory)
+  if (queued > (unsigned int)EVQ) __syncthreads();
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, last_wave = (int)(blockDim.x >> 6) - 1;
+  if (wv == last_wave) {
+    const bool listed = *sh.listed != 0u || queued > (unsigned int)(EVQ + ovq);
+    if (lane == 0 && listed) *sh.listed = 1u;
+    if (ticket) push_ticket<P, AC>(p, sh, listed);
+    // the tallies but the emission's, one per lane; the empty asm keeps the
+    // compiler from computing the per-lane address once at the kernel's start
+    // and holding it (spilled) across the push
+    int t = lane;
+    asm volatile("" : "+v"(t));
+    if (t < T_N) {
+      const unsigned int v = sh.tally[t];
+      if (v) atomicAdd(&p.tally[(size_t)g * T_N + t], (unsigned long long)v);
+    }
   }
-  // the tallies, one per thread; the empty asm keeps the compiler from
-  // computing the per-thread address once at the kernel's start and holding it
-  // (spilled) across the push
-  int t = (int)threadIdx.x;
-  asm volatile("" : "+v"(t));
-  if (t < T_N) {
-    const unsigned int v = sh.tally[t];
-    if (v) atomicAdd(&p.tally[(size_t)g * T_N + t], (unsigned long long)v);
+  if (ne > 0) {
+    // the emission's constants are read here, not at the kernel's start (held
+    // in registers across the push they would spill)
+    int ge = g;
+    asm volatile("" : "+s"(ge));
+    ConstGap &c = const_gap(p, ge);
+    const Event *ovf = p.ovf + (size_t)blockIdx.x * (size_t)p.ovq;
+    if (ne <= 64) {
+      if (wv == 0) {
+        uint32_t id = 0;
+        int wall = 0, nk = 0;
+        uint64_t blk[4] = {0, 0, 0, 0};
+        if (lane < ne) nk = queued_count(p, c, h, sel, sh.evq[lane], id, wall, blk);
+        const int incl = wave_incl_scan(nk);
+        const int tot = __builtin_amdgcn_readlane(incl, 63);
+        if (tot > 0) {
+          unsigned long long base = 0;
+          if (lane == 0) base = atomicAdd(&p.next_count[g * 2 + 0], (unsigned long long)tot);
+          base = __shfl(base, 0, 64);
+          unsigned int n[2];
+          see_write<P>(p, c, h.level, g, sel, id, wall, nk, blk, incl - nk, base, n);
+          if (lane == 0) {
+            emitted_charge<P>(p, h, n[0], n[1]);
+            if (n[0]) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT], (unsigned long long)n[0]);
+            if (n[1]) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT + 1], (unsigned long long)n[1]);
+          }
+        }
+      }
+      flush_nodes<P, AC>(p, h, s, sh);
+    } else {
+      unsigned int e0 = 0, e1 = 0;
+#pragma unroll 1
+      for (int r0 = 0; r0 < ne; r0 += blockDim.x) {
+        const int i = r0 + (int)threadIdx.x;
+        uint32_t id = 0;
+        int wall = 0, nk = 0;
+        uint64_t blk[4] = {0, 0, 0, 0};
+        if (i < ne) {
+          // (the LDS queue, then the workgroup's overflow region)
+          Event ev;
+          if (i < EVQ)
+            ev = sh.evq[i];
+          else
+            ev = ovf[i - EVQ];
+          nk = queued_count(p, c, h, sel, ev, id, wall, blk);
+        }
+        int btot;
+        const int excl = block_exclusive_scan_i(nk, sh.wsum, &btot);
+        unsigned long long base = 0;
+        if (threadIdx.x == 0 && btot > 0) base = atomicAdd(&p.next_count[g * 2 + 0], (unsigned long long)btot);
+        if (r0 == 0) flush_nodes<P, AC>(p, h, s, sh);
+        if (threadIdx.x == 0) s_base = base;
+        lds_barrier();
+        unsigned int n[2];
+        const int wex = __builtin_amdgcn_readlane(excl, 0);
+        see_write<P>(p, c, h.level, g, sel, id, wall, nk, blk, excl - wex, s_base + (unsigned long long)wex, n);
+        e0 += n[0];
+        e1 += n[1];
+        lds_barrier();
+      }
+      if (lane == 0) {
+        emitted_charge<P>(p, h, e0, e1);
+        if (e0) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT], (unsigned long long)e0);
+        if (e1) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT + 1], (unsigned long long)e1);
+      }
+    }
+  } else {
+    flush_nodes<P, AC>(p, h, s, sh);
   }
-  __syncthreads();
+  lds_barrier();
 }
 
 // Stage one (gap, species) segment: clear the node accumulator and the
@@ -1547,33 +1806,43 @@ __device__ void flush_seg(const DevPtrs &p, const GapConst &c, const GapState &s
 // table (16-byte aligned, N + 2 entries) into LDS with 16-byte loads, the
 // first TQ per thread issued before anything else.  The table is the gap's,
 // for either species: table is false when LDS already holds it (the previous
-// segment was the gap's other species).
+// segment was the gap's other species).  stage is false for a segment that is
+// open already: only the beam goes in.
 template <class P, class AC>
-__device__ void load_seg(const DevPtrs &p, const GapConst &c, const GapState &st, int g, int sel,
-                         PushShared<P, AC> &sh, long long kb0, long long kb1, bool table) {
+__device__ void load_seg(const DevPtrs &p, const PushHead &h, int g, int sel,
+                         PushShared<P, AC> &sh, long long kb0, long long kb1, bool stage, bool table) {
   // the table moves as 16-byte vectors of a native vector type (arrays of it
   // stay in registers)
   typedef unsigned int V __attribute__((ext_vector_type(4)));
   constexpr int TQ = 5;  // table vectors per thread whose loads go out first
-  const V *geh = (const V *)((const P *)p.ehat + c.ebase);
+  const V *geh = (const V *)((const P *)p.ehat + h.ebase);
   V *leh = (V *)sh.eh;
-  const int nv = (int)(((size_t)(c.N + 2) * sizeof(P) + 15) / 16);
+  const int nv = (int)(((size_t)(h.N + 2) * sizeof(P) + 15) / 16);
   const int bs = blockDim.x;
   const int tid = threadIdx.x;
+  // the gap's constants that the beam and the emission read, a word of each of
+  // their cache lines, into the scalar cache before they are needed
+  static_assert(offsetof(GapConst, sL) <= 8 * 64, "lines to touch");
+  unsigned int warm = 0u;
+#pragma unroll
+  for (int q = 0; q < 9; ++q)
+    warm ^= ((const __attribute__((address_space(4))) unsigned int *)&const_gap(p, g))[q * 16];
   // loads past the table repeat its last vector
   V t[TQ];
   if (table) {
 #pragma unroll
     for (int q = 0; q < TQ; ++q) t[q] = geh[min(tid + q * bs, nv - 1)];
   }
-  for (int j = tid; j <= c.N; j += bs) sh.acc[j] = 0;
-  if (tid < T_N) sh.tally[tid] = 0u;
-  if (tid == 0) *sh.evq_n = 0u;
+  if (stage) {
+    for (int j = tid; j <= h.N; j += bs) sh.acc[j] = 0;
+    if (tid < T_N) sh.tally[tid] = 0u;
+    if (tid == 0) *sh.evq_n = *sh.piece = 0u;
+  }
   // the beam goes in while the table's loads are in flight (the beam's slots
   // lie past the swept range; its charge only has to reach the next density)
   if (kb1 > kb0) {
-    __syncthreads();
-    beam_inject<P, AC>(p, c, st, g, sel, kb0, kb1, sh.acc, &sh.tally[T_INJ]);
+    if (stage) lds_barrier();
+    beam_inject<P, AC>(p, const_gap(p, g), h, g, sel, kb0, kb1, sh.acc, &sh.tally[T_INJ]);
   }
   if (table) {
 #pragma unroll
@@ -1588,7 +1857,8 @@ __device__ void load_seg(const DevPtrs &p, const GapConst &c, const GapState &st
         if (j0 + q * bs < nv) leh[j0 + q * bs] = r[q];
     }
   }
-  __syncthreads();
+  asm volatile("" ::"s"(warm));
+  if (stage) lds_barrier();
 }
 
 // Per-thread running counts of one segment.
@@ -1783,27 +2053,28 @@ __device__ inline void load_chunk(const P *X, const P *U, long long r0, typename
 // The remainder goes slot by slot: slots past b may be receiving appended
 // particles.
 template <class P, class AC, int BS, int PPT, bool NT>
-__device__ void push_range(const DevPtrs &p, const GapConst &gc, const GapState &st, int g, int s, int sel,
-                           PushShared<P, AC> &sh, long long a, long long b, long long run, long long step,
-                           int nrun, long long kb0, long long kb1, bool stage, bool table, SegCount &cnt) {
+__device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, int sel, PushShared<P, AC> &sh,
+                           long long a, long long b, long long run, long long step, int nrun, long long kb0,
+                           long long kb1, bool stage, bool table, SegCount &cnt) {
   typedef typename Vec<P>::type V;
   constexpr int VN = Vec<P>::n;
   constexpr int NV = PPT / VN;
   constexpr int CH = BS * PPT;
+  const int64_t pb = of_species(h.pbase, s);
   SegK c;
-  c.N = gc.N;
+  c.N = h.N;
   c.g = g;
-  c.evbase = gc.evbase;
-  c.evcap = gc.evcap;
-  c.gacc = p.acc + gc.nbase;
-  c.ids = p.ID[sel] + gc.pbase[s];
+  c.evbase = h.evbase;
+  c.evcap = h.evcap;
+  c.gacc = p.acc + h.nbase;
+  c.ids = of_species(p.ID, sel) + pb;
   c.masks = sh.masks;
-  c.live = p.live + gc.pbase[s] / 64;
-  P *X = (P *)p.X[sel] + gc.pbase[s];
-  P *U = (P *)p.U[sel] + gc.pbase[s];
-  const P alpha = (P)gc.alpha[s];
-  const bool see = (s == 1) && (gc.see_amp > 0.0) && (gc.Z[1] > 0);
-  const long long zhi = (long long)gc.Z[s] * 4294967296ll;
+  c.live = p.live + pb / 64;
+  P *X = (P *)of_species(p.X, sel) + pb;
+  P *U = (P *)of_species(p.U, sel) + pb;
+  const P alpha = (P)of_species(h.alpha, s);
+  const bool see = s == 1 && h.see != 0;
+  const long long zhi = (long long)of_species(h.Z, s) * 4294967296ll;
   // runs before the last are whole (a later tile of the region exists)
   const int cpr = (int)(run / CH);
   const long long last = a + (long long)(nrun - 1) * step;
@@ -1812,10 +2083,7 @@ __device__ void push_range(const DevPtrs &p, const GapConst &gc, const GapState 
   // the first chunk's loads are in flight while the segment is staged (or,
   // when the segment is already open, while this range's beam goes in)
   if (nfull > 0) load_chunk<P, BS, PPT, NT>(X, U, a, xa, ua);
-  if (stage)
-    load_seg<P, AC>(p, gc, st, g, sel, sh, kb0, kb1, table);
-  else if (kb1 > kb0)
-    beam_inject<P, AC>(p, gc, st, g, sel, kb0, kb1, sh.acc, &sh.tally[T_INJ]);
+  if (stage || kb1 > kb0) load_seg<P, AC>(p, h, g, sel, sh, kb0, kb1, stage, table);
   // one copy of the chunk body (the kernel's instruction footprint is what
   // limits it): the next chunk's loads go out before this chunk is pushed,
   // and the buffers are swapped by register moves
@@ -1861,33 +2129,32 @@ __device__ void push_range(const DevPtrs &p, const GapConst &gc, const GapState 
 // (Plain functions, not lambdas: a closure holding the kernel's argument block
 // by address would copy it to the stack.)
 template <class P, class AC>
-__device__ __forceinline__ void close_seg(const DevPtrs &p, PushShared<P, AC> &sh, int sel, int og, int os) {
+__device__ __forceinline__ void close_seg(PushShared<P, AC> &sh, int sel, int og, int os,
+                                          bool ticket) {
   // (workgroup-uniform; made scalars for the emission's scalar loads)
   const int g = __builtin_amdgcn_readfirstlane(og), s = __builtin_amdgcn_readfirstlane(os);
-  flush_seg<P, AC>(p, p.gc[g], p.gs[g], g, s, sel, sh);
+  const PushHead h = load_head(push_args(), g);
+  flush_seg<P, AC>(h, g, s, sel, sh, ticket);
 }
 
 template <class P, class AC, int BS, int PPT, bool NT>
-__device__ __forceinline__ void push_piece(const DevPtrs &p, PushShared<P, AC> &sh, int tile, int sel, int g,
-                                           int s, int ls, int le, int stride, int &og, int &os) {
+__device__ __forceinline__ void push_piece(PushShared<P, AC> &sh, int tile, int sel, int g,
+                                           int s, int ls, int le, int stride, int ti, int og, int os) {
   g = __builtin_amdgcn_readfirstlane(g);
   s = __builtin_amdgcn_readfirstlane(s);
   ls = __builtin_amdgcn_readfirstlane(ls);
   le = __builtin_amdgcn_readfirstlane(le);
   stride = __builtin_amdgcn_readfirstlane(stride);
-  const GapConst &c = p.gc[g];
-  const GapState &st = p.gs[g];
-  int te, ti;
-  gap_tiles(st, st.beam_now, tile, te, ti);
+  const DevPtrs p = push_args();
+  const PushHead st = load_head(p, g);
   const bool stage = !(g == og && s == os);
   const bool table = og != g;  // (LDS holds the table of the last gap staged)
-  if (stage && og >= 0) close_seg<P, AC>(p, sh, sel, og, os);
   SegCount cnt;
   // the local tiles ls, ls + stride, ... below le (stride 1: the run [ls, le))
   const int nrun = stride == 1 ? 1 : (le - ls + stride - 1) / stride;
   const int lt = stride == 1 ? le - 1 : ls + (nrun - 1) * stride;
   const long long a = (long long)ls * tile;
-  const long long b = min((long long)(lt + 1) * tile, st.count[s]);
+  const long long b = min((long long)(lt + 1) * tile, (long long)of_species(st.count, s));
   const long long run = stride == 1 ? (long long)(le - ls) * tile : (long long)tile;
   const long long step = stride == 1 ? run : (long long)stride * tile;
   // the beam: over a run of tiles it is split by the gap's ion tiles, tile lt
@@ -1898,10 +2165,10 @@ __device__ __forceinline__ void push_piece(const DevPtrs &p, PushShared<P, AC> &
   long long kb0 = 0, kb1 = 0;
   if (s == 1) {
     const int nb = stride == 1 ? ti : min(ti, stride);
-    kb0 = st.beam_now * ls / nb;
-    kb1 = st.beam_now * (stride == 1 ? le : ls + 1) / nb;
+    kb0 = share_of((unsigned int)st.beam_now, (unsigned int)ls, (unsigned int)nb);
+    kb1 = share_of((unsigned int)st.beam_now, (unsigned int)(stride == 1 ? le : ls + 1), (unsigned int)nb);
   }
-  push_range<P, AC, BS, PPT, NT>(p, c, st, g, s, sel, sh, a, b, run, step, nrun, kb0, kb1, stage, table, cnt);
+  push_range<P, AC, BS, PPT, NT>(p, st, g, s, sel, sh, a, b, run, step, nrun, kb0, kb1, stage, table, cnt);
   // wave-level sums, then one LDS atomic per wave
   const unsigned int v0 = wave_sum(cnt.pushed), v1 = wave_sum(cnt.abs0), v2 = wave_sum(cnt.abs1);
   if ((threadIdx.x & 63) == 0) {
@@ -1909,75 +2176,18 @@ __device__ __forceinline__ void push_piece(const DevPtrs &p, PushShared<P, AC> &
     if (v1) atomicAdd(&sh.tally[T_ABS + s * 2 + 0], v1);
     if (v2) atomicAdd(&sh.tally[T_ABS + s * 2 + 1], v2);
   }
-  og = g;
-  os = s;
-}
-
-// the pieces of the global tiles [ta, tb) of gap g, whose tiles start at t_g
-template <class P, class AC, int BS, int PPT, bool NT>
-__device__ __forceinline__ void push_tiles(const DevPtrs &p, PushShared<P, AC> &sh, int tile, int sel, int g,
-                                           int t_g, int ta, int tb, int &og, int &os) {
-  int te, ti;
-  gap_tiles(p.gs[g], p.gs[g].beam_now, tile, te, ti);
-  const int la = ta - t_g, lb = tb - t_g;
-  if (la < te) push_piece<P, AC, BS, PPT, NT>(p, sh, tile, sel, g, 0, la, min(lb, te), 1, og, os);
-  if (lb > te) push_piece<P, AC, BS, PPT, NT>(p, sh, tile, sel, g, 1, max(la, te) - te, lb - te, 1, og, os);
-}
-
-// The gaps' lists of absorbed ions (the events past the workgroups' own
-// queues) are complete once every workgroup has pushed its particles.  Each
-// workgroup counts itself, before its last flush (which the count's return
-// then overlaps), in the counter of its group (blockIdx.x mod TICKET_GROUPS, a
-// cache line each, so that a large grid does not queue on one address); the
-// high half counts those that added to a list, after making their entries
-// visible device-wide.  The workgroup that completes a group adds the group
-// to the top counter, and the one that completes that is the last: when some
-// workgroup added to a list, it emits the lists after its flush, as k_emit
-// would after the push.  It leaves every counter at zero for the next launch,
-// and the number of list events it emitted in the host word from which the
-// host chooses who emits the next push's lists.  (The grid is below 2^16
-// workgroups.)  push_ticket returns, in thread 0, 0 for a workgroup that is
-// not the last, else 1 + the number of workgroups that added to a list.
-constexpr int TICKET_LINE = 32;    // counter words per cache line
-constexpr int TICKET_GROUPS = 32;  // group counters (see the allocation of push_done)
-template <class P, class AC>
-__device__ __forceinline__ unsigned int push_ticket(const DevPtrs &p, PushShared<P, AC> &sh, int os) {
-  __syncthreads();
-  const unsigned int lim = (unsigned int)EVQ + ((long long)blockIdx.x < p.ovf_wgs ? (unsigned int)p.ovq : 0u);
-  const bool listed = *sh.listed != 0u || (os == 1 && *sh.evq_n > lim);
-  if (listed) {
-    __threadfence();
-    __syncthreads();
-  }
-  unsigned int last = 0u;
-  if (threadIdx.x == 0) {
-    constexpr unsigned int NG = (unsigned int)TICKET_GROUPS;
-    const unsigned int q = blockIdx.x % NG;
-    const unsigned int nq = (gridDim.x - q + NG - 1u) / NG;  // workgroups in group q
-    const unsigned int add = listed ? 0x10001u : 1u;
-    const unsigned int gq = atomicAdd(&p.push_done[TICKET_LINE * (1u + q)], add) + add;
-    if ((gq & 0xFFFFu) == nq) {
-      if (gq >> 16) __threadfence();  // the group's list entries, on to the last one
-      const unsigned int add2 = 1u + ((gq >> 16) << 16);
-      const unsigned int t = atomicAdd(&p.push_done[0], add2) + add2;
-      if ((t & 0xFFFFu) == min(gridDim.x, NG)) last = 1u + (t >> 16);
-    }
-  }
-  return last;
 }
 
 constexpr int LIST_CH = 1 << 20;  // events per emission call
+// (after the last flush's closing barrier)
 template <class P, class AC>
-__device__ __forceinline__ void push_tail_emit(const DevPtrs &p, PushShared<P, AC> &sh, int G, int sel,
-                                               unsigned int ticket) {
-  __shared__ unsigned int s_last;
+__device__ __forceinline__ void push_tail_emit(PushShared<P, AC> &sh, int G, int sel) {
   __shared__ unsigned long long s_mask[16];
   __shared__ unsigned long long s_base;
   __shared__ unsigned int s_emit[2];
-  if (threadIdx.x == 0) s_last = ticket;
-  __syncthreads();
-  const unsigned int last = s_last;
+  const unsigned int last = *sh.ticket;
   if (last == 0u) return;
+  const DevPtrs p = push_args();
   if (threadIdx.x <= (unsigned int)TICKET_GROUPS) p.push_done[TICKET_LINE * threadIdx.x] = 0u;
   if (last == 1u) {
     if (threadIdx.x == 0) *p.list_seen = 0ull;
@@ -2009,20 +2219,22 @@ __device__ __forceinline__ void push_tail_emit(const DevPtrs &p, PushShared<P, A
 
 template <class P, class AC, int BS, int PPT, bool NT>
 __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int nmax, int steal, int rr,
-                                                 int masks, int lists) {
+                                                 int min_wgs, int masks, int lists) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   typedef typename AC::cell cell;
   __shared__ int scan_sh[BS];
   __shared__ Event evq[EVQ];
   __shared__ unsigned int evq_n;
   __shared__ int wsum_sh[BS / 64];
-  __shared__ unsigned int listed_sh;
+  __shared__ unsigned int listed_sh, piece_sh, ticket_sh;
   // layout: tally[T_N] | prefix[G+1] | eh[nmax+2] (P) | acc[nmax+1] (cell)
   PushShared<P, AC> sh;
   sh.evq = evq;
   sh.evq_n = &evq_n;
   sh.wsum = wsum_sh;
   sh.listed = &listed_sh;
+  sh.piece = &piece_sh;
+  sh.ticket = &ticket_sh;
   sh.masks = masks;
   sh.tally = (unsigned int *)lds_raw;
   sh.prefix = (int *)(lds_raw + 64);
@@ -2037,11 +2249,13 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
 
   // tiles per gap and their prefix (each workgroup builds its own copy in LDS;
   // one gap needs no scan)
-  int total1 = 0;
+  int total1 = 0, te1 = 0, ti1 = 0;
   if (G == 1) {
-    int te, ti;
-    gap_tiles(p.gs[0], p.gs[0].beam_now, tile, te, ti);
-    total1 = te + ti;
+    // (the head's second cache line on its way with the first)
+    const int64_t second = const_head(p, 0).pad;
+    asm volatile("" ::"s"(second));
+    gap_tiles(load_head(p, 0), tile, te1, ti1);
+    total1 = te1 + ti1;
   } else {
     const int per = (G + BS - 1) / BS;
     int mine = 0;
@@ -2049,7 +2263,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
       const int g = tid * per + q;
       if (g < G) {
         int te, ti;
-        gap_tiles(p.gs[g], p.gs[g].beam_now, tile, te, ti);
+        gap_tiles(p.head[g], tile, te, ti);
         mine += te + ti;
       }
     }
@@ -2060,7 +2274,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
       if (g < G) {
         sh.prefix[g] = run;
         int te, ti;
-        gap_tiles(p.gs[g], p.gs[g].beam_now, tile, te, ti);
+        gap_tiles(p.head[g], tile, te, ti);
         run += te + ti;
       }
     }
@@ -2071,84 +2285,106 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   auto prefix = [&](int i) { return G == 1 ? (i == 0 ? 0 : total1) : sh.prefix[i]; };
 
   const int total = prefix(G);
-  const int nwg = (int)gridDim.x;
+  // the workgroups that take part: at most one per tile, the first ones (they
+  // start first, and the others end at once)
+  int nwg = min((int)gridDim.x, max(total, 1));
+  if (G == 1 && !rr && steal == 0) {
+    // and, of one gap, no more than leave each FLUSH_SHARE slots per node, down to
+    // min_wgs (one per CU; all, when the caller set the grid): every one adds its
+    // node sums to the gap's row.  2.3e6 particles on 4096 cells: 256 workgroups
+    // take 22 us, the 768 that fit the chip 37, with 3e6 additions in the flush
+    const PushHead h0 = load_head(p, 0);
+    const unsigned int slots = (unsigned int)h0.count[0] + (unsigned int)h0.count[1];
+    const unsigned int most = slots / (unsigned int)(FLUSH_SHARE * (h0.N + 1));
+    nwg = min(nwg, (int)max(most, (unsigned int)min_wgs));
+  }
+  nwg = __builtin_amdgcn_readfirstlane(nwg);
+  if ((int)blockIdx.x >= nwg) return;
+  sh.nact = nwg;
+  // The workgroup's tiles.  Contiguous: the run [t, t1), with stealing on the
+  // last R of every run going to a pool instead (runs differ by at most one tile,
+  // so each holds at least 8 R).  Round robin: the tiles w, w + nwg, w + 2 nwg, ..,
+  // so that at any moment the workgroups stream neighbouring tiles, one window of
+  // memory, rather than nwg regions far apart; its tiles in one region are one
+  // strided piece, and t visits the workgroup's first tile of each region it has
+  // tiles in (that tile's local index is below nwg).
+  const int R = !rr && steal > 0 ? (total / nwg) / steal : 0;
+  int t = rr ? (int)blockIdx.x : (int)share_of((unsigned int)total, blockIdx.x, (unsigned int)nwg);
+  int t1 = rr ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
+  // pool tile q is tile k = q / nwg of run w = q % nwg's reserved end: the first
+  // reserved tile of every run goes out first
+  // (the next index is taken while a tile is pushed: the counter is one address
+  // for the whole device, and its atomics return slowly)
+  __shared__ int s_q;
+  const int npool = R * nwg;
+  bool pool = false;
+  unsigned int qn = 0u;
+  int g = 0;
   int og = -1, os = 0;  // the open segment (gap, species), none yet
-  if (rr) {
-    // round robin: workgroup w takes the tiles w, w + nwg, w + 2 nwg, ...  At
-    // any moment the workgroups then stream neighbouring tiles, one window of
-    // memory, rather than nwg regions far apart.  Its tiles in one region are
-    // one strided piece; t visits the workgroup's first tile of each region
-    // it has tiles in (that tile's local index is below nwg)
-    int g = 0;
-    int t = (int)blockIdx.x;
-    while (t < total) {
-      while (prefix(g + 1) <= t) ++g;
-      int te, ti;
-      gap_tiles(p.gs[g], p.gs[g].beam_now, tile, te, ti);
-      const int tg = prefix(g);
-      const int s = t - tg < te ? 0 : 1;
-      const int T0 = s ? tg + te : tg, T1 = s ? tg + te + ti : tg + te;
-      push_piece<P, AC, BS, PPT, NT>(p, sh, tile, sel, g, s, t - T0, T1 - T0, nwg, og, os);
-      t += ((T1 - t + nwg - 1) / nwg) * nwg;  // the first of its tiles past the region
-    }
-    const unsigned int ticket = lists ? push_ticket<P, AC>(p, sh, os) : 0u;
-    if (og >= 0) close_seg<P, AC>(p, sh, sel, og, os);
-    if (lists) push_tail_emit<P, AC>(p, sh, G, sel, ticket);
-    return;
-  }
-  // the workgroup's contiguous run of tiles; with stealing on, the last R of
-  // every run go to the pool instead (runs differ by at most one tile, so each
-  // holds at least 8 R)
-  const int R = p.steal != nullptr && steal > 0 ? (total / nwg) / steal : 0;
-  const int t0 = (int)(((long long)blockIdx.x * total) / nwg);
-  const int t1 = (int)(((long long)(blockIdx.x + 1) * total) / nwg) - R;
-  {
-    int g = 0, t = t0;
-    while (t < t1) {
-      while (prefix(g + 1) <= t) ++g;
-      const int e = min(t1, prefix(g + 1));
-      push_tiles<P, AC, BS, PPT, NT>(p, sh, tile, sel, g, prefix(g), t, e, og, os);
-      t = e;
-    }
-  }
-  if (R > 0) {
-    // pool tile q is tile k = q / nwg of run w = q % nwg's reserved end: the
-    // first reserved tile of every run goes out first
-    // (the next index is taken while a tile is pushed: the counter is one
-    // address for the whole device, and its atomics return slowly)
-    __shared__ int s_q;
-    const int npool = R * nwg;
-    unsigned int qn = 0u;
-    if (tid == 0) qn = atomicAdd(p.steal, 1u);
-    for (;;) {
+  // one piece a pass: what a workgroup runs stays one copy of each part (its code
+  // is fetched as it is first run: with the parts inlined at five places the
+  // kernel was 30000 instructions, and a small push spent microseconds on fetches)
+  for (;;) {
+    if (t >= t1 && R > 0) {
+      unsigned int *const counter = push_args().steal;
+      if (!pool && tid == 0) qn = atomicAdd(counter, 1u);
+      pool = true;
       __syncthreads();
       if (tid == 0) s_q = (int)qn;
       __syncthreads();
       // (the same for every thread: made a scalar, as the tile arithmetic is)
       const int q = __builtin_amdgcn_readfirstlane(s_q);
-      if (q >= npool) break;
-      if (tid == 0) qn = atomicAdd(p.steal, 1u);
-      const int w = q % nwg, k = q / nwg;
-      const int tt = (int)(((long long)(w + 1) * total) / nwg) - R + k;
-      // the gap holding tile tt (binary search over the tile prefix)
-      int g = 0;
-      if (G > 1) {
+      if (q < npool) {
+        if (tid == 0) qn = atomicAdd(counter, 1u);
+        const int w = q % nwg, k = q / nwg;
+        t = (int)share_of((unsigned int)total, (unsigned int)(w + 1), (unsigned int)nwg) - R + k;
+        t1 = t + 1;
+        g = 0;
+      }
+    }
+    const bool more = t < t1;
+    int s = 0, ls = 0, le = 0, te = te1, ti = ti1;
+    if (more) {
+      if (G > 1 && pool) {
+        // the gap holding tile t (binary search over the tile prefix)
         int lo = 0, hi = G - 1;
         while (lo < hi) {
           const int mid = (lo + hi + 1) >> 1;
-          if (prefix(mid) <= tt)
+          if (prefix(mid) <= t)
             lo = mid;
           else
             hi = mid - 1;
         }
         g = lo;
       }
-      push_tiles<P, AC, BS, PPT, NT>(p, sh, tile, sel, g, prefix(g), tt, tt + 1, og, os);
+      while (prefix(g + 1) <= t) ++g;
+      g = __builtin_amdgcn_readfirstlane(g);
+      if (G > 1) gap_tiles(load_head(push_args(), g), tile, te, ti);
+      const int tg = prefix(g);
+      s = t - tg < te ? 0 : 1;
+      const int T0 = s ? tg + te : tg, T1 = s ? tg + te + ti : tg + te;  // the region's tiles
+      ls = t - T0;
+      if (rr) {
+        le = T1 - T0;
+        t += ((T1 - t + nwg - 1) / nwg) * nwg;  // the first of its tiles past the region
+      } else {
+        le = min(t1, T1) - T0;
+        t = T0 + le;
+      }
     }
+    if (og >= 0 && !(more && g == og && s == os)) close_seg<P, AC>(sh, sel, og, os, lists != 0 && !more);
+    if (!more) break;
+    push_piece<P, AC, BS, PPT, NT>(sh, tile, sel, g, s, ls, le, rr ? nwg : 1, ti, og, os);
+    og = g;
+    os = s;
   }
-  const unsigned int ticket = lists ? push_ticket<P, AC>(p, sh, os) : 0u;
-  if (og >= 0) close_seg<P, AC>(p, sh, sel, og, os);
-  if (lists) push_tail_emit<P, AC>(p, sh, G, sel, ticket);
+  if (og < 0 && lists) {
+    // (an empty launch: its one workgroup)
+    __syncthreads();
+    if (threadIdx.x < 64) push_ticket<P, AC>(push_args(), sh, false);
+    __syncthreads();
+  }
+  if (lists) push_tail_emit<P, AC>(sh, G, sel);
 }
 
 template <class P, class AC, int BS, int PPT, bool NT>
@@ -2162,8 +2398,8 @@ static hipError_t push_t(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream
     if (e != hipSuccess) return e;
     attr_set = lds;
   }
-  return launch_k(k_push<P, AC, BS, PPT, NT>, dim3(lc.grid), dim3(BS), lds, s, t.a, t.b, p, G, lc.tile,
-                  lc.nmax, lc.steal, (lc.stream & STREAM_RR) ? 1 : 0, lc.masks, lc.lists);
+  return launch_k(k_push<P, AC, BS, PPT, NT>, dim3(std::min(lc.grid, lc.max_wgs)), dim3(BS), lds, s, t.a, t.b, p, G, lc.tile,
+                  lc.nmax, lc.steal, (lc.stream & STREAM_RR) ? 1 : 0, lc.min_wgs, lc.masks, lc.lists);
 }
 
 template <class P, class AC, int PPT, bool NT>
@@ -2793,9 +3029,9 @@ __global__ __launch_bounds__(FW) void k_fill_move(DevPtrs p, int G) {
     const long long q = (long long)p.wrank[c.pbase[s] / 64 + j / 64] + __popcll(m & before);
     const uint32_t *hl = (const uint32_t *)p.X[sel ^ 1] + c.pbase[s];
     const long long dst = (long long)hl[q];
-    P *X = (P *)p.X[sel] + c.pbase[s];
-    P *U = (P *)p.U[sel] + c.pbase[s];
-    uint32_t *I = p.ID[sel] + c.pbase[s];
+    P *X = (P *)of_species(p.X, sel) + c.pbase[s];
+    P *U = (P *)of_species(p.U, sel) + c.pbase[s];
+    uint32_t *I = of_species(p.ID, sel) + c.pbase[s];
     X[dst] = X[j];
     U[dst] = U[j];
     I[dst] = I[j];
@@ -2826,9 +3062,9 @@ __device__ inline bool inject_one(const DevPtrs &p, const GapConst &c, int gap, 
   const P xi = (P)(xs / c.dx);
   const P u = (P)((vs * c.dt) / c.dx);
   const size_t k = (size_t)c.pbase[species] + slot;
-  ((P *)p.X[sel])[k] = xi;
-  ((P *)p.U[sel])[k] = u;
-  p.ID[sel][k] = id;
+  ((P *)of_species(p.X, sel))[k] = xi;
+  ((P *)of_species(p.U, sel))[k] = u;
+  of_species(p.ID, sel)[k] = id;
   j = (int)xi;
   if (j > c.N - 1) j = c.N - 1;
   const P f = xi - (P)j;

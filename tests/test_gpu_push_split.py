@@ -1,0 +1,63 @@
+"""The push's split of small and uneven work, and its emission of many electrons per
+ion, against the oracle's binary32 mode.
+
+Bars: counts exact, both populations bit-equal as multisets, gap voltage and surface
+charge within 1e-5.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2603_24010_amd import workloads as W
+from test_gpu_parity import _series_rel, assert_counts_equal, run_pair, sorted_state
+
+pytestmark = pytest.mark.gpu
+
+
+def _check(sim, orc, recs):
+    for dg, do in recs:
+        assert_counts_equal(dg, do)
+    for key in ("phi0", "sigma"):
+        assert _series_rel([d[key] for d, _ in recs], [o[key] for _, o in recs]) <= 1e-5, key
+    for s in (0, 1):
+        xg, ug, _ = sim.particles(0, s)
+        xo, uo, _ = orc.particles_f32(s)
+        for a, b in zip(sorted_state(xg, ug), sorted_state(xo, uo)):
+            np.testing.assert_array_equal(a, b)
+    sim.close()
+
+
+@pytest.mark.parametrize("law", [W.SEE_FIXED, W.SEE_EXP, W.SEE_LOGNORMAL])
+@pytest.mark.parametrize("ions,amp", [(40, 30.0), (3000, 30.0), (3000, 0.7), (60_000, 6.0)])
+def test_many_electrons_per_ion(ions, amp, law):
+    # ions that reach the grounded electrode in the first steps: from a few of them
+    # in one workgroup's wave to several rounds of one workgroup (its grid is one) and
+    # the gap's list (room for an eighth of the ion slots)
+    cfg = W.config2(n_cells=200, beam_per_step=7, weight=1.0).replace(
+        see_amp=amp, see_max=70, see_law=law, see_ln_mu=1.2, see_ln_sigma=0.8)
+    rng = np.random.default_rng(ions)
+    v = 3e6
+    x = cfg.d - rng.uniform(0.0, 3.0, ions) * v * cfg.dt
+    from paper_2603_24010_amd import gapsim as gs
+    sim, orc, recs = run_pair(cfg, {1: (x, np.full(ions, v))}, oracle.WEAK, 4, True,
+                              (80 * ions + 1000, 10 * ions + 1000), {gs.OPT_GRID: 1} if ions > 3000 else None)
+    assert recs[-1][0]["emit_cum"].sum() > 0.3 * min(amp, 60.0) * ions
+    _check(sim, orc, recs)
+
+
+@pytest.mark.parametrize("cells,n,beam", [
+    (64, 0, 0), (64, 0, 5), (64, 1, 3), (64, 2048, 1), (64, 2049, 3000),
+    (64, 120_000, 40), (700, 600_001, 90), (4096, 600_001, 1000), (16384, 40_000, 17),
+])
+@pytest.mark.parametrize("opts", [{}, {"OPT_STREAM": 1}, {"OPT_STEAL": 4}, {"OPT_GRID": 3}, {"OPT_BLOCK": 1024}])
+def test_split_of_small_work(cells, n, beam, opts):
+    from paper_2603_24010_amd import gapsim as gs
+    cfg = W.config2(n_cells=cells, beam_per_step=beam, weight=1e3)
+    loads = {}
+    if n:
+        rng = np.random.default_rng(n + cells)
+        loads = {0: (rng.uniform(0, cfg.d, n // 3 + 1), rng.normal(0, 4e6, n // 3 + 1)),
+                 1: (rng.uniform(0, cfg.d, n), rng.uniform(4e5, 3e6, n))}
+    sim, orc, recs = run_pair(cfg, loads, oracle.STRICT, 3, True, (n + 20_000, n + 20_000),
+                              {getattr(gs, k): v for k, v in opts.items()})
+    _check(sim, orc, recs)
