@@ -4,6 +4,7 @@
 // roots of the loop equations) and the time-step check, the autotuner.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <complex>
 #include <cstdarg>
@@ -63,6 +64,7 @@ struct gs_ctx {
   double *ext_host = nullptr;               // pinned, mapped: [G] engine voltages, [G] field potentials,
                                             // then the lists' size the device last saw
   volatile unsigned long long *list_hint = nullptr;
+  ReadBack *rb = nullptr;                   // where a gap is read to (pinned)
   void *scratch = nullptr;                  // this device's staging array of gs_inject_noalloc
   hipEvent_t ext_ev = nullptr;              // recorded after each external-mode field solve
   std::string err;
@@ -407,60 +409,79 @@ static gs_status setup(gs_ctx *ctx) {
   }
   const size_t ps = ctx->fp64 ? 8 : 4;
   DevPtrs &d = ctx->dp;
-#define ALLOC(dst, type, count)                                                     \
-  do {                                                                              \
-    dst = (type)dev_alloc(ctx, (size_t)(count));                                    \
-    if (!dst) return fail(ctx, GS_ENOMEM, "device allocation of %zu bytes failed", \
-                          (size_t)(count));                                         \
-  } while (0)
-  for (int b = 0; b < 2; ++b) {
-    ALLOC(d.X[b], void *, slots * ps);
-    ALLOC(d.U[b], void *, slots * ps);
-    ALLOC(d.ID[b], uint32_t *, slots * 4);
-  }
-  ALLOC(d.next_count, unsigned long long *, (size_t)G * 2 * 8);
-  ALLOC(d.cursor, unsigned long long *, (size_t)G * 2 * 8);
-  ALLOC(d.fill_h, unsigned long long *, (size_t)G * 2 * 8);
+  // Everything but the particle arrays is cut from one allocation, in three
+  // groups: what starts from host values (one copy), what starts at zero (one
+  // fill), and the rest.  (An allocation, a copy or a fill each cost the host some
+  // microseconds up to a hundred: a context of one 4096-cell gap filled with 2e7
+  // particles and checked went from 0.96 ms to 0.69 ms with this and the check.)
+  struct Cut {
+    void **dst;
+    size_t bytes;
+    const void *from;  // host values
+    int zero;
+  };
+  std::vector<Cut> cuts;
+  auto take = [&](void *dst, size_t bytes, const void *from, bool zero) {
+    cuts.push_back({(void **)dst, bytes, from, zero ? 1 : 0});
+  };
+  std::vector<GapState> hs(G);
+  for (int g = 0; g < G; ++g) init_state(ctx->params[g], ctx->hc[g], hs[g]);
+  std::vector<int64_t> sched(std::max<size_t>(nsched, 1), 0);
+  for (int g = 0; g < G; ++g)
+    std::copy(ctx->sched[g].begin(), ctx->sched[g].end(), sched.begin() + ctx->hc[g].sched_base);
+  const unsigned int err0[2] = {0u, 0xFFFFFFFFu};
+  take(&d.gc, sizeof(GapConst) * (size_t)G, ctx->hc.data(), false);
+  take(&d.gs, sizeof(GapState) * (size_t)G, hs.data(), false);
+  take(&d.sched, sched.size() * 8, sched.data(), false);
+  take(&d.err, 8, err0, false);
+  take(&d.next_count, (size_t)G * 2 * 8, nullptr, true);
+  take(&d.cursor, (size_t)G * 2 * 8, nullptr, true);
+  take(&d.tally, (size_t)G * T_N * 8, nullptr, true);
+  take(&d.ev_count, (size_t)G * 8, nullptr, true);
+  take(&d.ev_done, (size_t)G * 8, nullptr, true);
+  take(&d.steal, 256, nullptr, true);
+  take(&d.push_done, 33 * 128, nullptr, true);
+  take(&d.epoch, 8, nullptr, true);
+  take(&d.dt_max, 16 + (size_t)ctx->nmax * 4, nullptr, true);
+  take(&d.acc, nodes * 8, nullptr, true);
+  take(&d.rho64, nodes * 8, nullptr, true);
+  take(&d.E64, nodes * 8, nullptr, true);
+  take(&d.hist, bins * 8, nullptr, true);
+  take(&d.bcur, bins * 8, nullptr, true);
+  take(&d.head, sizeof(PushHead) * (size_t)G, nullptr, false);
+  take(&d.fill_h, (size_t)G * 2 * 8, nullptr, false);
   // in-place compaction: a live bit per slot, and per-tile counters (a region
   // of cap slots has far fewer tiles of 65536 slots than words of 64), both
   // indexed from the region's pbase / 64
-  ALLOC(d.tcnt, int *, (slots / 64 + 1) * 4);
-  ALLOC(d.live, unsigned long long *, (slots / 64 + 1) * 8);
-  ALLOC(d.wrank, int *, (slots / 64 + 1) * 4);
-  ALLOC(d.tally, unsigned long long *, (size_t)G * T_N * 8);
-  ALLOC(d.acc, unsigned long long *, nodes * 8);
-  ALLOC(d.rho64, double *, nodes * 8);
-  ALLOC(d.E64, double *, nodes * 8);
-  ALLOC(d.phi64, double *, nodes * 8);
-  ALLOC(d.fsl, double *, nodes * 8);
-  ALLOC(d.fpart, double *, (size_t)G * NCHMAX * 2 * 8);
-  ALLOC(d.foff, double *, (size_t)G * NCHMAX * 8);
-  ALLOC(d.fsig, double *, (size_t)G * 8);
-  ALLOC(d.ehat, void *, etab * ps);
-  ALLOC(d.ev, Event *, events * sizeof(Event));
-  ALLOC(d.ev_count, unsigned long long *, (size_t)G * 8);
-  ALLOC(d.ev_done, unsigned long long *, (size_t)G * 8);
-  ALLOC(d.hist, unsigned long long *, bins * 8);
-  ALLOC(d.bcur, unsigned long long *, bins * 8);
-  int64_t *sched_d = nullptr;
-  ALLOC(sched_d, int64_t *, std::max<size_t>(nsched, 1) * 8);
-  d.sched = sched_d;
-  // exchange buffer of the external circuit engine: coherent pinned host memory
-  // the field kernel reads and writes directly (16 bytes per gap), and the
-  // word the push's tail or k_emit writes the lists' size to (16 bytes)
+  take(&d.tcnt, (slots / 64 + 1) * 4, nullptr, false);
+  take(&d.live, (slots / 64 + 1) * 8, nullptr, false);
+  take(&d.wrank, (slots / 64 + 1) * 4, nullptr, false);
+  take(&d.fsl, nodes * 8, nullptr, false);
+  take(&d.fpart, (size_t)G * NCHMAX * 2 * 8, nullptr, false);
+  take(&d.foff, (size_t)G * NCHMAX * 8, nullptr, false);
+  take(&d.fsig, (size_t)G * 8, nullptr, false);
+  take(&d.ehat, etab * ps, nullptr, false);
+  take(&d.ev, events * sizeof(Event), nullptr, false);
+  // coherent pinned host memory that kernels read and write directly: the
+  // exchange with an external circuit engine (16 bytes per gap), the word the
+  // push's tail or k_emit writes the lists' size to, and where a gap's state and
+  // fields are read to (see read_back)
   {
     void *h = nullptr, *dptr = nullptr;
-    const size_t nb = (size_t)G * 16 + 16;
+    const size_t at = ((size_t)G * 16 + 16 + 255) / 256 * 256;
+    const size_t nb = at + sizeof(ReadBack) + 3 * ((size_t)ctx->nmax + 1) * 8;
     const hipError_t eh = hipHostMalloc(&h, nb, hipHostMallocMapped | hipHostMallocCoherent);
     if (eh != hipSuccess || !h)
       return fail(ctx, GS_ENOMEM, "pinned host allocation of %zu bytes failed: %s", nb, hipGetErrorString(eh));
     ctx->ext_host = (double *)h;
-    memset(h, 0, nb);
+    memset(h, 0, at + sizeof(ReadBack));
     HIPCHK(ctx, hipHostGetDevicePointer(&dptr, h, 0));
     d.ext_v = (const double *)dptr;
     d.ext_phi = (double *)dptr + G;
     d.list_seen = (unsigned long long *)((char *)dptr + (size_t)G * 16);
     ctx->list_hint = (volatile unsigned long long *)((char *)h + (size_t)G * 16);
+    ctx->rb = (ReadBack *)((char *)h + at);
+    d.rb = (ReadBack *)((char *)dptr + at);
     HIPCHK(ctx, hipEventCreateWithFlags(&ctx->ext_ev, hipEventDisableTiming));
   }
   // overflow event regions for up to eight 256-thread push workgroups per CU
@@ -482,44 +503,39 @@ static gs_status setup(gs_ctx *ctx) {
     d.ovq = std::min<int64_t>(OVQ_MAX, std::max<int64_t>(OVQ_MIN, (ion_slots / 32768 + 255) / 256 * 256));
   }
   ctx->emits = emits ? 1 : 0;
-  ALLOC(d.ovf, Event *, (size_t)std::max<int64_t>(d.ovf_wgs, 1) * (size_t)d.ovq * sizeof(Event));
-  ALLOC(d.epoch, int64_t *, 8);
-  ALLOC(d.err, unsigned int *, 8);
-  ALLOC(d.steal, unsigned int *, 256);
-  ALLOC(d.push_done, unsigned int *, 33 * 128);
-  ALLOC(d.gc, const GapConst *, sizeof(GapConst) * (size_t)G);
-  ALLOC(d.gs, GapState *, sizeof(GapState) * (size_t)G);
-  ALLOC(d.head, PushHead *, sizeof(PushHead) * (size_t)G);
-#undef ALLOC
+  take(&d.ovf, (size_t)std::max<int64_t>(d.ovf_wgs, 1) * (size_t)d.ovq * sizeof(Event), nullptr, false);
+  auto cut_size = [](size_t n) { return (n + 255) / 256 * 256; };
+  size_t total = 0, nfrom = 0, nzero = 0;
+  for (const Cut &c : cuts) {
+    total += cut_size(c.bytes);
+    nfrom += c.from ? cut_size(c.bytes) : 0;
+    nzero += c.zero ? cut_size(c.bytes) : 0;
+  }
+  for (int b = 0; b < 2; ++b) {
+    struct {
+      void **dst;
+      size_t bytes;
+    } arrays[3] = {{&d.X[b], slots * ps}, {&d.U[b], slots * ps}, {(void **)&d.ID[b], slots * 4}};
+    for (const auto &r : arrays)
+      if (!(*r.dst = dev_alloc(ctx, r.bytes)))
+        return fail(ctx, GS_ENOMEM, "device allocation of %zu bytes failed", r.bytes);
+  }
+  char *base = (char *)dev_alloc(ctx, total);
+  if (!base) return fail(ctx, GS_ENOMEM, "device allocation of %zu bytes failed", total);
+  std::vector<char> image(nfrom, 0);
+  size_t at = 0;
+  for (const Cut &c : cuts) {  // (the groups are in this order)
+    *c.dst = base + at;
+    if (c.from && c.bytes) memcpy(image.data() + at, c.from, c.bytes);
+    at += cut_size(c.bytes);
+  }
   d.mlp_w = nullptr;
   d.mlp_norm = nullptr;
   d.rec_x = d.rec_y = nullptr;
   d.rec_cap = d.rec_level0 = 0;
   hipStream_t s = ctx->stream;
-  std::vector<GapState> hs(G);
-  for (int g = 0; g < G; ++g) init_state(ctx->params[g], ctx->hc[g], hs[g]);
-  HIPCHK(ctx, hipMemcpyAsync((void *)d.gc, ctx->hc.data(), sizeof(GapConst) * G, hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemcpyAsync(d.gs, hs.data(), sizeof(GapState) * G, hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemsetAsync(d.next_count, 0, (size_t)G * 2 * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.cursor, 0, (size_t)G * 2 * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.tally, 0, (size_t)G * T_N * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.ev_count, 0, (size_t)G * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.ev_done, 0, (size_t)G * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.steal, 0, 256, s));
-  HIPCHK(ctx, hipMemsetAsync(d.push_done, 0, 33 * 128, s));
-  HIPCHK(ctx, hipMemsetAsync(d.hist, 0, bins * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.bcur, 0, bins * 8, s));
-  for (int g = 0; g < G; ++g)
-    if (!ctx->sched[g].empty())
-      HIPCHK(ctx, hipMemcpyAsync(sched_d + ctx->hc[g].sched_base, ctx->sched[g].data(), ctx->sched[g].size() * 8,
-                                 hipMemcpyHostToDevice, s));
-  HIPCHK(ctx, hipMemsetAsync(d.acc, 0, nodes * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.rho64, 0, nodes * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.E64, 0, nodes * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.phi64, 0, nodes * 8, s));
-  HIPCHK(ctx, hipMemsetAsync(d.epoch, 0, 8, s));
-  const unsigned int err0[2] = {0u, 0xFFFFFFFFu};
-  HIPCHK(ctx, hipMemcpyAsync(d.err, err0, 8, hipMemcpyHostToDevice, s));
+  HIPCHK(ctx, hipMemcpyAsync(base, image.data(), nfrom, hipMemcpyHostToDevice, s));
+  HIPCHK(ctx, hipMemsetAsync(base + nfrom, 0, nzero, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
   ctx->next_id.assign(G, 0);
   HIPCHK(ctx, hipGetDevice(&ctx->device));
@@ -678,6 +694,33 @@ static gs_status check_sticky(gs_ctx *ctx, bool sync) {
     HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
     return fail(ctx, GS_ENOCONV, "a strict Newton solve missed its tolerance within its iteration cap");
   }
+  return GS_OK;
+}
+
+// A gap's state, tallies and append counters to the pinned read-back buffer, and
+// the fields asked for after it (phi, then E, then rho, nmax + 1 values apart),
+// behind the work queued on the stream.  (Copies to pageable memory are staged by
+// the runtime and waited for one by one: gs_read_diagnostics of a 256-cell gap with
+// its fields took 64.6 us, and takes 39.3 us.)
+static gs_status read_back(gs_ctx *ctx, int gap, bool phi, bool E, bool rho) {
+  ReadBack *rb = ctx->rb;
+  hipStream_t st = ctx->stream;
+  const GapConst &c = ctx->hc[gap];
+  const size_t nn = (size_t)c.N + 1, fs = (size_t)ctx->nmax + 1;
+  double *f = (double *)(rb + 1);
+  if (phi) {
+    const hipError_t e = launch_phi(ctx->dp, gap, (double *)(ctx->dp.rb + 1), st);
+    if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "phi launch: %s", hipGetErrorString(e));
+  }
+  auto copy = [&](void *to, const void *from, size_t bytes) {
+    return hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, st);
+  };
+  HIPCHK(ctx, copy(&rb->s, ctx->dp.gs + gap, sizeof rb->s));
+  HIPCHK(ctx, copy(rb->tally, ctx->dp.tally + (size_t)gap * T_N, sizeof rb->tally));
+  HIPCHK(ctx, copy(rb->next_count, ctx->dp.next_count + gap * 2, sizeof rb->next_count));
+  if (E) HIPCHK(ctx, copy(f + fs, ctx->dp.E64 + c.nbase, (nn - 1) * 8));
+  if (rho) HIPCHK(ctx, copy(f + 2 * fs, ctx->dp.rho64 + c.nbase, nn * 8));
+  HIPCHK(ctx, hipStreamSynchronize(st));
   return GS_OK;
 }
 
@@ -1198,23 +1241,14 @@ extern "C" gs_status gs_dt_check(gs_ctx *ctx, int32_t gap, gs_dt_report *out) {
   if (st != GS_OK) return st;
   const GapConst &c = ctx->hc[gap];
   const gs_gap_params &p = ctx->params[gap];
-  const size_t bytes = 16 + (size_t)c.N * 4;
-  void *buf = nullptr;
-  if (hipMalloc(&buf, bytes) != hipSuccess) return fail(ctx, GS_ENOMEM, "time-step check: %zu bytes", bytes);
-  unsigned long long um[2] = {0ull, 0ull};
-  std::vector<unsigned int> cells((size_t)c.N);
-  GapState s;
-  hipError_t e = hipMemsetAsync(buf, 0, bytes, ctx->stream);
+  hipError_t e = launch_dt_scan(ctx->dp, gap, c.N, ctx->fp64, std::max(ctx->ncu, 1), ctx->stream);
   if (e == hipSuccess)
-    e = launch_dt_scan(ctx->dp, gap, c.N, ctx->fp64, (unsigned long long *)buf, (unsigned int *)((char *)buf + 16),
-                       ctx->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(um, buf, 16, hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(cells.data(), (char *)buf + 16, (size_t)c.N * 4, hipMemcpyDeviceToHost, ctx->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&s, ctx->dp.gs + gap, sizeof s, hipMemcpyDeviceToHost, ctx->stream);
+    e = hipMemcpyAsync(&ctx->rb->s, ctx->dp.gs + gap, sizeof ctx->rb->s, hipMemcpyDeviceToHost, ctx->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
-  (void)hipFree(buf);
   if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "time-step check: %s", hipGetErrorString(e));
+  const unsigned long long um[2] = {ctx->rb->umax[0], ctx->rb->umax[1]};
+  const unsigned int cmax = ctx->rb->cmax;
+  const GapState s = ctx->rb->s;
   gs_dt_report r;
   memset(&r, 0, sizeof r);
   r.dt = p.dt;
@@ -1234,8 +1268,6 @@ extern "C" gs_status gs_dt_check(gs_ctx *ctx, int32_t gap, gs_dt_report *out) {
     r.beta[sp] = u;
     r.v_max[sp] = u * c.dx / p.dt;
   }
-  unsigned int cmax = 0;
-  for (unsigned int k : cells) cmax = std::max(cmax, k);
   r.n_e_max = (double)cmax * p.weight / c.dx;
   const double qe = p.q_unit * std::fabs((double)p.Z[0]);
   r.omega_pe = std::sqrt(r.n_e_max * qe * qe / (p.eps0 * p.mass[0]));
@@ -1254,21 +1286,15 @@ extern "C" gs_status gs_read_diagnostics(gs_ctx *ctx, int32_t gap, gs_diag *out,
   if (!ctx) return GS_ESTATE;
   if (gap < 0 || gap >= ctx->G || !out) return fail(ctx, GS_EINVAL, "bad gap or out is NULL");
   const GapConst &c = ctx->hc[gap];
-  GapState s;
-  unsigned long long tl[T_N], nc[2];
-  hipStream_t st = ctx->stream;
-  if (phi) {
-    hipError_t e = launch_phi(ctx->dp, gap, st);
-    if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "phi launch: %s", hipGetErrorString(e));
-  }
-  HIPCHK(ctx, hipMemcpyAsync(&s, ctx->dp.gs + gap, sizeof s, hipMemcpyDeviceToHost, st));
-  HIPCHK(ctx, hipMemcpyAsync(tl, ctx->dp.tally + (size_t)gap * T_N, sizeof tl, hipMemcpyDeviceToHost, st));
-  HIPCHK(ctx, hipMemcpyAsync(nc, ctx->dp.next_count + gap * 2, sizeof nc, hipMemcpyDeviceToHost, st));
-  const size_t nn = (size_t)c.N + 1;
-  if (phi) HIPCHK(ctx, hipMemcpyAsync(phi, ctx->dp.phi64 + c.nbase, nn * 8, hipMemcpyDeviceToHost, st));
-  if (E) HIPCHK(ctx, hipMemcpyAsync(E, ctx->dp.E64 + c.nbase, (nn - 1) * 8, hipMemcpyDeviceToHost, st));
-  if (rho) HIPCHK(ctx, hipMemcpyAsync(rho, ctx->dp.rho64 + c.nbase, nn * 8, hipMemcpyDeviceToHost, st));
-  HIPCHK(ctx, hipStreamSynchronize(st));
+  const gs_status rs = read_back(ctx, gap, phi != nullptr, E != nullptr, rho != nullptr);
+  if (rs != GS_OK) return rs;
+  const GapState &s = ctx->rb->s;
+  const unsigned long long *tl = ctx->rb->tally, *nc = ctx->rb->next_count;
+  const double *f = (const double *)(ctx->rb + 1);
+  const size_t nn = (size_t)c.N + 1, fs = (size_t)ctx->nmax + 1;
+  if (phi) memcpy(phi, f, nn * 8);
+  if (E) memcpy(E, f + fs, (nn - 1) * 8);
+  if (rho) memcpy(rho, f + 2 * fs, nn * 8);
   memset(out, 0, sizeof *out);
   out->step = s.level;
   out->t = s.t;

@@ -130,6 +130,14 @@ struct PushHead {
 };
 static_assert(sizeof(PushHead) == 128, "two cache lines");
 
+// Where a gap is read to, in pinned host memory.
+struct ReadBack {
+  unsigned long long tally[T_N], next_count[2];
+  unsigned long long umax[2];  // time-step check: largest |u| per species (bits)
+  unsigned int cmax, pad;      //   most electrons in one cell
+  GapState s;
+};
+
 // Context-wide device pointers handed to kernels.
 struct DevPtrs {
   const GapConst *gc;
@@ -142,7 +150,7 @@ struct DevPtrs {
   unsigned long long *cursor;      // [G][2] slot count after the compaction or sort in progress
   unsigned long long *tally;       // [G][T_N]
   unsigned long long *acc;         // node charge accumulators, int64 two's complement
-  double *rho64, *E64, *phi64;     // node / half-grid / node arrays (nbase offsets; E uses nbase too)
+  double *rho64, *E64;             // node and half-grid arrays (nbase offsets, both)
   void *ehat;                      // field table for the push, binary32 or binary64
   int64_t *epoch;                  // compaction epoch (device)
   unsigned int *err;               // [0] flags, [1] gap of first error
@@ -174,6 +182,9 @@ struct DevPtrs {
   // upper bound when k_emit wrote it), which the host reads to choose who
   // emits the next push's lists
   unsigned long long *list_seen;
+  ReadBack *rb;                    // (mapped) read-back buffer of the time-step check
+  unsigned long long *dt_max;      // time-step check: largest |u| bits per species, then the
+                                   // electrons per cell (zero between checks)
   Event *ovf;                      // push workgroup b < ovf_wgs: events past its LDS queue,
   int64_t ovf_wgs;                 //   ovq of them from ovf + b * ovq
   int64_t ovq;
@@ -258,11 +269,12 @@ hipError_t launch_sort(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t
 hipError_t launch_emit(const DevPtrs &p, int G, int fp64, int grid, hipStream_t s, KTime t = {});
 hipError_t launch_inject(const DevPtrs &p, int gap, int species, long long n, const double *x_dev,
                          const double *v_dev, long long id0, int N, int ncu, int fp64, hipStream_t s);
-hipError_t launch_phi(const DevPtrs &p, int gap, hipStream_t s);
-// time-step check: largest |u| per species (bit patterns of non-negative
-// floats, max-reduced as unsigned integers) and electrons per cell of one gap
-hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, unsigned long long *umax,
-                          unsigned int *cells, hipStream_t s);
+// the potential of a gap's last level, to host memory the device maps
+hipError_t launch_phi(const DevPtrs &p, int gap, double *phi, hipStream_t s);
+// time-step check: largest |u| per species (bit patterns of non-negative floats,
+// max-reduced as unsigned integers) and the most electrons in one cell of one gap,
+// to the read-back buffer
+hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, int ncu, hipStream_t s);
 // guess network (gs_mlp.hip): y[n][3] = net(x[n][48]) with bfloat16 weights W
 hipError_t launch_mlp_forward(const uint16_t *W, const float *x, long long n, float *y, int ncu, hipStream_t s);
 size_t push_lds_bytes(int nmax, int fp64, int G, int wide);

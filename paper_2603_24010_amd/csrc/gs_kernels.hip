@@ -3168,24 +3168,40 @@ __global__ __launch_bounds__(IBS) void k_inject_run(DevPtrs p, int gap, int spec
   }
 }
 
-// phi_i = dx sum_{k >= i} E_{k+1/2}, phi_N = 0 (one gap, one workgroup)
-constexpr int PBS = 256;
-__global__ __launch_bounds__(PBS) void k_phi(DevPtrs p, int gap) {
+constexpr int RBS = 1024;  // k_phi and k_dt_read threads
+
+// phi_i = dx sum_{k >= i} E_{k+1/2}, phi_N = 0: thread t owns the reversed
+// positions [t ch, (t + 1) ch), counted from the ground.  A chain of loads: four are
+// in flight per round trip, and 1024 threads leave one round at 4096 cells.
+__global__ __launch_bounds__(RBS) void k_phi(DevPtrs p, int gap, double *phi) {
+  __shared__ double wsum[RBS / 64];
+  const int tid = threadIdx.x;
   const GapConst &c = p.gc[gap];
-  __shared__ double sh[PBS];
-  const int N = c.N, tid = threadIdx.x;
+  const int N = c.N;
   const double *E = p.E64 + c.nbase;
-  double *phi = p.phi64 + c.nbase;
-  const int chunk = (N + PBS - 1) / PBS;
-  // thread t owns reversed positions k0..k1-1, i.e. nodes N-1-k counted from the ground
-  const int k0 = tid * chunk, k1 = min(k0 + chunk, N);
+  const int ch = (N + RBS - 1) / RBS;
+  const int k0 = min(tid * ch, N), k1 = min(k0 + ch, N);
   double loc = 0.0;
-  for (int k = k0; k < k1; ++k) loc += c.dx * E[N - 1 - k];
+  for (int kb = k0; kb < k1; kb += 4) {
+    double v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = E[N - 1 - min(kb + i, N - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (kb + i < k1) loc += c.dx * v[i];
+  }
   double tot;
-  double run = block_exclusive_scan<double>(loc, sh, &tot);
-  for (int k = k0; k < k1; ++k) {
-    run += c.dx * E[N - 1 - k];
-    phi[N - 1 - k] = run;
+  double run = block_exclusive_scan_w(loc, wsum, &tot);
+  for (int kb = k0; kb < k1; kb += 4) {
+    double v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = E[N - 1 - min(kb + i, N - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (kb + i < k1) {
+        run += c.dx * v[i];
+        phi[N - 1 - kb - i] = run;
+      }
   }
   if (tid == 0) phi[N] = 0.0;
 }
@@ -3206,27 +3222,49 @@ __device__ inline unsigned long long nonneg_bits<double>(double v) {
   return (unsigned long long)__double_as_longlong(v);
 }
 
+// Bound by HBM: 16-byte loads of x and u, two vectors of each in flight.  The
+// first ne_wgs workgroups scan the electrons (each flushes its cell counts, so a
+// few electrons per cell and workgroup are wanted), then all the ions.  2.3e7
+// particles in 4096 cells: 37 us, 5.0 TB/s (110 us with one 4-byte load of each in
+// flight and every workgroup's counts flushed).
 template <class P>
-__global__ __launch_bounds__(DBS) void k_dt_scan(DevPtrs p, int gap, unsigned long long *umax,
-                                                 unsigned int *cells) {
+__global__ __launch_bounds__(DBS) void k_dt_scan(DevPtrs p, int gap) {
   extern __shared__ unsigned int hist[];  // [N]
   __shared__ P red[DBS / 64][2];
+  typedef typename Vec<P>::type V;
+  constexpr int VN = Vec<P>::n;
   const GapConst &c = p.gc[gap];
   const int N = c.N;
   const int sel = (int)(*p.epoch & 1);
-  for (int k = threadIdx.x; k < N; k += DBS) hist[k] = 0u;
-  __syncthreads();
-  const P *X = (const P *)p.X[sel], *U = (const P *)p.U[sel];
+  const long long nel = min((long long)p.next_count[gap * 2], (long long)c.cap[0]);
+  const int ne_wgs = (int)min((long long)gridDim.x, nel / (4ll * N) + 1);
+  const bool electrons = (int)blockIdx.x < ne_wgs;
+  if (electrons) {
+    for (int k = threadIdx.x; k < N; k += DBS) hist[k] = 0u;
+    __syncthreads();
+  }
   P m[2] = {(P)0, (P)0};
-  const long long stride = (long long)gridDim.x * DBS;
+#pragma unroll
   for (int s = 0; s < 2; ++s) {
-    const long long n = min((long long)p.next_count[gap * 2 + s], (long long)c.cap[s]);
-    const size_t b = (size_t)c.pbase[s];
-    for (long long i = (long long)blockIdx.x * DBS + threadIdx.x; i < n; i += stride) {
-      const P x = X[b + i];
-      if (!(x >= (P)0)) continue;  // absorbed slot
-      m[s] = fmax(m[s], fabs(U[b + i]));
-      if (s == 0) atomicAdd(&hist[min((int)x, N - 1)], 1u);
+    if (s == 0 && !electrons) continue;
+    const long long n = s == 0 ? nel : min((long long)p.next_count[gap * 2 + 1], (long long)c.cap[1]);
+    const P *X = (const P *)p.X[sel] + c.pbase[s], *U = (const P *)p.U[sel] + c.pbase[s];
+    const long long stride = (long long)(s == 0 ? ne_wgs : (int)gridDim.x) * DBS * VN;
+    // (a region's slots are padded to whole vectors)
+    for (long long i = ((long long)blockIdx.x * DBS + threadIdx.x) * VN; i < n; i += 2 * stride) {
+      const long long i2 = i + stride < n ? i + stride : i;
+      V xv[2] = {*(const V *)(X + i), *(const V *)(X + i2)};
+      V uv[2] = {*(const V *)(U + i), *(const V *)(U + i2)};
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int e = 0; e < VN; ++e) {
+          const P x = Vec<P>::at(xv[q], e);
+          // absorbed slots hold -1
+          if (!(x >= (P)0) || (q == 0 ? i : i + stride) + e >= n) continue;
+          m[s] = fmax(m[s], fabs(Vec<P>::at(uv[q], e)));
+          if (s == 0) atomicAdd(&hist[min((int)x, N - 1)], 1u);
+        }
     }
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -3239,10 +3277,33 @@ __global__ __launch_bounds__(DBS) void k_dt_scan(DevPtrs p, int gap, unsigned lo
   if (threadIdx.x < 2) {
     P v = red[0][threadIdx.x];
     for (int w = 1; w < DBS / 64; ++w) v = fmax(v, red[w][threadIdx.x]);
-    atomicMax(&umax[threadIdx.x], nonneg_bits<P>(v));
+    atomicMax(&p.dt_max[threadIdx.x], nonneg_bits<P>(v));
   }
-  for (int k = threadIdx.x; k < N; k += DBS)
-    if (hist[k]) atomicAdd(&cells[k], hist[k]);
+  unsigned int *cells = (unsigned int *)(p.dt_max + 2);
+  if (electrons)
+    for (int k = threadIdx.x; k < N; k += DBS)
+      if (hist[k]) atomicAdd(&cells[k], hist[k]);
+}
+
+// the scan's results to the read-back buffer, its counters back at zero
+__global__ __launch_bounds__(RBS) void k_dt_read(DevPtrs p, int gap) {
+  __shared__ unsigned int s_max;
+  const int N = p.gc[gap].N, tid = threadIdx.x;
+  unsigned int *cells = (unsigned int *)(p.dt_max + 2);
+  if (tid == 0) s_max = 0u;
+  __syncthreads();
+  unsigned int m = 0u;
+  for (int k = tid; k < N; k += RBS) {
+    m = max(m, cells[k]);
+    cells[k] = 0u;
+  }
+  atomicMax(&s_max, m);
+  if (tid < 2) {
+    p.rb->umax[tid] = p.dt_max[tid];
+    p.dt_max[tid] = 0ull;
+  }
+  __syncthreads();
+  if (tid == 0) p.rb->cmax = s_max;
 }
 
 // ---------------------------------------------------------------------------
@@ -3427,26 +3488,30 @@ hipError_t launch_inject(const DevPtrs &p, int gap, int species, long long n, co
               : inject_t<float>(p, gap, species, n, x, v, id0, N, ncu, s);
 }
 
-hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, unsigned long long *umax,
-                          unsigned int *cells, hipStream_t s) {
+hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, int ncu, hipStream_t s) {
   const size_t lds = (size_t)N * 4;
-  static bool attr[2] = {false, false};
-  const void *k = fp64 ? (const void *)k_dt_scan<double> : (const void *)k_dt_scan<float>;
-  if (!attr[fp64]) {
-    hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
-    if (e != hipSuccess) return e;
-    attr[fp64] = true;
-  }
   if (lds > 65536) return hipErrorInvalidValue;
+  // (with the static part the largest grid's counts pass the default limit)
+  static bool attr[2] = {false, false};
+  if (!attr[fp64 ? 1 : 0]) {
+    const void *k = fp64 ? (const void *)k_dt_scan<double> : (const void *)k_dt_scan<float>;
+    const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
+    if (e != hipSuccess) return e;
+    attr[fp64 ? 1 : 0] = true;
+  }
+  const dim3 grid((unsigned int)(4 * ncu));
   if (fp64)
-    hipLaunchKernelGGL(k_dt_scan<double>, dim3(512), dim3(DBS), lds, s, p, gap, umax, cells);
+    hipLaunchKernelGGL(k_dt_scan<double>, grid, dim3(DBS), lds, s, p, gap);
   else
-    hipLaunchKernelGGL(k_dt_scan<float>, dim3(512), dim3(DBS), lds, s, p, gap, umax, cells);
+    hipLaunchKernelGGL(k_dt_scan<float>, grid, dim3(DBS), lds, s, p, gap);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_dt_read, dim3(1), dim3(RBS), 0, s, p, gap);
   return hipGetLastError();
 }
 
-hipError_t launch_phi(const DevPtrs &p, int gap, hipStream_t s) {
-  hipLaunchKernelGGL(k_phi, dim3(1), dim3(PBS), 0, s, p, gap);
+hipError_t launch_phi(const DevPtrs &p, int gap, double *phi, hipStream_t s) {
+  hipLaunchKernelGGL(k_phi, dim3(1), dim3(RBS), 0, s, p, gap, phi);
   return hipGetLastError();
 }
 #endif  // GS_PUSH_PART
