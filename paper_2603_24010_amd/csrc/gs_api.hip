@@ -387,8 +387,9 @@ static gs_status setup(gs_ctx *ctx) {
     slots += pad((size_t)c.cap[0]);
     c.pbase[1] = (int64_t)slots;
     slots += pad((size_t)c.cap[1]);
+    // (whole runs of acc_row_at)
     c.nbase = (int64_t)nodes;
-    nodes += (size_t)c.N + 1;
+    nodes += ((size_t)c.N + 1 + 31) / 32 * 32;
     // absorbed-ion events of one push: up to an eighth of the ion slots
     c.evbase = (int64_t)events;
     c.evcap = (ctx->params[g].see_amp > 0.0) ? (int64_t)(c.cap[1] / 8 + 4096) : 0;
@@ -436,7 +437,7 @@ static gs_status setup(gs_ctx *ctx) {
   take(&d.err, 8, err0, false);
   take(&d.next_count, (size_t)G * 2 * 8, nullptr, true);
   take(&d.cursor, (size_t)G * 2 * 8, nullptr, true);
-  take(&d.tally, (size_t)G * T_N * 8, nullptr, true);
+  take(&d.tally, (size_t)G * TALLY_ROWS * TALLY_ROW * 8, nullptr, true);
   take(&d.ev_count, (size_t)G * 8, nullptr, true);
   take(&d.ev_done, (size_t)G * 8, nullptr, true);
   take(&d.steal, 256, nullptr, true);
@@ -444,6 +445,12 @@ static gs_status setup(gs_ctx *ctx) {
   take(&d.epoch, 8, nullptr, true);
   take(&d.dt_max, 16 + (size_t)ctx->nmax * 4, nullptr, true);
   take(&d.acc, nodes * 8, nullptr, true);
+  int64_t most_slots = 0;
+  for (const GapConst &c : ctx->hc) most_slots = std::max(most_slots, c.cap[0] + c.cap[1]);
+  if (ctx->nmax <= ACC_ROWS_NMAX && G <= ACC_ROWS_GAPS && most_slots >= ACC_ROWS_SLOTS)
+    take(&d.acc_rows, nodes * ACC_ROWS * 8, nullptr, true);
+  else
+    d.acc_rows = nullptr;
   take(&d.rho64, nodes * 8, nullptr, true);
   take(&d.E64, nodes * 8, nullptr, true);
   take(&d.hist, bins * 8, nullptr, true);
@@ -716,7 +723,7 @@ static gs_status read_back(gs_ctx *ctx, int gap, bool phi, bool E, bool rho) {
     return hipMemcpyAsync(to, from, bytes, hipMemcpyDeviceToHost, st);
   };
   HIPCHK(ctx, copy(&rb->s, ctx->dp.gs + gap, sizeof rb->s));
-  HIPCHK(ctx, copy(rb->tally, ctx->dp.tally + (size_t)gap * T_N, sizeof rb->tally));
+  HIPCHK(ctx, copy(rb->tally, ctx->dp.tally + (size_t)gap * TALLY_ROWS * TALLY_ROW, sizeof rb->tally));
   HIPCHK(ctx, copy(rb->next_count, ctx->dp.next_count + gap * 2, sizeof rb->next_count));
   if (E) HIPCHK(ctx, copy(f + fs, ctx->dp.E64 + c.nbase, (nn - 1) * 8));
   if (rho) HIPCHK(ctx, copy(f + 2 * fs, ctx->dp.rho64 + c.nbase, nn * 8));
@@ -1289,7 +1296,10 @@ extern "C" gs_status gs_read_diagnostics(gs_ctx *ctx, int32_t gap, gs_diag *out,
   const gs_status rs = read_back(ctx, gap, phi != nullptr, E != nullptr, rho != nullptr);
   if (rs != GS_OK) return rs;
   const GapState &s = ctx->rb->s;
-  const unsigned long long *tl = ctx->rb->tally, *nc = ctx->rb->next_count;
+  unsigned long long tl[T_N] = {};
+  for (int r = 0; r < TALLY_ROWS; ++r)
+    for (int t = 0; t < T_N; ++t) tl[t] += ctx->rb->tally[r * TALLY_ROW + t];
+  const unsigned long long *nc = ctx->rb->next_count;
   const double *f = (const double *)(ctx->rb + 1);
   const size_t nn = (size_t)c.N + 1, fs = (size_t)ctx->nmax + 1;
   if (phi) memcpy(phi, f, nn * 8);

@@ -30,6 +30,24 @@ enum {
   T_PUSHED = 7,   // live particles pushed
   T_N = 8
 };
+// A gap's tallies, and on small grids its node sums, lie in rows: workgroups whose
+// blockIdx differs modulo the rows add to different ones, and the field solve takes
+// their sum.  Additions of many workgroups to one address are done one after the
+// other, 24 ns each (568 workgroups adding 513 nodes: 15.1 us to one row, 4.9 us to
+// four, 3.7 us to eight, while the field solve reads and clears a row more for each).
+constexpr int TALLY_ROWS = 4;   // 128 bytes apart
+constexpr int TALLY_ROW = 16;
+constexpr int ACC_ROWS = 4;
+// node k of row r, counted from ACC_ROWS times the gap's node offset: runs of 32
+// nodes, so that the rows spread over the memory channels
+__host__ __device__ inline int acc_row_at(int k, int r) { return (k & ~31) * ACC_ROWS + r * 32 + (k & 31); }
+// Grids and contexts whose node sums have rows.  With more nodes the additions are
+// bound by their number (4097 nodes, 256 workgroups: 8.8 us to one row, 7.8 to four);
+// with more gaps, or fewer slots than 256 tiles of 2048, a gap has few workgroups, and
+// the field solve's reads cost more (1e5 particles, 256 cells: 19.6 us a step, 19.3
+// with one row; 1e6 particles, 512 cells: 28.6 and 37.6).
+constexpr int ACC_ROWS_NMAX = 2559, ACC_ROWS_GAPS = 16;
+constexpr int64_t ACC_ROWS_SLOTS = 1 << 19;
 
 // Per-gap constants (read-only on the device).
 struct GapConst {
@@ -132,7 +150,7 @@ static_assert(sizeof(PushHead) == 128, "two cache lines");
 
 // Where a gap is read to, in pinned host memory.
 struct ReadBack {
-  unsigned long long tally[T_N], next_count[2];
+  unsigned long long tally[TALLY_ROWS * TALLY_ROW], next_count[2];
   unsigned long long umax[2];  // time-step check: largest |u| per species (bits)
   unsigned int cmax, pad;      //   most electrons in one cell
   GapState s;
@@ -148,8 +166,9 @@ struct DevPtrs {
   uint32_t *ID[2];
   unsigned long long *next_count;  // [G][2] append cursor
   unsigned long long *cursor;      // [G][2] slot count after the compaction or sort in progress
-  unsigned long long *tally;       // [G][T_N]
+  unsigned long long *tally;       // [G][TALLY_ROWS][TALLY_ROW], T_N of a row used
   unsigned long long *acc;         // node charge accumulators, int64 two's complement
+  unsigned long long *acc_rows;    // more rows of them for the push's sums, or null (see acc_row_at)
   double *rho64, *E64;             // node and half-grid arrays (nbase offsets, both)
   void *ehat;                      // field table for the push, binary32 or binary64
   int64_t *epoch;                  // compaction epoch (device)

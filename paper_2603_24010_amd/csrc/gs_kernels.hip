@@ -309,6 +309,7 @@ __device__ __forceinline__ DevPtrs push_args() {
   as_global(p.next_count);
   as_global(p.tally);
   as_global(p.acc);
+  as_global(p.acc_rows);
   as_global(p.ehat);
   as_global(p.err);
   as_global(p.steal);
@@ -320,6 +321,11 @@ __device__ __forceinline__ DevPtrs push_args() {
   as_global(p.list_seen);
   as_global(p.ovf);
   return p;
+}
+
+// this workgroup's row of the gap's tallies
+__device__ inline unsigned long long *tally_row(const DevPtrs &p, int g) {
+  return p.tally + ((size_t)g * TALLY_ROWS + blockIdx.x % TALLY_ROWS) * TALLY_ROW;
 }
 
 // one of a pair by a run-time species or buffer (an index into a local struct would put it
@@ -865,6 +871,15 @@ __device__ void level_end(const DevPtrs &p, int g, const GapConst &c, GapState &
   }
 }
 
+// Tally word t of a gap, its rows' sum.
+__device__ inline unsigned long long tally_sum(const DevPtrs &p, int g, int t) {
+  const unsigned long long *row = p.tally + (size_t)g * TALLY_ROWS * TALLY_ROW + t;
+  unsigned long long v = 0ull;
+#pragma unroll
+  for (int r = 0; r < TALLY_ROWS; ++r) v += row[r * TALLY_ROW];
+  return v;
+}
+
 // k_field1: level n of one gap per workgroup, for grids up to FIELD1_NMAX
 // cells: the nodal density (the accumulator cleared for the next push), the
 // prefix sums S_k, the circuit and the surface charge, the half-grid field and
@@ -877,7 +892,8 @@ __device__ void level_end(const DevPtrs &p, int g, const GapConst &c, GapState &
 // MLP: strict steps that start Newton from the guess network (a variant of its
 // own, so that the weights' loads stand in no branch, where they would be waited
 // for)
-template <int BS, int NQ, bool MLP>
+// ROWS: the push's node sums are in rows (see ACC_ROWS)
+template <int BS, int NQ, bool MLP, bool ROWS>
 __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, double tol, int maxit, int fp64) {
   const int g = blockIdx.x, tid = threadIdx.x;
   extern __shared__ __align__(16) double Sk[];  // S_k, one per cell (padded, see the prefix sums)
@@ -909,6 +925,18 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
     const unsigned long long *a0 = p.acc + p.gc[g].nbase;
 #pragma unroll
     for (int q = 0; q < NQ; ++q) av[q] = a0[min(tid + q * BS, n0)];
+    if (ROWS) {
+      const unsigned long long *ar = p.acc_rows + ACC_ROWS * p.gc[g].nbase;
+      unsigned long long rv[ACC_ROWS][NQ];
+#pragma unroll
+      for (int r = 0; r < ACC_ROWS; ++r)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) rv[r][q] = ar[acc_row_at(min(tid + q * BS, n0), r)];
+#pragma unroll
+      for (int r = 0; r < ACC_ROWS; ++r)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) av[q] += rv[r][q];
+    }
   }
   // the coming push's tile pool starts empty
   if (g == 0 && tid == 0) *p.steal = 0u;
@@ -917,23 +945,23 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
   // are cleared at the kernel's end
   {
     constexpr int NC = (int)(sizeof(GapConst) / 8), NS = (int)(sizeof(GapState) / 8);
-    constexpr int NW = (int)(sizeof(Staged) / 8);
+    constexpr int NW = NC + NS;
     static_assert(sizeof(Staged) == sizeof(GapConst) + sizeof(GapState) + 8 * (T_N + 2), "no padding");
     constexpr int WPT = (NW + BS - 1) / BS;
     unsigned long long v[WPT];
 #pragma unroll
     for (int q = 0; q < WPT; ++q) {
       const int w = tid + q * BS;
-      const unsigned long long *src =
-          w < NC ? (const unsigned long long *)&p.gc[g] + w
-          : w < NC + NS ? (const unsigned long long *)&p.gs[g] + (w - NC)
-          : w < NC + NS + T_N ? p.tally + (size_t)g * T_N + (w - NC - NS)
-                              : p.next_count + (size_t)g * 2 + min(w - NC - NS - T_N, 1);
+      const unsigned long long *src = w < NC ? (const unsigned long long *)&p.gc[g] + w
+                                             : (const unsigned long long *)&p.gs[g] + min(w - NC, NS - 1);
       v[q] = *src;
     }
+    const unsigned long long tl = tally_sum(p, g, tid & (T_N - 1)), nc = p.next_count[(size_t)g * 2 + (tid & 1)];
 #pragma unroll
     for (int q = 0; q < WPT; ++q)
       if (tid + q * BS < NW) ((unsigned long long *)&stg)[tid + q * BS] = v[q];
+    if (tid < T_N) s_tally[tid] = tl;
+    if (tid < 2) stg.next_count[tid] = nc;
   }
   // (the guess network's weights on their way before the first barrier)
   constexpr bool want_mlp = MLP;
@@ -1002,6 +1030,9 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
     const double r = node_rho(s0, dx, rdx, av[q], k, N, fp64);
     rho[k] = r;
     acc[k] = 0ull;
+    if (ROWS)
+#pragma unroll
+      for (int w = 0; w < ACC_ROWS; ++w) p.acc_rows[ACC_ROWS * sc.nbase + acc_row_at(k, w)] = 0ull;
     if (k < N)
       Sk[pad(k)] = (k == 0) ? dx * r / 2.0 : dx * r;
     else
@@ -1091,7 +1122,7 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
     for (int i = tid; i < (int)(sizeof(GapState) / 8); i += BS) b[i] = a[i];
     if (tid < 15) write_head(p, g, sc, ss, tid);
   }
-  if (tid < T_N) p.tally[(size_t)g * T_N + tid] = 0ull;
+  if (tid < TALLY_ROWS * TALLY_ROW) p.tally[(size_t)g * TALLY_ROWS * TALLY_ROW + tid] = 0ull;
 }
 
 
@@ -1187,16 +1218,16 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
   // the kernel's end
   {
     constexpr int NC = (int)(sizeof(GapConst) / 8), NS = (int)(sizeof(GapState) / 8);
-    constexpr int NW = (int)(sizeof(Staged) / 8);
+    constexpr int NW = NC + NS;
     static_assert(sizeof(Staged) == sizeof(GapConst) + sizeof(GapState) + 8 * (T_N + 2) && NW <= FBS,
                   "one staged word per thread");
-    const unsigned long long *src =
-        tid < NC ? (const unsigned long long *)&p.gc[g] + tid
-        : tid < NC + NS ? (const unsigned long long *)&p.gs[g] + (tid - NC)
-        : tid < NC + NS + T_N ? p.tally + (size_t)g * T_N + (tid - NC - NS)
-                              : p.next_count + (size_t)g * 2 + min(tid - NC - NS - T_N, 1);
+    const unsigned long long *src = tid < NC ? (const unsigned long long *)&p.gc[g] + tid
+                                             : (const unsigned long long *)&p.gs[g] + min(tid - NC, NS - 1);
     const unsigned long long v = *src;
+    const unsigned long long tl = tally_sum(p, g, tid & (T_N - 1)), nc = p.next_count[(size_t)g * 2 + (tid & 1)];
     if (tid < NW) ((unsigned long long *)&stg)[tid] = v;
+    if (tid < T_N) s_tally[tid] = tl;
+    if (tid < 2) stg.next_count[tid] = nc;
   }
   const bool want_mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
   MlpWeights<FBS> mw;
@@ -1299,7 +1330,7 @@ __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, d
     for (int i = tid; i < (int)(sizeof(GapState) / 8); i += FBS) b[i] = a[i];
     if (tid < 15) write_head(p, g, sc, ss, tid);
   }
-  if (tid < T_N) p.tally[(size_t)g * T_N + tid] = 0ull;
+  if (tid < TALLY_ROWS * TALLY_ROW) p.tally[(size_t)g * TALLY_ROWS * TALLY_ROW + tid] = 0ull;
 }
 
 // k_ftable: the half-grid field E_{k+1/2} = (sigma + S_k) / eps0, S_k = O_c +
@@ -1503,18 +1534,20 @@ __device__ void emit_list(const DevPtrs &p, int g, int sel, long long r0, int nr
     unsigned long long *gacc = p.acc + c.nbase;
     if (e0) {
       atomicAdd(&gacc[0], (unsigned long long)(ze * (long long)e0));
-      atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT], (unsigned long long)e0);
+      atomicAdd(&tally_row(p, g)[T_EMIT], (unsigned long long)e0);
     }
     if (e1) {
       atomicAdd(&gacc[c.N], (unsigned long long)(ze * (long long)e1));
-      atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT + 1], (unsigned long long)e1);
+      atomicAdd(&tally_row(p, g)[T_EMIT + 1], (unsigned long long)e1);
     }
     atomicAdd(&p.ev_done[g], (unsigned long long)nr);
   }
   __syncthreads();
 }
 
-constexpr int FLUSH_SHARE = 4;  // least slots per node and workgroup of a single gap (see k_push)
+// least slots per node and workgroup of a single gap, with one row of node sums and
+// with several (see k_push)
+constexpr int FLUSH_SHARE = 4, FLUSH_SHARE_ROWS = 2;
 constexpr int EVQ = 128;  // absorbed-ion events a push workgroup queues in LDS
 // (more go to the workgroup's overflow region of a global buffer; both are
 // emitted at the segment's flush, so a step's emission completes in its push)
@@ -1657,7 +1690,10 @@ __device__ __forceinline__ void push_ticket(const DevPtrs &p, PushShared<P, AC> 
 // addresses.
 template <class P, class AC>
 __device__ inline void flush_nodes(const DevPtrs &p, const PushHead &h, int s, PushShared<P, AC> &sh) {
-  unsigned long long *gacc = p.acc + h.nbase;
+  // (this workgroup's row, or the one row there is)
+  const bool rows = p.acc_rows != nullptr;
+  unsigned long long *gacc = rows ? p.acc_rows + ACC_ROWS * h.nbase + blockIdx.x % ACC_ROWS * 32 : p.acc + h.nbase;
+  const int mul = rows ? ACC_ROWS - 1 : 0;
   const long long Z = (long long)of_species(h.Z, s);
   const int nn = h.N + 1;
   const int lane = threadIdx.x & 63;
@@ -1673,7 +1709,7 @@ __device__ inline void flush_nodes(const DevPtrs &p, const PushHead &h, int s, P
       int j = q + rot;
       j = j >= nn ? j - nn : j;
       const unsigned long long v = q < nn ? (unsigned long long)sh.acc[j] : 0ull;
-      if (v != 0ull) atomicAdd(&gacc[j], (unsigned long long)(Z * (long long)v));
+      if (v != 0ull) atomicAdd(&gacc[j + (j & ~31) * mul], (unsigned long long)(Z * (long long)v));
     }
   }
 }
@@ -1681,10 +1717,12 @@ __device__ inline void flush_nodes(const DevPtrs &p, const PushHead &h, int s, P
 // an emitted electron carries its full weight on its wall node
 template <class P>
 __device__ inline void emitted_charge(const DevPtrs &p, const PushHead &h, unsigned int e0, unsigned int e1) {
-  unsigned long long *gacc = p.acc + h.nbase;
+  const bool rows = p.acc_rows != nullptr;
+  const int r = (int)(blockIdx.x % ACC_ROWS);
+  unsigned long long *gacc = rows ? p.acc_rows + ACC_ROWS * h.nbase : p.acc + h.nbase;
   const long long ze = (long long)h.Z[0] * Prec<P>::W;
-  if (e0) atomicAdd(&gacc[0], (unsigned long long)(ze * (long long)e0));
-  if (e1) atomicAdd(&gacc[h.N], (unsigned long long)(ze * (long long)e1));
+  if (e0) atomicAdd(&gacc[rows ? acc_row_at(0, r) : 0], (unsigned long long)(ze * (long long)e0));
+  if (e1) atomicAdd(&gacc[rows ? acc_row_at(h.N, r) : h.N], (unsigned long long)(ze * (long long)e1));
 }
 
 // A queued event's ion id, wall and Poisson count.
@@ -1726,7 +1764,7 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
     asm volatile("" : "+v"(t));
     if (t < T_N) {
       const unsigned int v = sh.tally[t];
-      if (v) atomicAdd(&p.tally[(size_t)g * T_N + t], (unsigned long long)v);
+      if (v) atomicAdd(&tally_row(p, g)[t], (unsigned long long)v);
     }
   }
   if (ne > 0) {
@@ -1752,8 +1790,8 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
           see_write<P>(p, c, h.level, g, sel, id, wall, nk, blk, incl - nk, base, n);
           if (lane == 0) {
             emitted_charge<P>(p, h, n[0], n[1]);
-            if (n[0]) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT], (unsigned long long)n[0]);
-            if (n[1]) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT + 1], (unsigned long long)n[1]);
+            if (n[0]) atomicAdd(&tally_row(p, g)[T_EMIT], (unsigned long long)n[0]);
+            if (n[1]) atomicAdd(&tally_row(p, g)[T_EMIT + 1], (unsigned long long)n[1]);
           }
         }
       }
@@ -1791,8 +1829,8 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
       }
       if (lane == 0) {
         emitted_charge<P>(p, h, e0, e1);
-        if (e0) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT], (unsigned long long)e0);
-        if (e1) atomicAdd(&p.tally[(size_t)g * T_N + T_EMIT + 1], (unsigned long long)e1);
+        if (e0) atomicAdd(&tally_row(p, g)[T_EMIT], (unsigned long long)e0);
+        if (e1) atomicAdd(&tally_row(p, g)[T_EMIT + 1], (unsigned long long)e1);
       }
     }
   } else {
@@ -2292,10 +2330,12 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
     // and, of one gap, no more than leave each FLUSH_SHARE slots per node, down to
     // min_wgs (one per CU; all, when the caller set the grid): every one adds its
     // node sums to the gap's row.  2.3e6 particles on 4096 cells: 256 workgroups
-    // take 22 us, the 768 that fit the chip 37, with 3e6 additions in the flush
+    // take 22 us, the 768 that fit the chip 37, with 3e6 additions in the flush.
+    // (FLUSH_SHARE_ROWS with rows: 1e6 on 512 cells, 28.6 us a step, 28.8 with 4 and
+    // 30.1 with 8)
     const PushHead h0 = load_head(p, 0);
     const unsigned int slots = (unsigned int)h0.count[0] + (unsigned int)h0.count[1];
-    const unsigned int most = slots / (unsigned int)(FLUSH_SHARE * (h0.N + 1));
+    const unsigned int most = slots / (unsigned int)((p.acc_rows ? FLUSH_SHARE_ROWS : FLUSH_SHARE) * (h0.N + 1));
     nwg = min(nwg, (int)max(most, (unsigned int)min_wgs));
   }
   nwg = __builtin_amdgcn_readfirstlane(nwg);
@@ -3317,7 +3357,7 @@ size_t push_lds_bytes(int nmax, int fp64, int G, int wide) {
   return off;
 }
 
-template <int BS, int NQ, bool MLP>
+template <int BS, int NQ, bool MLP, bool ROWS>
 static hipError_t field1_m(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit, int fp64, int nmax,
                            hipStream_t s, KTime t) {
   // S_k of every cell, padded by one double per chunk of the prefix sums
@@ -3325,20 +3365,28 @@ static hipError_t field1_m(const DevPtrs &p, int G, int mode, int guess, double 
   const size_t lds = ((size_t)nmax + (size_t)BS + 1) * 8;
   static size_t attr_set = 32768;
   if (lds > attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_field1<BS, NQ, MLP>,
+    hipError_t e = hipFuncSetAttribute((const void *)k_field1<BS, NQ, MLP, ROWS>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_set = lds;
   }
-  return launch_k(k_field1<BS, NQ, MLP>, dim3(G), dim3(BS), lds, s, t.a, t.b, p, mode, guess, tol, maxit, fp64);
+  return launch_k(k_field1<BS, NQ, MLP, ROWS>, dim3(G), dim3(BS), lds, s, t.a, t.b, p, mode, guess, tol, maxit, fp64);
+}
+
+template <int BS, int NQ, bool ROWS>
+static hipError_t field1_r(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit, int fp64, int nmax,
+                           hipStream_t s, KTime t) {
+  const bool mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
+  return mlp ? field1_m<BS, NQ, true, ROWS>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t)
+             : field1_m<BS, NQ, false, ROWS>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
 }
 
 template <int BS, int NQ>
 static hipError_t field1_t(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit, int fp64, int nmax,
                            hipStream_t s, KTime t) {
-  const bool mlp = mode == 0 && guess == GS_GUESS_MLP && p.mlp_w != nullptr;
-  return mlp ? field1_m<BS, NQ, true>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t)
-             : field1_m<BS, NQ, false>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  if constexpr (BS * NQ <= ACC_ROWS_NMAX + 1)
+    if (p.acc_rows) return field1_r<BS, NQ, true>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
+  return field1_r<BS, NQ, false>(p, G, mode, guess, tol, maxit, fp64, nmax, s, t);
 }
 
 hipError_t launch_field(const DevPtrs &p, int G, int mode, int guess, double tol, int maxit,
