@@ -2255,6 +2255,28 @@ __device__ __forceinline__ void push_tail_emit(PushShared<P, AC> &sh, int G, int
   if (threadIdx.x == 0) *p.list_seen = seen;
 }
 
+// Of nwg workgroups that take one gap's te electron and ti ion tiles round robin, how
+// many take the electrons alone, or 0 when all take both.  Workgroups of their own
+// flush nwg segments where shared ones flush twice as many (at 4096 cells and 256
+// workgroups a flush of all is 7-8 us of additions, in which little is loaded: 2.3e7
+// particles take 79 us shared and 71 split, 2e8 on 16384 cells 710 and 683).  What it
+// can cost is a tile more for some: taken when none has more, or a tile is little of
+// what each has.
+__device__ inline int rr_electrons(int te, int ti, int nwg) {
+  const int m = (te + ti + nwg - 1) / nwg;  // tiles of the busiest when shared
+  if (te == 0 || ti == 0 || m < 2) return 0;
+  int best = 0, most = m < 8 ? m : m + 1;
+  for (int ne = (te + m - 1) / m, i = 0; i < 2; ++i, --ne)
+    if (ne > 0 && ne < nwg) {
+      const int c = max((te + ne - 1) / ne, (ti + nwg - ne - 1) / (nwg - ne));
+      if (c <= most) {
+        best = ne;
+        most = c - 1;
+      }
+    }
+  return best;
+}
+
 template <class P, class AC, int BS, int PPT, bool NT>
 __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int nmax, int steal, int rr,
                                                  int min_wgs, int masks, int lists) {
@@ -2349,8 +2371,16 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   // strided piece, and t visits the workgroup's first tile of each region it has
   // tiles in (that tile's local index is below nwg).
   const int R = !rr && steal > 0 ? (total / nwg) / steal : 0;
-  int t = rr ? (int)blockIdx.x : (int)share_of((unsigned int)total, blockIdx.x, (unsigned int)nwg);
-  int t1 = rr ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
+  // Round robin over one gap gives each region workgroups of its own, in proportion to
+  // its tiles (see rr_electrons): a workgroup with tiles of both stages and flushes
+  // two segments.
+  const int ne = G == 1 && rr ? rr_electrons(te1, ti1, nwg) : 0;
+  const bool own = ne > 0, ions = own && (int)blockIdx.x >= ne;
+  const int stride = !rr ? 1 : ions ? nwg - ne : own ? ne : nwg;  // (of a workgroup's tiles)
+  int t = ions ? te1 + (int)blockIdx.x - ne
+          : rr ? (int)blockIdx.x
+               : (int)share_of((unsigned int)total, blockIdx.x, (unsigned int)nwg);
+  int t1 = own && !ions ? te1 : rr ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
   // pool tile q is tile k = q / nwg of run w = q % nwg's reserved end: the first
   // reserved tile of every run goes out first
   // (the next index is taken while a tile is pushed: the counter is one address
@@ -2406,7 +2436,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
       ls = t - T0;
       if (rr) {
         le = T1 - T0;
-        t += ((T1 - t + nwg - 1) / nwg) * nwg;  // the first of its tiles past the region
+        t += ((T1 - t + stride - 1) / stride) * stride;  // the first of its tiles past the region
       } else {
         le = min(t1, T1) - T0;
         t = T0 + le;
@@ -2414,7 +2444,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
     }
     if (og >= 0 && !(more && g == og && s == os)) close_seg<P, AC>(sh, sel, og, os, lists != 0 && !more);
     if (!more) break;
-    push_piece<P, AC, BS, PPT, NT>(sh, tile, sel, g, s, ls, le, rr ? nwg : 1, ti, og, os);
+    push_piece<P, AC, BS, PPT, NT>(sh, tile, sel, g, s, ls, le, stride, ti, og, os);
     og = g;
     os = s;
   }

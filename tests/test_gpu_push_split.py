@@ -61,3 +61,19 @@ def test_split_of_small_work(cells, n, beam, opts):
     sim, orc, recs = run_pair(cfg, loads, oracle.STRICT, 3, True, (n + 20_000, n + 20_000),
                               {getattr(gs, k): v for k, v in opts.items()})
     _check(sim, orc, recs)
+
+
+@pytest.mark.parametrize("ne,ni,grid", [
+    (30_000, 30_000, 2), (2100, 150_000, 5), (150_000, 2100, 5), (70_000, 80_001, 7), (5, 200_000, 256),
+    (200_000, 5, 11), (2048 * 9, 2048 * 7, 4),
+])
+def test_round_robin_split(ne, ni, grid):
+    # round-robin workgroups of their own for electrons and ions, and shared ones where
+    # that would give some a tile too many
+    from paper_2603_24010_amd import gapsim as gs
+    cfg = W.config2(n_cells=90, beam_per_step=301, weight=1e3)
+    rng = np.random.default_rng(ne + ni)
+    loads = {0: (rng.uniform(0, cfg.d, ne), rng.normal(0, 4e6, ne)), 1: (rng.uniform(0, cfg.d, ni), rng.uniform(4e5, 3e6, ni))}
+    sim, orc, recs = run_pair(cfg, loads, oracle.WEAK, 3, True, (ne + 60_000, ni + 20_000),
+                              {gs.OPT_STREAM: 1, gs.OPT_GRID: grid})
+    _check(sim, orc, recs)
