@@ -23,8 +23,8 @@ namespace gs {
 // k_train_update sums one 16 x 16 block of a weight gradient over the batch per
 // workgroup and applies Adam to it.  What bounds a step at the usual batches is
 // latency: 14.6 GFLOP in 64 steps of batch 1024 is 1.5 us of matrix work a step.
-// At batch 1024 (64 row tiles, 160 blocks) the two kernels take 19.7 and 8.3 us
-// and a step 30.4 us, launches included; one kernel per GEMM, column sum and
+// At batch 1024 (64 row tiles, 160 blocks) the two kernels take 17.5 and 8.3 us
+// (19.7 with the library's erff and expf) and a step 26.7 us, launches included; one kernel per GEMM, column sum and
 // reduction (22 launches) took 157 us.
 //
 // All products run on the matrix cores in binary32 (v_mfma_f32_16x16x4_f32:
@@ -36,10 +36,34 @@ namespace gs {
 // ---------------------------------------------------------------------------
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// Phi(z), the normal distribution function, in some twenty instructions without a
+// branch (the library's erff has two, and a wave takes both): Phi(-t) = 2^-(1 + t
+// P(t)) for t >= 0, where t P(t) = -log2 erfc(t / sqrt 2) is nearly a parabola.  P is
+// the minimax polynomial of degree 9 on [0, 5.5] for the absolute error of Phi
+// (1.6e-9), constant past it (Phi(-5.5) = 1.9e-8).  GELU with it, against 64 bits in
+// the 2-norm, for normal z of scale 0.05, 0.5, 1 and 3: 4.3, 3.8, 3.3 and 2.6e-8, and
+// 3.7, 4.0, 3.7 and 2.9e-8 with a correctly rounded erff.
+__device__ inline float normal_cdf(float z) {
+  const float t = fabsf(z), u = fminf(t, 5.5f);
+  float h = 3.639413037603845e-08f;
+  h = __builtin_fmaf(h, u, -1.0236597063340014e-06f);
+  h = __builtin_fmaf(h, u, 1.2430210517777596e-05f);
+  h = __builtin_fmaf(h, u, -8.325302042067051e-05f);
+  h = __builtin_fmaf(h, u, 0.0002973641094285995f);
+  h = __builtin_fmaf(h, u, -2.5722472855704837e-05f);
+  h = __builtin_fmaf(h, u, -0.006927415728569031f);
+  h = __builtin_fmaf(h, u, 0.052434973418712616f);
+  h = __builtin_fmaf(h, u, 0.45922109484672546f);
+  h = __builtin_fmaf(h, u, 1.1511043310165405f);
+  const float a = 0.5f * __builtin_amdgcn_exp2f(-t * h);
+  return z >= 0.0f ? 1.0f - a : a;
+}
+
 __device__ inline float gelu_both(float z, float *grad) {
-  const float Phi = 0.5f * (1.0f + erff(z * 0.70710678118654752f));
-  *grad = Phi + z * (0.39894228040143268f * expf(-0.5f * z * z));
-  return gelu_f32(z);
+  const float Phi = normal_cdf(z);
+  // (2^x: -z^2 / (2 ln 2))
+  *grad = Phi + z * (0.39894228040143268f * __builtin_amdgcn_exp2f(-0.72134752044448170f * z * z));
+  return z * Phi;
 }
 
 // four consecutive floats from 4-byte aligned memory (the caller's arrays)
@@ -342,8 +366,10 @@ __global__ __launch_bounds__(UPT) void k_train_update(TrainRows o, int B, int nt
 // bfloat16 terms, 8 significant bits each (hi + mid + lo), and the three
 // products, each exact, are summed in binary32 by v_mfma_f32_16x16x32_bf16, the
 // smallest first.  Errors against 64 bits (2-norm, 32 to 1e6 rows): 4.1e-8, the
-// row kernel's 5.1e-8.  92000 rows take 55 us (436 us by rows), 1e6 rows 0.46 ms
-// (4.5 ms); most of it is GELU's error function on the vector units.
+// row kernel's 5.1e-8.  92000 rows take 45 us (423 us by rows), 1e6 rows 0.42 ms
+// (4.5 ms): the activations' reads from LDS, GELU with the splits, and the barriers
+// between the layers share that.  (Waves of 32 outputs, which read half as much, took
+// 6% off 92000 rows and added 5% at 2048.)
 // Lane l gives A(l % 16, 8 (l / 16) + i) and B(8 (l / 16) + i, l % 16), i =
 // 0..7, and holds D(4 (l / 16) + r, l % 16): A rows are outputs, B columns batch
 // rows, so that a lane ends up with four consecutive outputs of one row.
@@ -359,27 +385,34 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const uint16_t *W, const fl
 }
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-// The row kernel up to here: 8.2 us at 512 rows against the tiles' 8.9, 8.9 and
-// 8.9 at 1024, 13.5 against 9.0 at 2048 (launches included)
-constexpr long long FORWARD_ROWS_MAX = 1024;
+// The row kernel up to here: 5.5 us at 512 rows against the tiles' 7.5, 6.9 and 7.6 at
+// 768, 7.9 and 7.6 at 896, 13.5 and 7.6 at 2048 (launches included)
+constexpr long long FORWARD_ROWS_MAX = 768;
 constexpr int FTW = 8, FTT = FTW * 64;  // waves (one 16-output block each) and threads
 constexpr int FTR = 32;                 // rows per tile: two blocks of 16
 constexpr int FTLD = MLP_H + 8;         // row stride of an activation plane in LDS (bfloat16)
 constexpr int FTP = FTR * FTLD;         // one plane; three per buffer, two buffers
 static_assert(FTW * 16 == MLP_H, "a wave per output block");
 
-// x = hi + mid + lo exactly (bits of each); infinities and NaN stay in hi
-__device__ inline void split3(float x, uint32_t *hi, uint32_t *mid, uint32_t *lo) {
-  const uint32_t b = __float_as_uint(x);
-  const bool fin = (b & 0x7F800000u) != 0x7F800000u;
-  const uint32_t h = x != x ? 0x7FC00000u : b & 0xFFFF0000u;
-  const float r1 = fin ? x - __uint_as_float(h) : 0.0f;
-  const uint32_t m = __float_as_uint(r1) & 0xFFFF0000u;
-  const float r2 = r1 - __uint_as_float(m);
-  *hi = h >> 16;
-  *mid = m >> 16;
-  *lo = __float_as_uint(r2) >> 16;
+// Two values as three pairs of bfloat16, x = hi + mid + lo exactly (truncation leaves
+// 8 of 24 significant bits to each); infinities and NaN stay in hi, a NaN by its quiet
+// bit (results of arithmetic have it set; see quiet for others).
+__device__ inline void split3(float x0, float x1, uint32_t *hi, uint32_t *mid, uint32_t *lo) {
+  const float x[2] = {x0, x1};
+  float r1[2], r2[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const float d = x[i] - __uint_as_float(__float_as_uint(x[i]) & 0xFFFF0000u);
+    r1[i] = d == d ? d : 0.0f;
+    r2[i] = r1[i] - __uint_as_float(__float_as_uint(r1[i]) & 0xFFFF0000u);
+  }
+  // the upper halves of both
+  *hi = __builtin_amdgcn_perm(__float_as_uint(x[1]), __float_as_uint(x[0]), 0x07060302u);
+  *mid = __builtin_amdgcn_perm(__float_as_uint(r1[1]), __float_as_uint(r1[0]), 0x07060302u);
+  *lo = __builtin_amdgcn_perm(__float_as_uint(r2[1]), __float_as_uint(r2[0]), 0x07060302u);
 }
+
+__device__ inline float quiet(float x) { return x != x ? __uint_as_float(0x7FC00000u) : x; }
 
 __device__ inline v8bf ld8(const uint16_t *a) {
   v8bf v;
@@ -443,20 +476,13 @@ __global__ __launch_bounds__(FTT, 4) void k_mlp_tiles(const uint16_t *W, const f
     const long long row = min(t * FTR + r, n - 1);
     const v4f a = ld4(x + row * MLP_IN + (f < MLP_IN ? f : 0));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = f < MLP_IN ? a[i] : 0.0f;
+    for (int i = 0; i < 4; ++i) v[i] = f < MLP_IN ? quiet(a[i]) : 0.0f;
   };
   // four consecutive values of row r, from column k, to a buffer's planes
   auto put = [&](uint16_t *dst, int r, int k, const float *v) {
-    uint32_t h[4], m[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) split3(v[i], &h[i], &m[i], &l[i]);
     uint32_t *d = (uint32_t *)(dst + r * FTLD + k);
-    d[0] = h[0] | h[1] << 16;
-    d[1] = h[2] | h[3] << 16;
-    d[FTP / 2] = m[0] | m[1] << 16;
-    d[FTP / 2 + 1] = m[2] | m[3] << 16;
-    d[FTP] = l[0] | l[1] << 16;
-    d[FTP + 1] = l[2] | l[3] << 16;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) split3(v[2 * i], v[2 * i + 1], &d[i], &d[FTP / 2 + i], &d[FTP + i]);
   };
   v4f acc[2];
   auto hidden = [&](uint16_t *dst, const float *bias) {
@@ -464,7 +490,10 @@ __global__ __launch_bounds__(FTT, 4) void k_mlp_tiles(const uint16_t *W, const f
     for (int m = 0; m < 2; ++m) {
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = gelu_f32(acc[m][r] + bias[r]);
+      for (int r = 0; r < 4; ++r) {
+        const float z = acc[m][r] + bias[r];
+        v[r] = z * normal_cdf(z);
+      }
       put(dst, 16 * m + c, o0 + 4 * q, v);
     }
     lds_barrier();

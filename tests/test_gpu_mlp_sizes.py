@@ -61,7 +61,7 @@ def test_bad_sample_indices_are_reported():
             gs.mlp_train(x, t, order, 20, th, torch.zeros_like(th), torch.zeros_like(th))
 
 
-@pytest.mark.parametrize("n", [1, 31, 33, 1024, 1025, 1055, 1057, 16385, 50_001])
+@pytest.mark.parametrize("n", [1, 31, 33, 768, 769, 1024, 1025, 1055, 1057, 16385, 50_001])
 def test_forward_at_tile_edges(n):
     from paper_2603_24010_amd import gapsim as gs
     from paper_2603_24010_amd import workloads as W
