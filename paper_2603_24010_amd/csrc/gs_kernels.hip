@@ -54,6 +54,25 @@ __device__ inline double unit_open(uint64_t r) {
   return ((double)(r >> 11) + 0.5) * (1.0 / 9007199254740992.0);
 }
 
+// The region r of n that holds position t: the first from r on whose end pre[r + 1]
+// lies past t.  It is mostly this one or the next; the first of a workgroup may be any,
+// and is found by halving (one by one, the regions of 512 gaps took the last workgroups
+// 40 us).
+template <class T>
+__device__ inline int region_of(const T *pre, int r, int n, T t) {
+  if (pre[r + 1] > t) return r;
+  if (pre[++r + 1] > t) return r;
+  int hi = n - 1;
+  for (++r; r < hi;) {
+    const int mid = (r + hi) >> 1;
+    if (pre[mid + 1] > t)
+      hi = mid;
+    else
+      r = mid + 1;
+  }
+  return r;
+}
+
 // random streams: SEE of an ion (step, id, 1, block); beam particle k (step, k, 2, 0)
 __device__ inline void rng_block(uint64_t seed, uint64_t a, uint64_t b, uint64_t c, uint64_t d,
                                  uint64_t out[4]) {
@@ -2446,21 +2465,10 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
     const bool more = t < t1;
     int s = 0, ls = 0, le = 0, te = te1, ti = ti1;
     if (more) {
-      if (G > 1 && pool) {
-        // the gap holding tile t (binary search over the tile prefix)
-        int lo = 0, hi = G - 1;
-        while (lo < hi) {
-          const int mid = (lo + hi + 1) >> 1;
-          if (prefix(mid) <= t)
-            lo = mid;
-          else
-            hi = mid - 1;
-        }
-        g = lo;
+      if (G > 1) {
+        g = __builtin_amdgcn_readfirstlane(region_of(sh.prefix, g, G, t));
+        gap_tiles(load_head(push_args(), g), tile, te, ti);
       }
-      while (prefix(g + 1) <= t) ++g;
-      g = __builtin_amdgcn_readfirstlane(g);
-      if (G > 1) gap_tiles(load_head(push_args(), g), tile, te, ti);
       const int tg = prefix(g);
       s = t - tg < te ? 0 : 1;
       const int T0 = s ? tg + te : tg, T1 = s ? tg + te + ti : tg + te;  // the region's tiles
@@ -2668,7 +2676,7 @@ __global__ __launch_bounds__(BS) void k_sort_count(DevPtrs p, int G, int tile, i
   constexpr int VN = Vec<P>::n;
   int r = 0;
   for (int t = t0; t < t1;) {
-    while (prefix[r + 1] <= t) ++r;
+    r = region_of(prefix, r, 2 * G, t);
     const int tend = min(t1, prefix[r + 1]);
     const int g = r >> 1, s = r & 1;
     const GapConst &c = p.gc[g];
@@ -2748,7 +2756,7 @@ __global__ __launch_bounds__(BS) void k_sort_scatter(DevPtrs p, int G, int tile,
   constexpr int VN = Vec<P>::n;
   int r = 0;
   for (int t = t0; t < t1;) {
-    while (prefix[r + 1] <= t) ++r;
+    r = region_of(prefix, r, 2 * G, t);
     const int tend = min(t1, prefix[r + 1]);
     const int g = r >> 1, s = r & 1;
     const GapConst &c = p.gc[g];
@@ -2924,7 +2932,7 @@ __global__ __launch_bounds__(FW) void k_fill_count(DevPtrs p, int G, int masks) 
   constexpr int NV = 64 / VN;  // vectors per word
   int r = 0;
   for (int t = t0; t < t1; ++t) {
-    while (prefix[r + 1] <= t) ++r;
+    r = region_of(prefix, r, 2 * G, t);
     const int s = r & 1, k = t - prefix[r];
     const GapConst &c = p.gc[r >> 1];
     const long long n = min((long long)p.next_count[r], c.cap[s]);
@@ -2998,7 +3006,7 @@ __global__ __launch_bounds__(FW) void k_fill_holes(DevPtrs p, int G) {
   FILL_TILE_RUN
   int r = 0;
   for (int t = t0; t < t1; ++t) {
-    while (prefix[r + 1] <= t) ++r;
+    r = region_of(prefix, r, 2 * G, t);
     const int s = r & 1, k = t - prefix[r];
     const GapConst &c = p.gc[r >> 1];
     const long long n = min((long long)p.next_count[r], c.cap[s]);
@@ -3049,7 +3057,7 @@ __global__ __launch_bounds__(FW) void k_fill_rank(DevPtrs p, int G) {
   (void)sel;
   int r = 0;
   for (int t = t0; t < t1; ++t) {
-    while (prefix[r + 1] <= t) ++r;
+    r = region_of(prefix, r, 2 * G, t);
     const int s = r & 1, k = t - prefix[r];
     const GapConst &c = p.gc[r >> 1];
     const long long n = min((long long)p.next_count[r], c.cap[s]);
@@ -3116,7 +3124,7 @@ __global__ __launch_bounds__(FW) void k_fill_move(DevPtrs p, int G) {
   const long long total = tpre[R];
   int r = 0;
   for (long long f = (long long)blockIdx.x * FW + tid; f < total; f += (long long)gridDim.x * FW) {
-    while (tpre[r + 1] <= f) ++r;
+    r = region_of(tpre, r, R, f);
     const int s = r & 1;
     const GapConst &c = p.gc[r >> 1];
     const long long L = (long long)p.cursor[r];

@@ -77,3 +77,38 @@ def test_round_robin_split(ne, ni, grid):
     sim, orc, recs = run_pair(cfg, loads, oracle.WEAK, 3, True, (ne + 60_000, ni + 20_000),
                               {gs.OPT_STREAM: 1, gs.OPT_GRID: grid})
     _check(sim, orc, recs)
+
+
+@pytest.mark.parametrize("opts", [{}, {"OPT_STEAL": 3, "OPT_GRID": 20}, {"OPT_STREAM": 1}, {"OPT_SORT_BIN": 16}])
+def test_many_gaps_with_empty_ones_as_each_alone(opts):
+    # the lookup of a tile's region among those of many gaps, runs of empty ones between
+    # them, through two compactions: bit for bit what each gap does by itself
+    from paper_2603_24010_amd import gapsim as gs
+    rng = np.random.default_rng(5)
+    cfgs, loads, caps = [], [], []
+    for g in range(90):
+        ne, ni = (0, 0) if g % 7 in (2, 3, 4) else (int(rng.integers(0, 5000)), int(rng.integers(0, 9000)))
+        cfg = W.config2(n_cells=20 + g, beam_per_step=g % 3, weight=1e3, seed=g)
+        cfgs.append(cfg)
+        loads.append([(rng.uniform(0, cfg.d, n), rng.normal(0, 3e6, n)) for n in (ne, ni)])
+        caps.append((ne + 9000, ni + 500))
+
+    def run(which):
+        sim = gs.GapSim([cfgs[g] for g in which], particle_fp=32, capacity=[caps[g] for g in which])
+        for k, v in opts.items():
+            sim.set_option(getattr(gs, k), v)
+        for i, g in enumerate(which):
+            for s in (0, 1):
+                if loads[g][s][0].size:
+                    sim.inject(i, s, *loads[g][s])
+        sim.step_weak(70)
+        out = []
+        for i in range(len(which)):
+            d = sim.diag(i)
+            out.append([np.asarray(d[k]) for k in ("phi0", "sigma", "n_live", "abs_cum", "emit_cum", "inj_cum", "pushed_cum")])
+        sim.close()
+        return out
+
+    for g, a in enumerate(run(range(90))):
+        for x, y in zip(a, run([g])[0]):
+            np.testing.assert_array_equal(x, y)
