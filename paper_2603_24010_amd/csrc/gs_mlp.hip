@@ -23,9 +23,10 @@ namespace gs {
 // k_train_update sums one 16 x 16 block of a weight gradient over the batch per
 // workgroup and applies Adam to it.  What bounds a step at the usual batches is
 // latency: 14.6 GFLOP in 64 steps of batch 1024 is 1.5 us of matrix work a step.
-// At batch 1024 (64 row tiles, 160 blocks) the two kernels take 17.5 and 8.3 us
-// (19.7 with the library's erff and expf) and a step 26.7 us, launches included; one kernel per GEMM, column sum and
-// reduction (22 launches) took 157 us.
+// At batch 1024 (64 row tiles, 160 blocks) the two kernels take 16.2 and 8.2 us
+// (19.7 with the library's erff and expf, and indices, rows and biases fetched one
+// after the other where they are used) and a step 25.5 us, launches included; one
+// kernel per GEMM, column sum and reduction (22 launches) took 157 us.
 //
 // All products run on the matrix cores in binary32 (v_mfma_f32_16x16x4_f32:
 // binary32 products and sums).  Lane l gives A(l % 16, l / 16) and B(l / 16, l
@@ -147,31 +148,51 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
   const int r0 = blockIdx.x * R;
   const float *W1 = th + MLP_OFF_W1, *W2 = th + MLP_OFF_W2, *W3 = th + MLP_OFF_W3, *W4 = th + MLP_OFF_W4;
   v4f w1[MLP_IN / 16], wa[MLP_H / 16], wb[MLP_H / 16];
+  // (the last update wrote the parameters from every XCD: each first read of them is a
+  // trip to memory, so the small ones go out now too, not where they are used)
+  __shared__ float sW4[MLP_OUT * MLP_H];
+  const float w4v = tid < MLP_OUT * MLP_H ? W4[tid] : 0.0f;
+  const float b1 = th[MLP_OFF_B1 + n0 + c], b2 = th[MLP_OFF_B2 + n0 + c], b3 = th[MLP_OFF_B3 + n0 + c];
+  float b4[MLP_OUT];
+#pragma unroll
+  for (int u = 0; u < MLP_OUT; ++u) b4[u] = th[MLP_OFF_B4 + u];
   load_fwd<MLP_IN>(W1, n0, w1);
   load_fwd<MLP_H>(W2, n0, wa);
   // the batch's rows (past its end the last one, whose derivative is zeroed);
   // an index outside [0, n) is replaced by 0 and counted
-  for (int e = tid; e < R * (MLP_IN + MLP_OUT); e += TRT) {
-    const int r = e / (MLP_IN + MLP_OUT), f = e % (MLP_IN + MLP_OUT);
-    const int b = min(r0 + r, B - 1);
-    long long i = order[off + b];
-    if (i < 0 || i >= n) {
-      if (f == 0 && r0 + r < B) atomicAdd(o.bad, 1u);
-      i = 0;
-    }
+  // (an index, then the row it names: each of the two trips is made once, for all of a
+  // thread's words together)
+  constexpr int RW = MLP_IN + MLP_OUT, NE = (R * RW + TRT - 1) / TRT;
+  long long idx[NE];
+  float val[NE];
+#pragma unroll
+  for (int u = 0; u < NE; ++u) idx[u] = order[off + min(r0 + min((tid + u * TRT) / RW, R - 1), B - 1)];
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int f = (tid + u * TRT) % RW;
+    const bool ok = idx[u] >= 0 && idx[u] < n;
+    const long long i = ok ? idx[u] : 0;
+    idx[u] = ok ? 0 : 1;  // (from here: whether it was out of range)
+    val[u] = *(f < MLP_IN ? x + i * MLP_IN + f : t + i * MLP_OUT + f - MLP_IN);
+  }
+#pragma unroll
+  for (int u = 0; u < NE; ++u) {
+    const int e = tid + u * TRT, r = e / RW, f = e % RW;
+    if (e >= R * RW) break;
+    if (idx[u] && f == 0 && r0 + r < B) atomicAdd(o.bad, 1u);
     if (f < MLP_IN) {
-      const float v = x[i * MLP_IN + f];
-      A0[r * TLD + f] = v;
-      if (r0 + r < B) o.x[(size_t)b * MLP_IN + f] = v;
+      A0[r * TLD + f] = val[u];
+      if (r0 + r < B) o.x[(size_t)(r0 + r) * MLP_IN + f] = val[u];
     } else {
-      st[r * MLP_OUT + f - MLP_IN] = t[i * MLP_OUT + f - MLP_IN];
+      st[r * MLP_OUT + f - MLP_IN] = val[u];
     }
   }
+  static_assert(MLP_OUT * MLP_H <= TRT, "a word per thread");
+  if (tid < MLP_OUT * MLP_H) sW4[tid] = w4v;
   lds_barrier();
   // a hidden layer's epilogue: bias, GELU to LDS and the workspace, GELU' to LDS
   v4f acc[MB];
-  auto hidden = [&](const float *bias, float *out, float *g, float *global) {
-    const float bj = bias[n0 + c];
+  auto hidden = [&](float bj, float *out, float *g, float *global) {
 #pragma unroll
     for (int m = 0; m < MB; ++m)
 #pragma unroll
@@ -186,15 +207,15 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
   };
   mul_block<MB, MLP_IN>(A0, w1, acc);
   load_fwd<MLP_H>(W3, n0, wb);
-  hidden(th + MLP_OFF_B1, A1, G1, o.a1);
+  hidden(b1, A1, G1, o.a1);
   lds_barrier();
   mul_block<MB, MLP_H>(A1, wa, acc);
   load_bwd(W3, n0, wa);
-  hidden(th + MLP_OFF_B2, A0, G2, o.a2);
+  hidden(b2, A0, G2, o.a2);
   lds_barrier();
   mul_block<MB, MLP_H>(A0, wb, acc);
   load_bwd(W2, n0, wb);
-  hidden(th + MLP_OFF_B3, A1, G3, o.a3);
+  hidden(b3, A1, G3, o.a3);
   lds_barrier();
   // the output layer: eight lanes per output, sixteen inputs each
   const float inv = 1.0f / (float)(B * MLP_OUT);
@@ -202,13 +223,13 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
     const int p = e & 7, r = (e >> 3) / MLP_OUT, u = (e >> 3) % MLP_OUT;
     float s = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) s += A1[r * TLD + 16 * p + k] * W4[u * MLP_H + 16 * p + k];
+    for (int k = 0; k < 16; ++k) s += A1[r * TLD + 16 * p + k] * sW4[u * MLP_H + 16 * p + k];
     s += __shfl_xor(s, 4, 64);
     s += __shfl_xor(s, 2, 64);
     s += __shfl_xor(s, 1, 64);
     if (p == 0) {
       const bool in = r0 + r < B;
-      const float d = in ? s + th[MLP_OFF_B4 + u] - st[r * MLP_OUT + u] : 0.0f;
+      const float d = in ? s + (u == 0 ? b4[0] : u == 1 ? b4[1] : b4[2]) - st[r * MLP_OUT + u] : 0.0f;
       se[r * MLP_OUT + u] = d * d;
       sdy[r * MLP_OUT + u] = 2.0f * d * inv;
       if (in) o.dy[(size_t)(r0 + r) * MLP_OUT + u] = 2.0f * d * inv;
@@ -227,7 +248,7 @@ __global__ __launch_bounds__(TRT, 2) void k_train_rows(const float *x, const flo
     const int r = e / MLP_H, k = e % MLP_H;
     float s = 0.0f;
 #pragma unroll
-    for (int u = 0; u < MLP_OUT; ++u) s += sdy[r * MLP_OUT + u] * W4[u * MLP_H + k];
+    for (int u = 0; u < MLP_OUT; ++u) s += sdy[r * MLP_OUT + u] * sW4[u * MLP_H + k];
     s *= G3[r * TLD + k];
     A0[r * TLD + k] = s;
     if (r0 + r < B) o.d3[(size_t)(r0 + r) * MLP_H + k] = s;
