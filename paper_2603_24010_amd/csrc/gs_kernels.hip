@@ -1,9 +1,10 @@
 // Device side of the circuit-coupled 1D ES-PIC step for gfx950.
 //
 // Per step two kernels run on the context's stream:
-//   k_field   one workgroup per gap: charge accumulator -> rho, prefix scans for
-//             the half-grid field, the circuit/surface-charge update (strict or
-//             weak), the binary32/64 field table the push gathers from.
+//   k_field1  (past 8192 cells k_fdens, k_field, k_ftable) one workgroup per gap:
+//             charge accumulator -> rho, prefix scans for the half-grid field,
+//             the circuit/surface-charge update (strict or weak), the binary32/64
+//             field table the push gathers from.
 //             With an external circuit engine (field mode 2) the engine's gap
 //             voltage comes from, and the potential goes to, pinned host memory.
 //   k_push    persistent workgroups over tiles of every gap's particles: gather,
@@ -11,7 +12,7 @@
 //             workgroup; at the start of each of its ion segments a workgroup
 //             injects its share of the beam, at the end it emits the secondary
 //             electrons of the ions it absorbed.
-// Every few steps k_compact reclaims the slots of absorbed particles.  On
+// Every few steps the k_fill kernels reclaim the slots of absorbed particles.  On
 // request k_dt_scan reads one gap's particles for the time-step check.
 //
 // Compiled with -ffp-contract=off: the binary32 particle arithmetic is a fixed
@@ -1219,8 +1220,8 @@ __global__ __launch_bounds__(FDB) void k_fdens(DevPtrs p, int fp64) {
 
 // k_field: one workgroup per gap.  The chunks' totals give S_k's offsets, the
 // potential P = (dx / eps0) sum_k S_k that the space charge alone gives the
-// electrode and the space charge; thread 0 solves the circuit and the surface
-// charge (solve_level); the offsets and sigma go to k_ftable.
+// electrode and the space charge; the circuit and the surface charge are solved as
+// in k_field1; the offsets and sigma go to k_ftable.
 __global__ __launch_bounds__(FBS) void k_field(DevPtrs p, int mode, int guess, double tol,
                                                int maxit, int fp64) {
   const int g = blockIdx.x, tid = threadIdx.x;
@@ -1870,10 +1871,18 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
         e1 += n[1];
         lds_barrier();
       }
+      // the workgroup's sums to the wall nodes and the tallies (added by each wave they
+      // queued on the nodes' addresses, 24 ns apiece: 49 us for 2048 waves)
       if (lane == 0) {
-        emitted_charge<P>(p, h, e0, e1);
-        if (e0) atomicAdd(&tally_row(p, g)[T_EMIT], (unsigned long long)e0);
-        if (e1) atomicAdd(&tally_row(p, g)[T_EMIT + 1], (unsigned long long)e1);
+        if (e0) atomicAdd(&sh.tally[T_EMIT], e0);
+        if (e1) atomicAdd(&sh.tally[T_EMIT + 1], e1);
+      }
+      lds_barrier();
+      if (threadIdx.x == 0) {
+        const unsigned int n0 = sh.tally[T_EMIT], n1 = sh.tally[T_EMIT + 1];
+        emitted_charge<P>(p, h, n0, n1);
+        if (n0) atomicAdd(&tally_row(p, g)[T_EMIT], (unsigned long long)n0);
+        if (n1) atomicAdd(&tally_row(p, g)[T_EMIT + 1], (unsigned long long)n1);
       }
     }
   } else {
@@ -2297,11 +2306,14 @@ __device__ __forceinline__ void push_tail_emit(PushShared<P, AC> &sh, int G, int
 // flush nwg segments where shared ones flush twice as many (at 4096 cells and 256
 // workgroups a flush of all is 7-8 us of additions, in which little is loaded: 2.3e7
 // particles take 79 us shared and 71 split, 2e8 on 16384 cells 710 and 683).  What it
-// can cost is a tile more for some: taken when none has more, or a tile is little of
-// what each has.
+// costs is balance.  An ion tile takes up to a quarter longer than an electron tile (its
+// absorbed ions are queued and emit), so the electrons' workgroups idle, in proportion to
+// their tiles: with 4.9e7 electrons to 1.1e8 ions on 16384 cells a step is 628 us split
+// and 613 shared, with 2.1e7 to 1.6e8 658 and 667; hence a quarter.  And some may have a
+// tile more: taken when none has, or a tile is little of what each has.
 __device__ inline int rr_electrons(int te, int ti, int nwg) {
   const int m = (te + ti + nwg - 1) / nwg;  // tiles of the busiest when shared
-  if (te == 0 || ti == 0 || m < 2) return 0;
+  if (te == 0 || 4ll * te > ti || m < 2) return 0;
   int best = 0, most = m < 8 ? m : m + 1;
   for (int ne = (te + m - 1) / m, i = 0; i < 2; ++i, --ne)
     if (ne > 0 && ne < nwg) {
@@ -2611,7 +2623,7 @@ __device__ inline int bin_of(P x, int bin, int nb) {
   return b < nb - 1 ? b : nb - 1;
 }
 
-// The tile partition of k_compact over the regions' current slot counts:
+// The tile partition of the compaction over the regions' current slot counts:
 // prefix[r] = first tile of region r (LDS, 2G + 1 entries).
 template <int BS>
 __device__ inline void region_tile_prefix(const DevPtrs &p, int G, int tile, int *prefix, int *scan_sh) {
