@@ -1960,6 +1960,8 @@ struct SegK {
   unsigned long long *gacc;
   const uint32_t *ids;        // the region's particle ids (overflowing events carry the id)
   unsigned long long *live;   // the region's live masks, one word per 64 slots
+  unsigned int lim;           // events the LDS queue and the workgroup's overflow region hold,
+  Event *ovf;                 //   the region counted from the queue's end
 };
 
 // Push one chunk of BS * PPT slots starting at slot r0 (relative to the region
@@ -2071,16 +2073,18 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
     if (__ballot(nh != 0) != 0ull) {
       const int lane = tid & 63;
       const int incl = wave_incl_scan(nh);
-      const unsigned int tot = (unsigned int)__shfl(incl, 63, 64);
+      const unsigned int tot = (unsigned int)__builtin_amdgcn_readlane(incl, 63);
       unsigned int q0 = 0;
       if (lane == 0) q0 = atomicAdd(sh.evq_n, tot);
-      q0 = (unsigned int)__shfl((int)q0, 0, 64);
-      const unsigned int lim = (unsigned int)EVQ + ((long long)blockIdx.x < p.ovf_wgs ? (unsigned int)p.ovq : 0u);
+      q0 = (unsigned int)__builtin_amdgcn_readfirstlane((int)q0);
+      const unsigned int lim = c.lim;
       const unsigned int over0 = q0 > lim ? q0 : lim;
       const unsigned int n_over = q0 + tot > lim ? q0 + tot - over0 : 0u;
       unsigned long long gb = 0;
-      if (n_over && lane == 0) gb = atomicAdd(&p.ev_count[g], (unsigned long long)n_over);
-      gb = __shfl(gb, 0, 64);
+      if (n_over) {
+        if (lane == 0) gb = atomicAdd(&p.ev_count[g], (unsigned long long)n_over);
+        gb = __shfl(gb, 0, 64);
+      }
       unsigned int q = q0 + (unsigned int)(incl - nh);
       unsigned int rest = hit & 0xFFFFu;
       while (rest) {
@@ -2097,7 +2101,7 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
         if (q < (unsigned int)EVQ) {
           sh.evq[q] = ev;
         } else if (q < lim) {
-          p.ovf[(size_t)blockIdx.x * (size_t)p.ovq + (q - EVQ)] = ev;
+          c.ovf[q - EVQ] = ev;
         } else {
           const unsigned long long e = gb + (unsigned long long)(q - over0);
           if (e < (unsigned long long)c.evcap) {
@@ -2154,6 +2158,14 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
   c.ids = of_species(p.ID, sel) + pb;
   c.masks = sh.masks;
   c.live = p.live + pb / 64;
+  // (opaque, or they are worked out again for every wave with an absorbed ion: where a
+  // third of the waves have one in each chunk, 16384 cells and 2.9e5 absorbed of 1.6e8,
+  // its path in scalars with these at hand takes 645 us a step, 655 before)
+  c.lim = (unsigned int)EVQ + ((long long)blockIdx.x < p.ovf_wgs ? (unsigned int)p.ovq : 0u);
+  unsigned long long ovf = (unsigned long long)(p.ovf + (size_t)blockIdx.x * (size_t)p.ovq);
+  asm volatile("" : "+s"(c.lim), "+s"(ovf));
+  c.ovf = (Event *)ovf;
+  as_global(c.ovf);
   P *X = (P *)of_species(p.X, sel) + pb;
   P *U = (P *)of_species(p.U, sel) + pb;
   const P alpha = (P)of_species(h.alpha, s);
