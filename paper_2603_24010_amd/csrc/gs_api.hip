@@ -510,7 +510,7 @@ static gs_status setup(gs_ctx *ctx) {
     d.ovq = std::min<int64_t>(OVQ_MAX, std::max<int64_t>(OVQ_MIN, (ion_slots / 32768 + 255) / 256 * 256));
   }
   ctx->emits = emits ? 1 : 0;
-  take(&d.ovf, (size_t)std::max<int64_t>(d.ovf_wgs, 1) * (size_t)d.ovq * sizeof(Event), nullptr, false);
+  take(&d.ovf, (size_t)std::max<int64_t>(d.ovf_wgs, 1) * (size_t)(EVQ + d.ovq) * sizeof(Event), nullptr, false);
   auto cut_size = [](size_t n) { return (n + 255) / 256 * 256; };
   size_t total = 0, nfrom = 0, nzero = 0;
   for (const Cut &c : cuts) {

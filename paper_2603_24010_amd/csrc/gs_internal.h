@@ -204,9 +204,9 @@ struct DevPtrs {
   ReadBack *rb;                    // (mapped) read-back buffer of the time-step check
   unsigned long long *dt_max;      // time-step check: largest |u| bits per species, then the
                                    // electrons per cell (zero between checks)
-  Event *ovf;                      // push workgroup b < ovf_wgs: events past its LDS queue,
-  int64_t ovf_wgs;                 //   ovq of them from ovf + b * ovq
-  int64_t ovq;
+  Event *ovf;                      // push workgroups' events past their LDS queues: room for ovq
+  int64_t ovf_wgs;                 //   events of each of ovf_wgs workgroups and for as many LDS
+  int64_t ovq;                     //   queues (k_push divides it)
   // Newton guess network: bfloat16 weights (flat layout of gs_mlp_dev.h) and
   // the normalisation block; null until weights are set
   const uint16_t *mlp_w;
@@ -229,6 +229,8 @@ constexpr int NCHMAX = 16384 / FCN + 1;
 // the sort kernels (16384 cells -> 4096 bins per species).
 constexpr int SORT_BIN_MIN = 4;
 
+// Absorbed-ion events a push workgroup queues in LDS.
+constexpr int EVQ = 128;
 // Absorbed-ion events a push workgroup keeps in its global overflow region
 // (past these they go to the gap's list, emitted by k_emit after the push):
 // from OVQ_MIN to OVQ_MAX, in proportion to the emitting gaps' ion slots.  A

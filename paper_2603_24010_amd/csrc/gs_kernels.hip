@@ -1592,9 +1592,9 @@ __device__ void emit_list(const DevPtrs &p, int g, int sel, long long r0, int nr
 // least slots per node and workgroup of a single gap, with one row of node sums and
 // with several (see k_push)
 constexpr int FLUSH_SHARE = 4, FLUSH_SHARE_ROWS = 2;
-constexpr int EVQ = 128;  // absorbed-ion events a push workgroup queues in LDS
-// (more go to the workgroup's overflow region of a global buffer; both are
-// emitted at the segment's flush, so a step's emission completes in its push)
+// (events past the EVQ that a push workgroup queues in LDS go to its overflow region
+// of a global buffer; both are emitted at the segment's flush, so a step's emission
+// completes in its push)
 
 template <class P, class AC>
 struct PushShared {
@@ -1608,6 +1608,7 @@ struct PushShared {
   unsigned int *piece;  // the flush's next piece of nodes
   unsigned int *ticket; // see push_ticket
   int nact;             // workgroups of the launch that take part
+  unsigned int ovf_i, ovf_room;  // this workgroup's overflow region: the ovf_i-th of ovf_room events
   unsigned int *listed; // the workgroup put absorbed ions in a gap's list (set
                         // when a segment is closed: its queue count passed the
                         // LDS queue and the overflow region)
@@ -1791,14 +1792,14 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
   __shared__ unsigned long long s_base;
   lds_barrier();
   const DevPtrs p = push_args();
-  const int ovq = (long long)blockIdx.x < p.ovf_wgs ? (int)p.ovq : 0;
+  const unsigned int lim = (unsigned int)EVQ + sh.ovf_room;
   const unsigned int queued = s == 1 ? *sh.evq_n : 0u;
-  const int ne = (int)min(queued, (unsigned int)(EVQ + ovq));
+  const int ne = (int)min(queued, lim);
   // (events past the LDS queue went through memory)
   if (queued > (unsigned int)EVQ) __syncthreads();
   const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, last_wave = (int)(blockDim.x >> 6) - 1;
   if (wv == last_wave) {
-    const bool listed = *sh.listed != 0u || queued > (unsigned int)(EVQ + ovq);
+    const bool listed = *sh.listed != 0u || queued > lim;
     if (lane == 0 && listed) *sh.listed = 1u;
     if (ticket) push_ticket<P, AC>(p, sh, listed);
     // the tallies but the emission's, one per lane; the empty asm keeps the
@@ -1817,7 +1818,7 @@ __device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P
     int ge = g;
     asm volatile("" : "+s"(ge));
     ConstGap &c = const_gap(p, ge);
-    const Event *ovf = p.ovf + (size_t)blockIdx.x * (size_t)p.ovq;
+    const Event *ovf = p.ovf + (size_t)sh.ovf_i * sh.ovf_room;
     if (ne <= 64) {
       if (wv == 0) {
         uint32_t id = 0;
@@ -2161,8 +2162,8 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
   // (opaque, or they are worked out again for every wave with an absorbed ion: where a
   // third of the waves have one in each chunk, 16384 cells and 2.9e5 absorbed of 1.6e8,
   // its path in scalars with these at hand takes 645 us a step, 655 before)
-  c.lim = (unsigned int)EVQ + ((long long)blockIdx.x < p.ovf_wgs ? (unsigned int)p.ovq : 0u);
-  unsigned long long ovf = (unsigned long long)(p.ovf + (size_t)blockIdx.x * (size_t)p.ovq);
+  c.lim = (unsigned int)EVQ + sh.ovf_room;
+  unsigned long long ovf = (unsigned long long)(p.ovf + (size_t)sh.ovf_i * sh.ovf_room);
   asm volatile("" : "+s"(c.lim), "+s"(ovf));
   c.ovf = (Event *)ovf;
   as_global(c.ovf);
@@ -2411,7 +2412,8 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   const int total = prefix(G);
   // the workgroups that take part: at most one per tile, the first ones (they
   // start first, and the others end at once)
-  int nwg = min((int)gridDim.x, max(total, 1));
+  const int most_wgs = min((int)gridDim.x, max(total, 1));
+  int nwg = most_wgs;
   if (G == 1 && !rr && steal == 0) {
     // and, of one gap, no more than leave each FLUSH_SHARE slots per node, down to
     // min_wgs (one per CU; all, when the caller set the grid): every one adds its
@@ -2449,6 +2451,18 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   int t = ions ? te1 + (int)blockIdx.x - ne
           : rr ? (int)blockIdx.x
                : (int)share_of((unsigned int)total, blockIdx.x, (unsigned int)nwg);
+  // The overflow regions of the workgroups that take ions: p.ovq events to each, and when
+  // fewer take them than there are tiles and blocks for, what the others would have held
+  // (LDS queue and region) in equal shares, so that a step may absorb as many ions however
+  // its work is split.  (p.ovf holds ovf_wgs (EVQ + ovq) events.)
+  {
+    const unsigned int W = (unsigned int)p.ovf_wgs, n0 = (unsigned int)most_wgs;
+    const unsigned int n = (unsigned int)(nwg - ne), regions = min(n, W);
+    unsigned int room = (unsigned int)p.ovq;
+    if (n < n0 && W > 0u) room = (min(n0, W) * room + min(n0 - n, W) * (unsigned int)EVQ) / regions;
+    sh.ovf_i = blockIdx.x - (ions ? (unsigned int)ne : 0u);
+    sh.ovf_room = sh.ovf_i < regions && (ions || !own) ? room : 0u;
+  }
   int t1 = own && !ions ? te1 : rr ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
   // pool tile q is tile k = q / nwg of run w = q % nwg's reserved end: the first
   // reserved tile of every run goes out first
