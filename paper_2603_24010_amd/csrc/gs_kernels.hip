@@ -86,11 +86,17 @@ __device__ inline void rng_block(uint64_t seed, uint64_t a, uint64_t b, uint64_t
 
 // a / b with r = 1 / b: two Newton corrections of a r give the correctly rounded
 // quotient (in the normal range) in five operations, a fifth of the general
-// division's
+// division's.  An infinite quotient they make NaN.
 __device__ inline double div_by(double a, double b, double r) {
   double q = a * r;
   q = __builtin_fma(__builtin_fma(-q, b, a), r, q);
   return __builtin_fma(__builtin_fma(-q, b, a), r, q);
+}
+
+// the same with an infinite quotient as it is
+__device__ inline double div_by_inf(double a, double b, double r) {
+  const double q = div_by(a, b, r), q0 = a * r;
+  return __builtin_fabs(q0) < __builtin_inf() ? q : q0;
 }
 
 // (not inlined: the constants of the exponential would otherwise be held in
@@ -489,7 +495,10 @@ __device__ inline void see_write(const DevPtrs &p, ConstGap &c, long long level,
         atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)g);
       } else {
         ((P *)of_species(p.X, sel) + c.pbase[0])[sl] = wl == 0 ? (P)0 : (P)c.N;
-        ((P *)of_species(p.U, sel) + c.pbase[0])[sl] = (P)div_by(v_si * c.dt, c.dx, c.rdx);
+        // (NaN: the energy or the speed overflowed, as a lognormal draw may)
+        const double u_si = div_by(v_si * c.dt, c.dx, c.rdx);
+        ((P *)of_species(p.U, sel) + c.pbase[0])[sl] =
+            u_si == u_si ? (P)u_si : (P)(wl == 0 ? __builtin_inf() : -__builtin_inf());
         (of_species(p.ID, sel) + c.pbase[0])[sl] = NO_ID;
         wrote = true;
       }
@@ -1137,7 +1146,7 @@ __global__ __launch_bounds__(BS) void k_field1(DevPtrs p, int mode, int guess, d
   // 3. half-grid field E_{k+1/2} = (sigma + S_k) / eps0 and the gather table
   const size_t eb = (size_t)sc.ebase;
   for (int k = circuit_wave ? N : tid; k < N; k += BS - 64) {
-    const double e = div_by(sigma + Sk[pad(k)], eps0, reps0);
+    const double e = div_by_inf(sigma + Sk[pad(k)], eps0, reps0);
     E[k] = e;
     if (fp64)
       ((double *)p.ehat)[eb + k + 1] = e;
@@ -1399,7 +1408,7 @@ __global__ __launch_bounds__(FDB) void k_ftable(DevPtrs p, int fp64) {
   for (int i = 0; i < 4; ++i) {
     const int k = kb + i;
     if (k >= N) break;
-    const double e = div_by(sigma + (off + L[i]), eps0, gc.reps0);
+    const double e = div_by_inf(sigma + (off + L[i]), eps0, gc.reps0);
     E[k] = e;
     if (fp64)
       ((double *)p.ehat)[eb + k + 1] = e;
