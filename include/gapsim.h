@@ -410,10 +410,12 @@ gs_status gs_read_particles(gs_ctx *ctx, int32_t gap, int32_t species, void *xi,
 gs_status gs_mlp_set_weights(gs_ctx *ctx, const float *theta, int64_t n, const double *norm);
 
 /* Evaluate the installed network (bfloat16 weights, binary32 activations and
- * sums; up to 768 rows by the device routine the strict step uses, more on the
- * matrix cores) on n normalised inputs: x [n][48] and y [n][3] in device
- * memory, caller-owned.  Asynchronous on the context's
- * stream.  Errors: GS_ESTATE (no weights), GS_EINVAL, GS_EDEVICE. */
+ * sums) on n normalised inputs: x [n][48] and y [n][3] in device memory,
+ * caller-owned.  Up to 768 rows, or with a weight that bfloat16 rounds to an
+ * infinity, by the device routine the strict step uses; else on the matrix
+ * cores, whose sums are in another order and whose GELU is another evaluation,
+ * so that a row's answer may differ in its last digits.  Asynchronous on the
+ * context's stream.  Errors: GS_ESTATE (no weights), GS_EINVAL, GS_EDEVICE. */
 gs_status gs_mlp_forward(gs_ctx *ctx, const float *x, int64_t n, float *y);
 
 /* Record training samples from the following strict steps: the field solve of

@@ -83,6 +83,7 @@ struct gs_ctx {
   // guess network
   uint16_t *mlp_w = nullptr;
   double *mlp_norm = nullptr;
+  bool mlp_finite = true;  // no weight was rounded to an infinity
 };
 
 // ---------------------------------------------------------------------------
@@ -1425,7 +1426,11 @@ extern "C" gs_status gs_mlp_set_weights(gs_ctx *ctx, const float *theta, int64_t
       return fail(ctx, GS_EINVAL, "norm[%d] must be finite (and positive for a scale)", i);
   }
   std::vector<uint16_t> wb((size_t)n);
-  for (int64_t i = 0; i < n; ++i) wb[(size_t)i] = to_bf16(theta[i]);
+  bool finite = true;
+  for (int64_t i = 0; i < n; ++i) {
+    wb[(size_t)i] = to_bf16(theta[i]);
+    finite = finite && (wb[(size_t)i] & 0x7F80u) != 0x7F80u;
+  }
   if (!ctx->mlp_w) {
     ctx->mlp_w = (uint16_t *)dev_alloc(ctx, sizeof(uint16_t) * MLP_NPARAM);
     ctx->mlp_norm = (double *)dev_alloc(ctx, sizeof(double) * MLP_NORM);
@@ -1437,6 +1442,7 @@ extern "C" gs_status gs_mlp_set_weights(gs_ctx *ctx, const float *theta, int64_t
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   ctx->dp.mlp_w = ctx->mlp_w;
   ctx->dp.mlp_norm = ctx->mlp_norm;
+  ctx->mlp_finite = finite;
   drop_graphs(ctx);
   return GS_OK;
 }
@@ -1446,7 +1452,7 @@ extern "C" gs_status gs_mlp_forward(gs_ctx *ctx, const float *x, int64_t n, floa
   if (!ctx->mlp_w) return fail(ctx, GS_ESTATE, "no guess network weights (gs_mlp_set_weights)");
   if (n < 0 || (n > 0 && (!x || !y))) return fail(ctx, GS_EINVAL, "bad x, y or n");
   if (n == 0) return GS_OK;
-  hipError_t e = launch_mlp_forward(ctx->mlp_w, x, n, y, std::max(ctx->ncu, 1), ctx->stream);
+  hipError_t e = launch_mlp_forward(ctx->mlp_w, ctx->mlp_finite, x, n, y, std::max(ctx->ncu, 1), ctx->stream);
   if (e != hipSuccess) return fail(ctx, GS_EDEVICE, "guess network launch: %s", hipGetErrorString(e));
   return GS_OK;
 }

@@ -296,8 +296,9 @@ hipError_t launch_phi(const DevPtrs &p, int gap, double *phi, hipStream_t s);
 // max-reduced as unsigned integers) and the most electrons in one cell of one gap,
 // to the read-back buffer
 hipError_t launch_dt_scan(const DevPtrs &p, int gap, int N, int fp64, int ncu, hipStream_t s);
-// guess network (gs_mlp.hip): y[n][3] = net(x[n][48]) with bfloat16 weights W
-hipError_t launch_mlp_forward(const uint16_t *W, const float *x, long long n, float *y, int ncu, hipStream_t s);
+// guess network (gs_mlp.hip): y[n][3] = net(x[n][48]) with bfloat16 weights W (finite: all of them are)
+hipError_t launch_mlp_forward(const uint16_t *W, bool finite, const float *x, long long n, float *y, int ncu,
+                              hipStream_t s);
 size_t push_lds_bytes(int nmax, int fp64, int G, int wide);
 size_t sort_lds_bytes(int G, int nmax, int bin);
 

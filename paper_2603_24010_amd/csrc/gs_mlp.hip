@@ -544,15 +544,24 @@ __global__ __launch_bounds__(FTT, 4) void k_mlp_tiles(const uint16_t *W, const f
   }
 }
 
-hipError_t launch_mlp_forward(const uint16_t *W, const float *x, long long n, float *y, int ncu, hipStream_t s) {
-  if (n > FORWARD_ROWS_MAX) {
+// finite: no weight is infinite in bfloat16.  (The tiles' lower terms are mostly zero,
+// and zero times an infinite weight is NaN where the whole activation's product is not.)
+hipError_t launch_mlp_forward(const uint16_t *W, bool finite, const float *x, long long n, float *y, int ncu,
+                              hipStream_t s) {
+  if (n > FORWARD_ROWS_MAX && finite) {
     const long long tiles = (n + FTR - 1) / FTR;
     const unsigned int grid = (unsigned int)(tiles < 2ll * ncu ? tiles : 2ll * ncu);
     hipLaunchKernelGGL(k_mlp_tiles, dim3(grid), dim3(FTT), 0, s, W, x, n, y);
-  } else {
-    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned int)n), dim3(256), 0, s, W, x, y);
+    return hipGetLastError();
   }
-  return hipGetLastError();
+  constexpr long long MOST = 1 << 23;  // rows a launch (2^31 threads)
+  for (long long b = 0; b < n; b += MOST) {
+    const long long nb = n - b < MOST ? n - b : MOST;
+    hipLaunchKernelGGL(k_mlp_forward, dim3((unsigned int)nb), dim3(256), 0, s, W, x + b * MLP_IN, y + b * MLP_OUT);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // the workspace of a batch of B rows; returns its floats (work may be null)

@@ -1,6 +1,7 @@
 """Infinities where a quantity overflows its type are what plain division gives.
 
-Bars: counts exact, both populations bit-equal to the oracle's as multisets.
+Bars: counts exact, both populations bit-equal to the oracle's as multisets; fields and
+the network's answers equal.
 """
 import numpy as np
 import pytest
@@ -52,4 +53,30 @@ def test_field_past_the_largest_number(cells, sign):
     assert cfg.d < 0.05 and np.isfinite(d["sigma"]) and np.abs(d["phi0"] - sign * 1e307) < 1e303
     np.testing.assert_array_equal(E, np.full(cells, sign * np.inf))
     assert d["e_ground"] == sign * np.inf
+    sim.close()
+
+
+@pytest.mark.parametrize("n", [769, 5000])
+def test_network_with_a_weight_that_rounds_to_infinity(n):
+    """A finite weight may round to an infinite bfloat16: many rows then answer as few do,
+    which the matrix cores' split activations cannot (zero times infinity)."""
+    import torch
+    from paper_2603_24010_amd import gapsim as gs
+    rng = np.random.default_rng(n)
+    theta = rng.normal(0.0, 0.12, oracle.MLP_NPARAM).astype(np.float32)
+    theta[oracle.MLP_NPARAM - 3 - 3 * 128 + 5] = 3.4e38  # of the first output
+    sim = gs.GapSim(W.config2(64), particle_fp=32, capacity=(64, 64))
+    norm = np.concatenate([np.zeros(48), np.ones(48), np.zeros(3), np.ones(3)])
+    sim.mlp_set_weights(theta, norm)
+    x = torch.from_numpy(rng.normal(0, 1.5, (n, 48)).astype(np.float32)).cuda()
+    y = sim.mlp_forward(x).cpu().numpy()
+    few = np.concatenate([sim.mlp_forward(x[b:b + 700]).cpu().numpy() for b in range(0, n, 700)])
+    np.testing.assert_array_equal(y, few)
+    assert np.isinf(y[:, 0]).all() and np.isfinite(y[:, 1:]).all()
+    # finite weights again: the matrix cores again, equal to binary32's rounding
+    theta[oracle.MLP_NPARAM - 3 - 3 * 128 + 5] = 0.1
+    sim.mlp_set_weights(theta, norm)
+    y = sim.mlp_forward(x).cpu().numpy()
+    yo = oracle.mlp_forward(oracle.round_bf16(theta).astype(np.float64), x.cpu().numpy().astype(np.float64))
+    assert np.abs(y - yo).max() <= 1e-5 * np.abs(yo).max()
     sim.close()
