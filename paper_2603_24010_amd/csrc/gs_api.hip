@@ -428,13 +428,9 @@ static gs_status setup(gs_ctx *ctx) {
   };
   std::vector<GapState> hs(G);
   for (int g = 0; g < G; ++g) init_state(ctx->params[g], ctx->hc[g], hs[g]);
-  std::vector<int64_t> sched(std::max<size_t>(nsched, 1), 0);
-  for (int g = 0; g < G; ++g)
-    std::copy(ctx->sched[g].begin(), ctx->sched[g].end(), sched.begin() + ctx->hc[g].sched_base);
   const unsigned int err0[2] = {0u, 0xFFFFFFFFu};
   take(&d.gc, sizeof(GapConst) * (size_t)G, ctx->hc.data(), false);
   take(&d.gs, sizeof(GapState) * (size_t)G, hs.data(), false);
-  take(&d.sched, sched.size() * 8, sched.data(), false);
   take(&d.err, 8, err0, false);
   take(&d.next_count, (size_t)G * 2 * 8, nullptr, true);
   take(&d.cursor, (size_t)G * 2 * 8, nullptr, true);
@@ -444,6 +440,7 @@ static gs_status setup(gs_ctx *ctx) {
   take(&d.steal, 256, nullptr, true);
   take(&d.push_done, 33 * 128, nullptr, true);
   take(&d.epoch, 8, nullptr, true);
+  if (nsched == 0) take(&d.sched, 8, nullptr, true);
   take(&d.dt_max, 16 + (size_t)ctx->nmax * 4, nullptr, true);
   take(&d.acc, nodes * 8, nullptr, true);
   int64_t most_slots = 0;
@@ -456,6 +453,7 @@ static gs_status setup(gs_ctx *ctx) {
   take(&d.E64, nodes * 8, nullptr, true);
   take(&d.hist, bins * 8, nullptr, true);
   take(&d.bcur, bins * 8, nullptr, true);
+  if (nsched > 0) take(&d.sched, nsched * 8, nullptr, false);  // (from the context's copies)
   take(&d.head, sizeof(PushHead) * (size_t)G, nullptr, false);
   take(&d.fill_h, (size_t)G * 2 * 8, nullptr, false);
   // in-place compaction: a live bit per slot, and per-tile counters (a region
@@ -544,6 +542,10 @@ static gs_status setup(gs_ctx *ctx) {
   hipStream_t s = ctx->stream;
   HIPCHK(ctx, hipMemcpyAsync(base, image.data(), nfrom, hipMemcpyHostToDevice, s));
   HIPCHK(ctx, hipMemsetAsync(base + nfrom, 0, nzero, s));
+  for (int g = 0; g < G; ++g)
+    if (!ctx->sched[g].empty())
+      HIPCHK(ctx, hipMemcpyAsync((int64_t *)d.sched + ctx->hc[g].sched_base, ctx->sched[g].data(),
+                                 ctx->sched[g].size() * 8, hipMemcpyHostToDevice, s));
   HIPCHK(ctx, hipStreamSynchronize(s));
   ctx->next_id.assign(G, 0);
   HIPCHK(ctx, hipGetDevice(&ctx->device));
@@ -610,6 +612,33 @@ static gs_status scratch_setup(gs_ctx *ctx) {
   return GS_OK;
 }
 
+// A new context's copies of its parameters, and its set-up; may throw bad_alloc.
+static gs_status init_context(gs_ctx *ctx, int n_gaps, const gs_gap_params *params, const gs_allocator *alloc,
+                              hipStream_t stream) {
+  ctx->G = n_gaps;
+  ctx->fp64 = params[0].particle_fp == 64;
+  if (alloc) ctx->alloc = *alloc;
+  ctx->stream = stream;
+  int nm = 0;
+  for (int g = 0; g < n_gaps; ++g) nm = std::max(nm, params[g].n_cells);
+  if (push_lds_bytes(nm, ctx->fp64, n_gaps, ctx->fp64) + 256 * 4 > 163840)
+    return fail(ctx, GS_EINVAL, "grid of %d cells with %d gaps exceeds the 160 KiB LDS budget", nm, n_gaps);
+  ctx->params.assign(params, params + n_gaps);
+  // the schedules are copied; the caller keeps its arrays
+  ctx->sched.assign(n_gaps, std::vector<int64_t>());
+  ctx->sched_on.assign(n_gaps, 0);
+  for (int g = 0; g < n_gaps; ++g) {
+    if (params[g].beam_schedule) {
+      ctx->sched_on[g] = 1;
+      ctx->sched[g].assign(params[g].beam_schedule, params[g].beam_schedule + params[g].beam_schedule_len);
+    }
+    ctx->params[g].beam_schedule = nullptr;
+    ctx->params[g].beam_schedule_len = 0;
+  }
+  const gs_status st = setup(ctx);
+  return st == GS_OK ? scratch_setup(ctx) : st;
+}
+
 extern "C" gs_status gs_init_gap(gs_ctx **out, int32_t n_gaps, const gs_gap_params *params,
                              const gs_allocator *alloc, void *hip_stream) {
   if (!out) return fail(nullptr, GS_EINVAL, "out is NULL");
@@ -626,31 +655,13 @@ extern "C" gs_status gs_init_gap(gs_ctx **out, int32_t n_gaps, const gs_gap_para
     return fail(nullptr, GS_EINVAL, "allocator needs both alloc and release");
   gs_ctx *ctx = new (std::nothrow) gs_ctx();
   if (!ctx) return fail(nullptr, GS_ENOMEM, "out of host memory");
-  ctx->G = n_gaps;
-  ctx->fp64 = params[0].particle_fp == 64;
-  ctx->params.assign(params, params + n_gaps);
-  // the schedules are copied; the caller keeps its arrays
-  ctx->sched.assign(n_gaps, std::vector<int64_t>());
-  ctx->sched_on.assign(n_gaps, 0);
-  for (int g = 0; g < n_gaps; ++g) {
-    if (params[g].beam_schedule) {
-      ctx->sched_on[g] = 1;
-      ctx->sched[g].assign(params[g].beam_schedule, params[g].beam_schedule + params[g].beam_schedule_len);
-    }
-    ctx->params[g].beam_schedule = nullptr;
-    ctx->params[g].beam_schedule_len = 0;
+  gs_status st;
+  try {  // (the context's copies and lists)
+    st = init_context(ctx, n_gaps, params, alloc, (hipStream_t)hip_stream);
+  } catch (...) {
+    st = GS_ENOMEM;
+    ctx->err = "out of host memory";
   }
-  ctx->stream = (hipStream_t)hip_stream;
-  if (alloc) ctx->alloc = *alloc;
-  int nm = 0;
-  for (int g = 0; g < n_gaps; ++g) nm = std::max(nm, params[g].n_cells);
-  const size_t lds = push_lds_bytes(nm, ctx->fp64, n_gaps, ctx->fp64) + 256 * 4;
-  if (lds > 163840) {
-    delete ctx;
-    return fail(nullptr, GS_EINVAL, "grid of %d cells with %d gaps exceeds the 160 KiB LDS budget", nm, n_gaps);
-  }
-  gs_status st = setup(ctx);
-  if (st == GS_OK) st = scratch_setup(ctx);
   if (st != GS_OK) {
     g_init_error = ctx->err;
     if (ctx->ext_ev) (void)hipEventDestroy(ctx->ext_ev);
