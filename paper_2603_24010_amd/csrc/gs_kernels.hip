@@ -308,6 +308,8 @@ __device__ inline PushHead load_head(const DevPtrs &p, int g) {
 // The push kernel's pointers (its first argument), read where a part of it begins.
 // Held as ordinary values they are loaded at the kernel's start, one after the
 // other, and spilled: more of them than scalar registers, over a microsecond.
+// (The argument segment's address is a kernel's alone: every function that calls this
+// is forced inline, up to the kernel.)
 template <class T>
 __device__ __forceinline__ void as_global(T *&q) {
   q = (T *)(__attribute__((address_space(1))) T *)(unsigned long long)q;
@@ -353,7 +355,7 @@ __device__ __forceinline__ DevPtrs push_args() {
 // rather than line by line where push_args comes to them (1e5 particles on 256 cells:
 // 0.3 us of a step of 19.2).
 template <size_t BYTES>
-__device__ inline unsigned int touch_args() {
+__device__ __forceinline__ unsigned int touch_args() {
   const __attribute__((address_space(4))) unsigned int *a =
       (const __attribute__((address_space(4))) unsigned int *)__builtin_amdgcn_kernarg_segment_ptr();
   unsigned int w = 0u;
@@ -1796,7 +1798,7 @@ __device__ inline int queued_count(const DevPtrs &p, ConstGap &c, const PushHead
 // device), in flight while the nodes are flushed.  On the workgroup's last segment
 // the last wave takes its ticket (see push_ticket).
 template <class P, class AC>
-__device__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P, AC> &sh,
+__device__ __forceinline__ void flush_seg(const PushHead &h, int g, int s, int sel, PushShared<P, AC> &sh,
                           bool ticket) {
   __shared__ unsigned long long s_base;
   lds_barrier();

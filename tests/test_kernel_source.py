@@ -1,0 +1,30 @@
+"""What the kernels' source has to keep to for the compiled code to be right."""
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_24010_amd", "csrc")
+
+
+def _functions(text):
+    """(declaration, body) of every function that starts at the first column."""
+    text = re.sub(r"//[^\n]*", "", text)
+    for m in re.finditer(r"^(?:template <[^\n]*>\n)?[^\n#}]*\b__(?:device|global)__[^;{]*\{\n(.*?)^\}", text, re.S | re.M):
+        yield text[m.start():m.start(1)], m.group(1)
+
+
+def test_readers_of_the_kernel_arguments_are_inlined_into_a_kernel():
+    """__builtin_amdgcn_kernarg_segment_ptr() is null in a function that is not: its callers
+    (touch_args and push_args, and those that call them) are kernels or forced inline."""
+    fns = list(_functions(open(os.path.join(CSRC, "gs_kernels.hip")).read()))
+    reads, seen = {"__builtin_amdgcn_kernarg_segment_ptr"}, set()
+    while reads - seen:
+        name = (reads - seen).pop()
+        seen.add(name)
+        callers = [decl for decl, body in fns if re.search(r"\b%s\b" % name, body)]
+        assert callers, name
+        for decl in callers:
+            if "__global__" in decl:
+                continue
+            assert "__forceinline__" in decl, decl
+            reads.add(re.search(r"(\w+)\(", decl.split("__forceinline__")[1]).group(1))
+    assert {"push_args", "flush_seg", "close_seg", "push_piece", "push_tail_emit"} <= reads
