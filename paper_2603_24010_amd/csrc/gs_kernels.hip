@@ -3268,7 +3268,8 @@ __global__ void k_inject(DevPtrs p, int gap, int species, long long n, const dou
 // particle); what bounded the direct additions was their two global atomics
 // per particle.
 constexpr int IBS = 1024;    // threads
-constexpr int INJ_RUN = 4;   // least particles per node and workgroup (see inject_t)
+constexpr int INJ_RUN = 4, INJ_RUNS = 6;  // least particles per node and workgroup, and workgroups
+                                          // (see inject_t)
 constexpr int IU = 4;        // particles per thread whose loads are in flight together
 template <class P>
 __global__ __launch_bounds__(IBS) void k_inject_run(DevPtrs p, int gap, int species, long long n, const double *x,
@@ -3633,9 +3634,12 @@ static hipError_t inject_t(const DevPtrs &p, int gap, int species, long long n, 
                            long long id0, int N, int ncu, hipStream_t s) {
   // runs of at least INJ_RUN particles per node, so that a run's flush (N + 1
   // atomics at most) stays small beside the 2 x run atomics it replaces; below
-  // two such runs the direct kernel
+  // INJ_RUNS such runs the direct kernel, which has more of the chip at work.  A call with
+  // 8, 16 and 32 particles per node, us: 600 cells 28.2, 30.1 and 34.8 direct, 29.4, 32.0
+  // and 32.8 by runs; 4096 cells 33.4, 41.3, 58.6 and 43.4, 43.4, 44.4; 16384 cells 60.2,
+  // 99.9, 177 and 92.6, 93.6, 94.0
   const long long runs = n / (INJ_RUN * (long long)(N + 1));
-  if (runs < 2) {
+  if (runs < INJ_RUNS) {
     const int bs = 256;
     hipLaunchKernelGGL(k_inject<P>, dim3((unsigned int)((n + bs - 1) / bs)), dim3(bs), 0, s, p, gap, species, n, x, v,
                        id0);
