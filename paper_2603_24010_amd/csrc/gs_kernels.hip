@@ -3646,12 +3646,12 @@ static hipError_t inject_t(const DevPtrs &p, int gap, int species, long long n, 
     return hipGetLastError();
   }
   const size_t lds = (size_t)(N + 1) * 8;
-  static size_t attr_set = 65536;
-  if (lds > attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_inject_run<P>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds);
+  // (asked for on each such call, on whichever device is current, and always the largest
+  // grid's: nothing is remembered between calls, and calls of several threads agree)
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void *)k_inject_run<P>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (16384 + 1) * 8);
     if (e != hipSuccess) return e;
-    attr_set = lds;
   }
   // a workgroup's LDS lets two share a CU up to 8191 cells
   const long long most = (long long)std::max(ncu, 1) * (lds <= 65536 ? 2 : 1);

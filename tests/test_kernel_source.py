@@ -28,3 +28,11 @@ def test_readers_of_the_kernel_arguments_are_inlined_into_a_kernel():
             assert "__forceinline__" in decl, decl
             reads.add(re.search(r"(\w+)\(", decl.split("__forceinline__")[1]).group(1))
     assert {"push_args", "flush_seg", "close_seg", "push_piece", "push_tail_emit"} <= reads
+
+
+def test_injection_remembers_nothing_between_calls():
+    """A launch attribute set once per process is missing on a second device, and a smaller
+    one set later by another thread takes a larger one's place."""
+    src = re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, "gs_kernels.hip")).read())
+    body = re.search(r"static hipError_t inject_t\(.*?^\}", src, re.S | re.M).group(0)
+    assert "hipFuncSetAttribute" in body and "static" not in body.split("\n", 1)[1]
