@@ -1957,6 +1957,9 @@ __device__ void load_seg(const DevPtrs &p, const PushHead &h, int g, int sel,
   if (stage) lds_barrier();
 }
 
+// s_waitcnt for everything that a wave has under way in vector memory
+constexpr int VMCNT0 = 0x0F70;
+
 // Per-thread running counts of one segment.
 struct SegCount {
   unsigned int pushed = 0, abs0 = 0, abs1 = 0;
@@ -2035,43 +2038,6 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
     w1[k] = stay ? q1 : (typename Prec<P>::wt)0;
     w0[k] = stay ? (typename Prec<P>::wt)Prec<P>::W - q1 : (typename Prec<P>::wt)0;
   }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const long long i = r0 + (long long)(v * BS + tid) * VN;
-    if (FULL) {
-      st_stream<NT>((V *)(X + i), xw[v]);
-      st_stream<NT>((V *)(U + i), uw[v]);
-    } else {
-#pragma unroll
-      for (int k = 0; k < VN; ++k)
-        if (i + k < n_here) {
-          X[i + k] = Vec<P>::at(xw[v], k);
-          U[i + k] = Vec<P>::at(uw[v], k);
-        }
-    }
-  }
-  if (c.masks) {
-    // a compaction follows: the slots' liveness after this push, as whole
-    // 64-slot words of the region's live masks (the lanes of a word gather
-    // their bits; the compaction reads positions only for the words left)
-    constexpr int LPW = 64 / VN;  // lanes per word
-    const int lane = tid & 63;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      unsigned long long m = (unsigned long long)((alive >> (v * VN)) & ((1u << VN) - 1u))
-                             << (VN * (lane % LPW));
-#pragma unroll
-      for (int o = 1; o < LPW; o <<= 1) m |= __shfl_xor(m, o, 64);
-      const long long i = r0 + (long long)(v * BS + tid) * VN;
-      if (lane % LPW == 0 && (FULL || i + 64 <= n_here)) c.live[i / 64] = m;
-    }
-  }
-  // every slot adds (zero weights for slots that do not deposit): no branches
-#pragma unroll
-  for (int k = 0; k < PPT; ++k) {
-    acc_add<AC>(sh.acc, c.gacc, jj[k], (unsigned long long)w0[k], zhi);
-    acc_add<AC>(sh.acc, c.gacc, jj[k] + 1, (unsigned long long)w1[k], zhi);
-  }
   // absorbed ions are queued for secondary emission: in LDS (emitted at the
   // segment's flush), then in the workgroup's overflow region, then in the
   // gap's list (emitted at the end of the push by its last workgroup, or by
@@ -2079,7 +2045,9 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
   // takes its queue positions, and its share of the gap's list, with one atomic
   // each: a workgroup whose particles sit at a wall (sorted particles) absorbs
   // thousands of ions in one push, and an atomic per ion on the gap's counter
-  // would serialise them.
+  // would serialise them.  (Before the particles' own stores, behind which theirs would
+  // be the last that the wave waits for: 16384 cells, 3.1e5 ions absorbed of 1.3e8, 3.7e7
+  // electrons, 560 us a push and 585.)
   if (see) {
     const int nh = __popc(hit & 0xFFFFu);
     if (__ballot(nh != 0) != 0ull) {
@@ -2128,6 +2096,43 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
       }
     }
   }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const long long i = r0 + (long long)(v * BS + tid) * VN;
+    if (FULL) {
+      st_stream<NT>((V *)(X + i), xw[v]);
+      st_stream<NT>((V *)(U + i), uw[v]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < VN; ++k)
+        if (i + k < n_here) {
+          X[i + k] = Vec<P>::at(xw[v], k);
+          U[i + k] = Vec<P>::at(uw[v], k);
+        }
+    }
+  }
+  if (c.masks) {
+    // a compaction follows: the slots' liveness after this push, as whole
+    // 64-slot words of the region's live masks (the lanes of a word gather
+    // their bits; the compaction reads positions only for the words left)
+    constexpr int LPW = 64 / VN;  // lanes per word
+    const int lane = tid & 63;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      unsigned long long m = (unsigned long long)((alive >> (v * VN)) & ((1u << VN) - 1u))
+                             << (VN * (lane % LPW));
+#pragma unroll
+      for (int o = 1; o < LPW; o <<= 1) m |= __shfl_xor(m, o, 64);
+      const long long i = r0 + (long long)(v * BS + tid) * VN;
+      if (lane % LPW == 0 && (FULL || i + 64 <= n_here)) c.live[i / 64] = m;
+    }
+  }
+  // every slot adds (zero weights for slots that do not deposit): no branches
+#pragma unroll
+  for (int k = 0; k < PPT; ++k) {
+    acc_add<AC>(sh.acc, c.gacc, jj[k], (unsigned long long)w0[k], zhi);
+    acc_add<AC>(sh.acc, c.gacc, jj[k] + 1, (unsigned long long)w1[k], zhi);
+  }
 }
 
 template <class P, int BS, int PPT, bool NT>
@@ -2149,7 +2154,7 @@ __device__ inline void load_chunk(const P *X, const P *U, long long r0, typename
 // workgroup takes in round-robin order.)  Full chunks are software-pipelined,
 // across runs too: the loads of the next chunk are in flight while this one is
 // pushed.  Every load in the loop is unconditional (past the last full chunk
-// it repeats that chunk's, whose data is dropped), so the waits count exactly.
+// it repeats that chunk's, whose data is dropped).
 // The remainder goes slot by slot: slots past b may be receiving appended
 // particles.
 template <class P, class AC, int BS, int PPT, bool NT>
@@ -2192,6 +2197,11 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
   // when the segment is already open, while this range's beam goes in)
   if (nfull > 0) load_chunk<P, BS, PPT, NT>(X, U, a, xa, ua);
   if (stage || kb1 > kb0) load_seg<P, AC>(p, h, g, sel, sh, kb0, kb1, stage, table);
+  // (Those loads are waited for here, and in the loop all that a pass has under way at its
+  // end: left to itself the compiler put that wait where it found loads it could not
+  // count, at the loop's top.  With the stores running on into the next pass, 2e8 ions
+  // and 3e7 electrons on 16384 cells take 678 us a push; so, 668.)
+  __builtin_amdgcn_s_waitcnt(VMCNT0);
   // one copy of the chunk body (the kernel's instruction footprint is what
   // limits it): the next chunk's loads go out before this chunk is pushed,
   // and the buffers are swapped by register moves
@@ -2214,6 +2224,7 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
     }
     rb = rbn;
     ci = cin;
+    __builtin_amdgcn_s_waitcnt(VMCNT0);
   }
   const long long r0 = rb + (long long)ci * CH;
   if (r0 < b) {

@@ -1,6 +1,7 @@
 """What the kernels' source has to keep to for the compiled code to be right."""
 import os
 import re
+import subprocess
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_24010_amd", "csrc")
 
@@ -36,3 +37,27 @@ def test_injection_remembers_nothing_between_calls():
     src = re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, "gs_kernels.hip")).read())
     body = re.search(r"static hipError_t inject_t\(.*?^\}", src, re.S | re.M).group(0)
     assert "hipFuncSetAttribute" in body and "static" not in body.split("\n", 1)[1]
+
+
+def test_the_pushs_chunk_loop(tmp_path):
+    """The compiled loop over full chunks (binary32, one vector a thread): the absorbed
+    ions' stores go out before the particles' own, behind which the wave would wait for
+    them, and nothing is waited for between the loop's top and the next chunk's loads."""
+    from paper_2603_24010_amd import build as B
+    out = str(tmp_path / "push.s")
+    flags = [f for f in B.FLAGS if f != "-Wall"]
+    cmd = [B.HIPCC, *flags, "-w", "-I", os.path.join(B.ROOT, "include"), "-I", B.CSRC, "-DGS_PUSH_PART=4",
+           "--cuda-device-only", "-S", os.path.join(B.CSRC, "gs_kernels.hip"), "-o", out]
+    subprocess.run(cmd, check=True)
+    text = open(out).read()
+    seen = 0
+    for m in re.finditer(r"^_ZN2gs6k_push\w*Li4ELb1E\w*:(.*?)^\.Lfunc_end", text, re.S | re.M):
+        lines = m.group(1).splitlines()
+        store = next(i for i, ln in enumerate(lines) if "global_store_dwordx4" in ln and ln.rstrip().endswith(" nt"))
+        loads = [i for i in range(store) if "global_load_dwordx4" in lines[i] and lines[i].rstrip().endswith(" nt")][-2:]
+        top = max(i for i in range(loads[0]) if re.match(r"\.LBB.*Parent Loop BB\d+_\d+ Depth=1", lines[i]))
+        assert loads[1] - top < 60, "the chunk loop's top"
+        assert not any("vmcnt" in ln for ln in lines[top:loads[0]])
+        assert any("v_cvt_f64_f32" in ln for ln in lines[top:store]), "the queued ions' impact velocities"
+        seen += 1
+    assert seen == 4  # workgroups of 256, 512, 768 and 1024
