@@ -1759,7 +1759,6 @@ __device__ inline void flush_nodes(const DevPtrs &p, const PushHead &h, int s, P
     if (lane == 0) q0 = (int)atomicAdd(sh.piece, 256u);
     q0 = __builtin_amdgcn_readfirstlane(q0);
     if (q0 >= nn) break;
-#pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int q = q0 + 64 * i + lane;
       int j = q + rot;
@@ -2386,7 +2385,6 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   sh.eh = (P *)(lds_raw + off);
   sh.acc = (cell *)(lds_raw + off + ((((size_t)(nmax + 2) * sizeof(P)) + 15) / 16) * 16);
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
   const unsigned int args = touch_args<sizeof(DevPtrs) + 7 * 4>();
   asm volatile("" ::"s"(args));
   const int sel = (int)(*p.epoch & 1);
