@@ -1981,7 +1981,7 @@ struct SegK {
 // Push one chunk of BS * PPT slots starting at slot r0 (relative to the region
 // base): thread tid owns slots r0 + (v * BS + tid) * VN + kk.  FULL: every slot
 // lies below n_here, so vectors are stored whole; otherwise slot by slot.
-template <class P, class AC, int BS, int PPT, bool FULL, bool NT>
+template <class P, class AC, int BS, int PPT, bool FULL, bool NT, bool RR>
 __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P, AC> &sh, P *X, P *U,
                                   long long r0, long long n_here, typename Vec<P>::type *xv,
                                   typename Vec<P>::type *uv, P alpha, bool see, long long zhi, SegCount &cnt) {
@@ -2044,93 +2044,101 @@ __device__ inline void push_chunk(const DevPtrs &p, const SegK &c, PushShared<P,
   // takes its queue positions, and its share of the gap's list, with one atomic
   // each: a workgroup whose particles sit at a wall (sorted particles) absorbs
   // thousands of ions in one push, and an atomic per ion on the gap's counter
-  // would serialise them.  (Before the particles' own stores, behind which theirs would
-  // be the last that the wave waits for: 16384 cells, 3.1e5 ions absorbed of 1.3e8, 3.7e7
-  // electrons, 560 us a push and 585.)
-  if (see) {
-    const int nh = __popc(hit & 0xFFFFu);
-    if (__ballot(nh != 0) != 0ull) {
-      const int lane = tid & 63;
-      const int incl = wave_incl_scan(nh);
-      const unsigned int tot = (unsigned int)__builtin_amdgcn_readlane(incl, 63);
-      unsigned int q0 = 0;
-      if (lane == 0) q0 = atomicAdd(sh.evq_n, tot);
-      q0 = (unsigned int)__builtin_amdgcn_readfirstlane((int)q0);
-      const unsigned int lim = c.lim;
-      const unsigned int over0 = q0 > lim ? q0 : lim;
-      const unsigned int n_over = q0 + tot > lim ? q0 + tot - over0 : 0u;
-      unsigned long long gb = 0;
-      if (n_over) {
-        if (lane == 0) gb = atomicAdd(&p.ev_count[g], (unsigned long long)n_over);
-        gb = __shfl(gb, 0, 64);
-      }
-      unsigned int q = q0 + (unsigned int)(incl - nh);
-      unsigned int rest = hit & 0xFFFFu;
-      while (rest) {
-        const int k = __ffs(rest) - 1;
-        rest &= rest - 1u;
-        Event ev;
-        P uk = u_hit[0];
+  // would serialise them.
+  // Round-robin workgroups, whose passes end with a wait (see push_range), queue before
+  // the particles' stores: behind these the queue's would be the last waited for (16384
+  // cells, 3.1e5 ions absorbed of 1.3e8, 3.7e7 electrons: 564 us a push and 585).  The
+  // others queue last (1e8 ions: 534 us, 539 queueing first).
 #pragma unroll
-        for (int j = 1; j < PPT; ++j)
-          if (j == k) uk = u_hit[j];
-        ev.u = (double)uk;
-        ev.ref = (uint32_t)(r0 + (long long)((k / VN) * BS + tid) * VN + k % VN);
-        ev.wall = (hit >> (k + 16)) & 1u;
-        if (q < (unsigned int)EVQ) {
-          sh.evq[q] = ev;
-        } else if (q < lim) {
-          c.ovf[q - EVQ] = ev;
-        } else {
-          const unsigned long long e = gb + (unsigned long long)(q - over0);
-          if (e < (unsigned long long)c.evcap) {
-            ev.ref = c.ids[ev.ref];
-            p.ev[c.evbase + e] = ev;
-          } else {
-            atomicOr(&p.err[0], ERR_CAPACITY);
-            atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)g);
+  for (int half = 0; half < 2; ++half) {
+    if ((half == 0) == RR) {
+      if (see) {
+        const int nh = __popc(hit & 0xFFFFu);
+        if (__ballot(nh != 0) != 0ull) {
+          const int lane = tid & 63;
+          const int incl = wave_incl_scan(nh);
+          const unsigned int tot = (unsigned int)__builtin_amdgcn_readlane(incl, 63);
+          unsigned int q0 = 0;
+          if (lane == 0) q0 = atomicAdd(sh.evq_n, tot);
+          q0 = (unsigned int)__builtin_amdgcn_readfirstlane((int)q0);
+          const unsigned int lim = c.lim;
+          const unsigned int over0 = q0 > lim ? q0 : lim;
+          const unsigned int n_over = q0 + tot > lim ? q0 + tot - over0 : 0u;
+          unsigned long long gb = 0;
+          if (n_over) {
+            if (lane == 0) gb = atomicAdd(&p.ev_count[g], (unsigned long long)n_over);
+            gb = __shfl(gb, 0, 64);
+          }
+          unsigned int q = q0 + (unsigned int)(incl - nh);
+          unsigned int rest = hit & 0xFFFFu;
+          while (rest) {
+            const int k = __ffs(rest) - 1;
+            rest &= rest - 1u;
+            Event ev;
+            P uk = u_hit[0];
+#pragma unroll
+            for (int j = 1; j < PPT; ++j)
+              if (j == k) uk = u_hit[j];
+            ev.u = (double)uk;
+            ev.ref = (uint32_t)(r0 + (long long)((k / VN) * BS + tid) * VN + k % VN);
+            ev.wall = (hit >> (k + 16)) & 1u;
+            if (q < (unsigned int)EVQ) {
+              sh.evq[q] = ev;
+            } else if (q < lim) {
+              c.ovf[q - EVQ] = ev;
+            } else {
+              const unsigned long long e = gb + (unsigned long long)(q - over0);
+              if (e < (unsigned long long)c.evcap) {
+                ev.ref = c.ids[ev.ref];
+                p.ev[c.evbase + e] = ev;
+              } else {
+                atomicOr(&p.err[0], ERR_CAPACITY);
+                atomicCAS(&p.err[1], 0xFFFFFFFFu, (unsigned int)g);
+              }
+            }
+            q += 1u;
           }
         }
-        q += 1u;
       }
-    }
-  }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const long long i = r0 + (long long)(v * BS + tid) * VN;
-    if (FULL) {
-      st_stream<NT>((V *)(X + i), xw[v]);
-      st_stream<NT>((V *)(U + i), uw[v]);
     } else {
 #pragma unroll
-      for (int k = 0; k < VN; ++k)
-        if (i + k < n_here) {
-          X[i + k] = Vec<P>::at(xw[v], k);
-          U[i + k] = Vec<P>::at(uw[v], k);
+      for (int v = 0; v < NV; ++v) {
+        const long long i = r0 + (long long)(v * BS + tid) * VN;
+        if (FULL) {
+          st_stream<NT>((V *)(X + i), xw[v]);
+          st_stream<NT>((V *)(U + i), uw[v]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < VN; ++k)
+            if (i + k < n_here) {
+              X[i + k] = Vec<P>::at(xw[v], k);
+              U[i + k] = Vec<P>::at(uw[v], k);
+            }
         }
+      }
+      if (c.masks) {
+        // a compaction follows: the slots' liveness after this push, as whole
+        // 64-slot words of the region's live masks (the lanes of a word gather
+        // their bits; the compaction reads positions only for the words left)
+        constexpr int LPW = 64 / VN;  // lanes per word
+        const int lane = tid & 63;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          unsigned long long m = (unsigned long long)((alive >> (v * VN)) & ((1u << VN) - 1u))
+                                 << (VN * (lane % LPW));
+#pragma unroll
+          for (int o = 1; o < LPW; o <<= 1) m |= __shfl_xor(m, o, 64);
+          const long long i = r0 + (long long)(v * BS + tid) * VN;
+          if (lane % LPW == 0 && (FULL || i + 64 <= n_here)) c.live[i / 64] = m;
+        }
+      }
+      // every slot adds (zero weights for slots that do not deposit): no branches
+#pragma unroll
+      for (int k = 0; k < PPT; ++k) {
+        acc_add<AC>(sh.acc, c.gacc, jj[k], (unsigned long long)w0[k], zhi);
+        acc_add<AC>(sh.acc, c.gacc, jj[k] + 1, (unsigned long long)w1[k], zhi);
+      }
     }
-  }
-  if (c.masks) {
-    // a compaction follows: the slots' liveness after this push, as whole
-    // 64-slot words of the region's live masks (the lanes of a word gather
-    // their bits; the compaction reads positions only for the words left)
-    constexpr int LPW = 64 / VN;  // lanes per word
-    const int lane = tid & 63;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      unsigned long long m = (unsigned long long)((alive >> (v * VN)) & ((1u << VN) - 1u))
-                             << (VN * (lane % LPW));
-#pragma unroll
-      for (int o = 1; o < LPW; o <<= 1) m |= __shfl_xor(m, o, 64);
-      const long long i = r0 + (long long)(v * BS + tid) * VN;
-      if (lane % LPW == 0 && (FULL || i + 64 <= n_here)) c.live[i / 64] = m;
-    }
-  }
-  // every slot adds (zero weights for slots that do not deposit): no branches
-#pragma unroll
-  for (int k = 0; k < PPT; ++k) {
-    acc_add<AC>(sh.acc, c.gacc, jj[k], (unsigned long long)w0[k], zhi);
-    acc_add<AC>(sh.acc, c.gacc, jj[k] + 1, (unsigned long long)w1[k], zhi);
   }
 }
 
@@ -2153,10 +2161,10 @@ __device__ inline void load_chunk(const P *X, const P *U, long long r0, typename
 // workgroup takes in round-robin order.)  Full chunks are software-pipelined,
 // across runs too: the loads of the next chunk are in flight while this one is
 // pushed.  Every load in the loop is unconditional (past the last full chunk
-// it repeats that chunk's, whose data is dropped).
+// it repeats that chunk's, whose data is dropped), so the waits count exactly.
 // The remainder goes slot by slot: slots past b may be receiving appended
 // particles.
-template <class P, class AC, int BS, int PPT, bool NT>
+template <class P, class AC, int BS, int PPT, bool NT, bool RR>
 __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, int sel, PushShared<P, AC> &sh,
                            long long a, long long b, long long run, long long step, int nrun, long long kb0,
                            long long kb1, bool stage, bool table, SegCount &cnt) {
@@ -2196,10 +2204,13 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
   // when the segment is already open, while this range's beam goes in)
   if (nfull > 0) load_chunk<P, BS, PPT, NT>(X, U, a, xa, ua);
   if (stage || kb1 > kb0) load_seg<P, AC>(p, h, g, sel, sh, kb0, kb1, stage, table);
-  // (Those loads are waited for here, and in the loop all that a pass has under way at its
-  // end: left to itself the compiler put that wait where it found loads it could not
-  // count, at the loop's top.  With the stores running on into the next pass, 2e8 ions
-  // and 3e7 electrons on 16384 cells take 678 us a push; so, 668.)
+  // Those loads are waited for here: were they still under way where the loop begins, its
+  // first wait would be for everything under way, in every pass, the stores of the chunk
+  // before among it.  Where workgroups take tiles round robin that is wanted (at a pass's
+  // end): they stay together, 1e8 ions and 1.5e7 electrons on 16384 cells take 368 us a
+  // push and 376 without, 2e8 and 3e7 with non-temporal accesses 670 and 678.  With
+  // contiguous runs it is not: 559 and 534 us, and 16 gaps of 2e6 ions on 2500 cells 136
+  // and 127.
   __builtin_amdgcn_s_waitcnt(VMCNT0);
   // one copy of the chunk body (the kernel's instruction footprint is what
   // limits it): the next chunk's loads go out before this chunk is pushed,
@@ -2215,7 +2226,7 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
     }
     const long long cur = rb + (long long)ci * CH;
     load_chunk<P, BS, PPT, NT>(X, U, q + 1 < nfull ? rbn + (long long)cin * CH : cur, xb, ub);
-    push_chunk<P, AC, BS, PPT, true, NT>(p, c, sh, X, U, cur, b, xa, ua, alpha, see, zhi, cnt);
+    push_chunk<P, AC, BS, PPT, true, NT, RR>(p, c, sh, X, U, cur, b, xa, ua, alpha, see, zhi, cnt);
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       xa[v] = xb[v];
@@ -2223,7 +2234,7 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
     }
     rb = rbn;
     ci = cin;
-    __builtin_amdgcn_s_waitcnt(VMCNT0);
+    if (RR) __builtin_amdgcn_s_waitcnt(VMCNT0);
   }
   const long long r0 = rb + (long long)ci * CH;
   if (r0 < b) {
@@ -2236,7 +2247,7 @@ __device__ void push_range(const DevPtrs &p, const PushHead &h, int g, int s, in
         Vec<P>::at(ua[v], k) = (i + k < b) ? U[i + k] : (P)0;
       }
     }
-    push_chunk<P, AC, BS, PPT, false, NT>(p, c, sh, X, U, r0, b, xa, ua, alpha, see, zhi, cnt);
+    push_chunk<P, AC, BS, PPT, false, NT, RR>(p, c, sh, X, U, r0, b, xa, ua, alpha, see, zhi, cnt);
   }
 }
 
@@ -2255,7 +2266,7 @@ __device__ __forceinline__ void close_seg(PushShared<P, AC> &sh, int sel, int og
   flush_seg<P, AC>(h, g, s, sel, sh, ticket);
 }
 
-template <class P, class AC, int BS, int PPT, bool NT>
+template <class P, class AC, int BS, int PPT, bool NT, bool RR>
 __device__ __forceinline__ void push_piece(PushShared<P, AC> &sh, int tile, int sel, int g,
                                            int s, int ls, int le, int stride, int ti, int og, int os) {
   g = __builtin_amdgcn_readfirstlane(g);
@@ -2286,7 +2297,7 @@ __device__ __forceinline__ void push_piece(PushShared<P, AC> &sh, int tile, int 
     kb0 = share_of((unsigned int)st.beam_now, (unsigned int)ls, (unsigned int)nb);
     kb1 = share_of((unsigned int)st.beam_now, (unsigned int)(stride == 1 ? le : ls + 1), (unsigned int)nb);
   }
-  push_range<P, AC, BS, PPT, NT>(p, st, g, s, sel, sh, a, b, run, step, nrun, kb0, kb1, stage, table, cnt);
+  push_range<P, AC, BS, PPT, NT, RR>(p, st, g, s, sel, sh, a, b, run, step, nrun, kb0, kb1, stage, table, cnt);
   // wave-level sums, then one LDS atomic per wave
   const unsigned int v0 = wave_sum(cnt.pushed), v1 = wave_sum(cnt.abs0), v2 = wave_sum(cnt.abs1);
   if ((threadIdx.x & 63) == 0) {
@@ -2360,9 +2371,10 @@ __device__ inline int rr_electrons(int te, int ti, int nwg) {
   return best;
 }
 
-template <class P, class AC, int BS, int PPT, bool NT>
-__global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int nmax, int steal, int rr,
-                                                 int min_wgs, int masks, int lists) {
+// RR: round-robin tile order (STREAM_RR)
+template <class P, class AC, int BS, int PPT, bool NT, bool RR>
+__global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int nmax, int steal, int min_wgs,
+                                                 int masks, int lists) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   typedef typename AC::cell cell;
   __shared__ int scan_sh[BS];
@@ -2434,7 +2446,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   // start first, and the others end at once)
   const int most_wgs = min((int)gridDim.x, max(total, 1));
   int nwg = most_wgs;
-  if (G == 1 && !rr && steal == 0) {
+  if (G == 1 && !RR && steal == 0) {
     // and, of one gap, no more than leave each FLUSH_SHARE slots per node, down to
     // min_wgs (one per CU; all, when the caller set the grid): every one adds its
     // node sums to the gap's row.  2.3e6 particles on 4096 cells: 256 workgroups
@@ -2457,7 +2469,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   // strided piece, and t visits the workgroup's first tile of each region it has
   // tiles in (that tile's local index is below nwg).
   int R = 0;
-  if (!rr && steal > 0) {
+  if (!RR && steal > 0) {
     int st = steal;
     asm volatile("" : "+s"(st));
     R = (total / nwg) / st;
@@ -2465,11 +2477,11 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   // Round robin over one gap gives each region workgroups of its own, in proportion to
   // its tiles (see rr_electrons): a workgroup with tiles of both stages and flushes
   // two segments.
-  const int ne = G == 1 && rr ? rr_electrons(te1, ti1, nwg) : 0;
+  const int ne = G == 1 && RR ? rr_electrons(te1, ti1, nwg) : 0;
   const bool own = ne > 0, ions = own && (int)blockIdx.x >= ne;
-  const int stride = !rr ? 1 : ions ? nwg - ne : own ? ne : nwg;  // (of a workgroup's tiles)
+  const int stride = !RR ? 1 : ions ? nwg - ne : own ? ne : nwg;  // (of a workgroup's tiles)
   int t = ions ? te1 + (int)blockIdx.x - ne
-          : rr ? (int)blockIdx.x
+          : RR ? (int)blockIdx.x
                : (int)share_of((unsigned int)total, blockIdx.x, (unsigned int)nwg);
   // The overflow regions of the workgroups that take ions: p.ovq events to each, and when
   // fewer take them than there are tiles and blocks for, what the others would have held
@@ -2483,7 +2495,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
     sh.ovf_i = blockIdx.x - (ions ? (unsigned int)ne : 0u);
     sh.ovf_room = sh.ovf_i < regions && (ions || !own) ? room : 0u;
   }
-  int t1 = own && !ions ? te1 : rr ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
+  int t1 = own && !ions ? te1 : RR ? total : (int)share_of((unsigned int)total, blockIdx.x + 1u, (unsigned int)nwg) - R;
   // pool tile q is tile k = q / nwg of run w = q % nwg's reserved end: the first
   // reserved tile of every run goes out first
   // (the next index is taken while a tile is pushed: the counter is one address
@@ -2531,7 +2543,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
       s = t - tg < te ? 0 : 1;
       const int T0 = s ? tg + te : tg, T1 = s ? tg + te + ti : tg + te;  // the region's tiles
       ls = t - T0;
-      if (rr) {
+      if (RR) {
         le = T1 - T0;
         t += ((T1 - t + stride - 1) / stride) * stride;  // the first of its tiles past the region
       } else {
@@ -2541,7 +2553,7 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
     }
     if (og >= 0 && !(more && g == og && s == os)) close_seg<P, AC>(sh, sel, og, os, lists != 0 && !more);
     if (!more) break;
-    push_piece<P, AC, BS, PPT, NT>(sh, tile, sel, g, s, ls, le, stride, ti, og, os);
+    push_piece<P, AC, BS, PPT, NT, RR>(sh, tile, sel, g, s, ls, le, stride, ti, og, os);
     og = g;
     os = s;
   }
@@ -2554,35 +2566,40 @@ __global__ __launch_bounds__(BS, 3) void k_push(DevPtrs p, int G, int tile, int 
   if (lists) push_tail_emit<P, AC>(sh, G, sel);
 }
 
-template <class P, class AC, int BS, int PPT, bool NT>
+template <class P, class AC, int BS, int PPT, bool NT, bool RR>
 static hipError_t push_t(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t s, KTime t) {
   const size_t lds = push_lds_bytes(lc.nmax, lc.fp64, G, sizeof(typename AC::cell) == 8);
   // opt in to more than 64 KiB of dynamic LDS (gfx950 has 160 KiB per CU)
   static size_t attr_set = 65536;
   if (lds > attr_set) {
-    hipError_t e = hipFuncSetAttribute((const void *)k_push<P, AC, BS, PPT, NT>,
+    hipError_t e = hipFuncSetAttribute((const void *)k_push<P, AC, BS, PPT, NT, RR>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     attr_set = lds;
   }
-  return launch_k(k_push<P, AC, BS, PPT, NT>, dim3(std::min(lc.grid, lc.max_wgs)), dim3(BS), lds, s, t.a, t.b, p, G, lc.tile,
-                  lc.nmax, lc.steal, (lc.stream & STREAM_RR) ? 1 : 0, lc.min_wgs, lc.masks, lc.lists);
+  return launch_k(k_push<P, AC, BS, PPT, NT, RR>, dim3(std::min(lc.grid, lc.max_wgs)), dim3(BS), lds, s, t.a, t.b, p, G, lc.tile,
+                  lc.nmax, lc.steal, lc.min_wgs, lc.masks, lc.lists);
 }
 
-template <class P, class AC, int PPT, bool NT>
+template <class P, class AC, int PPT, bool NT, bool RR>
 static hipError_t push_bs(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t s, KTime t) {
   switch (lc.block) {
-    case 256: return push_t<P, AC, 256, PPT, NT>(p, G, lc, s, t);
-    case 512: return push_t<P, AC, 512, PPT, NT>(p, G, lc, s, t);
-    case 768: return push_t<P, AC, 768, PPT, NT>(p, G, lc, s, t);
-    default: return push_t<P, AC, 1024, PPT, NT>(p, G, lc, s, t);
+    case 256: return push_t<P, AC, 256, PPT, NT, RR>(p, G, lc, s, t);
+    case 512: return push_t<P, AC, 512, PPT, NT, RR>(p, G, lc, s, t);
+    case 768: return push_t<P, AC, 768, PPT, NT, RR>(p, G, lc, s, t);
+    default: return push_t<P, AC, 1024, PPT, NT, RR>(p, G, lc, s, t);
   }
+}
+
+template <class P, class AC, bool NT, bool RR>
+static hipError_t push_p(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t s, KTime t) {
+  if (lc.ppt >= 2 * Vec<P>::n) return push_bs<P, AC, 2 * Vec<P>::n, NT, RR>(p, G, lc, s, t);
+  return push_bs<P, AC, Vec<P>::n, NT, RR>(p, G, lc, s, t);
 }
 
 template <class P, class AC, bool NT>
 static hipError_t push_b(const DevPtrs &p, int G, const LaunchCfg &lc, hipStream_t s, KTime t) {
-  if (lc.ppt >= 2 * Vec<P>::n) return push_bs<P, AC, 2 * Vec<P>::n, NT>(p, G, lc, s, t);
-  return push_bs<P, AC, Vec<P>::n, NT>(p, G, lc, s, t);
+  return (lc.stream & STREAM_RR) ? push_p<P, AC, NT, true>(p, G, lc, s, t) : push_p<P, AC, NT, false>(p, G, lc, s, t);
 }
 #ifdef GS_PUSH_PART
 // one set of the push kernel's instantiations: particle precision, deposit

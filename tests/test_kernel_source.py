@@ -40,9 +40,9 @@ def test_injection_remembers_nothing_between_calls():
 
 
 def test_the_pushs_chunk_loop(tmp_path):
-    """The compiled loop over full chunks (binary32, one vector a thread): the absorbed
-    ions' stores go out before the particles' own, behind which the wave would wait for
-    them, and nothing is waited for between the loop's top and the next chunk's loads."""
+    """The compiled loop over full chunks (binary32, one vector a thread): nothing is waited
+    for between the loop's top and the next chunk's loads; and in round-robin order, whose
+    passes end with a wait, the absorbed ions' stores go out before the particles' own."""
     from paper_2603_24010_amd import build as B
     out = str(tmp_path / "push.s")
     flags = [f for f in B.FLAGS if f != "-Wall"]
@@ -51,13 +51,14 @@ def test_the_pushs_chunk_loop(tmp_path):
     subprocess.run(cmd, check=True)
     text = open(out).read()
     seen = 0
-    for m in re.finditer(r"^_ZN2gs6k_push\w*Li4ELb1E\w*:(.*?)^\.Lfunc_end", text, re.S | re.M):
-        lines = m.group(1).splitlines()
+    for m in re.finditer(r"^_ZN2gs6k_push\w*Li4ELb1ELb([01])E\w*:(.*?)^\.Lfunc_end", text, re.S | re.M):
+        lines = m.group(2).splitlines()
         store = next(i for i, ln in enumerate(lines) if "global_store_dwordx4" in ln and ln.rstrip().endswith(" nt"))
         loads = [i for i in range(store) if "global_load_dwordx4" in lines[i] and lines[i].rstrip().endswith(" nt")][-2:]
         top = max(i for i in range(loads[0]) if re.match(r"\.LBB.*Parent Loop BB\d+_\d+ Depth=1", lines[i]))
         assert loads[1] - top < 60, "the chunk loop's top"
         assert not any("vmcnt" in ln for ln in lines[top:loads[0]])
-        assert any("v_cvt_f64_f32" in ln for ln in lines[top:store]), "the queued ions' impact velocities"
+        queued = any("v_cvt_f64_f32" in ln for ln in lines[top:store])  # the absorbed ions' velocities
+        assert queued == (m.group(1) == "1")
         seen += 1
-    assert seen == 4  # workgroups of 256, 512, 768 and 1024
+    assert seen == 8  # workgroups of 256, 512, 768 and 1024, contiguous and round robin
