@@ -45,8 +45,10 @@ __host__ __device__ inline int acc_row_at(int k, int r) { return (k & ~31) * ACC
 // bound by their number (4097 nodes, 256 workgroups: 8.8 us to one row, 7.8 to four);
 // with more gaps, or fewer slots than 256 tiles of 2048, a gap has few workgroups, and
 // the field solve's reads cost more (1e5 particles, 256 cells: 19.6 us a step, 19.3
-// with one row; 1e6 particles, 512 cells: 28.6 and 37.6).
-constexpr int ACC_ROWS_NMAX = 2559, ACC_ROWS_GAPS = 16;
+// with one row; 1e6 particles, 512 cells: 28.6 and 37.6).  Gaps of 6e5 particles on 512
+// cells, us a step with rows and with one: 4 gaps 34.4 and 42.4, 8 gaps 46.0 and 48.3, 16
+// gaps 56.9 and 56.7; on 2500 cells 47.2 and 49.3, 51.1 and 51.4, 66.3 and 64.4.
+constexpr int ACC_ROWS_NMAX = 2559, ACC_ROWS_GAPS = 8;
 constexpr int64_t ACC_ROWS_SLOTS = 1 << 19;
 
 // Per-gap constants (read-only on the device).
