@@ -2,8 +2,9 @@
 //
 // Training is plain mini-batch gradient descent with Adam (Kingma and Ba,
 // 2015) on the mean squared error, in binary32 on the matrix cores; every
-// reduction has a fixed order, so a run is bitwise repeatable.  Batch evaluation uses the same device routine as the
-// strict step (bfloat16 weights, binary32 sums).
+// reduction has a fixed order, so a run is bitwise repeatable.  Batch evaluation uses
+// the strict step's device routine for few rows and the matrix cores for many
+// (bfloat16 weights, binary32 activations and sums in both).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
@@ -41,9 +42,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // branch (the library's erff has two, and a wave takes both): Phi(-t) = 2^-(1 + t
 // P(t)) for t >= 0, where t P(t) = -log2 erfc(t / sqrt 2) is nearly a parabola.  P is
 // the minimax polynomial of degree 9 on [0, 5.5] for the absolute error of Phi
-// (1.6e-9), constant past it (Phi(-5.5) = 1.9e-8).  GELU with it, against 64 bits in
-// the 2-norm, for normal z of scale 0.05, 0.5, 1 and 3: 4.3, 3.8, 3.3 and 2.6e-8, and
-// 3.7, 4.0, 3.7 and 2.9e-8 with a correctly rounded erff.
+// (1.6e-9), constant past it (Phi(-5.5) = 1.9e-8).  Against 64 bits in the 2-norm, for
+// normal z of scale 0.05, 0.2, 0.5, 1 and 3: GELU 4.3, 4.3, 3.8, 3.3 and 2.6e-8, its
+// derivative 4.4, 4.4, 4.2, 4.1 and 3.9e-8; with the library's erff and expf 3.7, 3.9,
+// 4.2, 3.9 and 2.9e-8, and 3.9, 3.9, 3.9, 4.1 and 4.0e-8.  So small z lose a little and
+// larger ones gain; over 42 training runs (batches 64 to 4096, 16 to 64 steps) the weights
+// are off by 1.71e-7 with either and the gradient by 2.93e-7, 2.98e-7 with the library's.
 __device__ inline float normal_cdf(float z) {
   const float t = fabsf(z), u = fminf(t, 5.5f);
   float h = 3.639413037603845e-08f;
@@ -78,7 +82,7 @@ constexpr int TRW = 8;              // waves of k_train_rows: one 16-wide column
 constexpr int TRT = TRW * 64;       // its threads
 constexpr int TLD = MLP_H + 4;      // row stride of the LDS tiles (spreads rows over the banks)
 constexpr int TRM = 16;             // batch rows per row block
-constexpr int TRAIN_MB1_MAX = 4096; // largest batch with one row block per workgroup
+constexpr int TRAIN_CUS = 256;      // workgroups of k_train_rows that run at once at full speed (one a CU)
 static_assert(TRW * 16 == MLP_H, "a wave per column block");
 
 // what k_train_rows leaves for the weight gradients (rows of the batch)
@@ -599,11 +603,16 @@ static hipError_t train_rows(const float *x, const float *t, long long n, const 
 static hipError_t train_step(const float *x, const float *t, long long n, const int32_t *order, long long off, int B,
                              float *th, float *m, float *v, long long step, float lr, float b1, float b2, float eps,
                              float *loss, float *grad, const TrainRows &o, hipStream_t s) {
-  // one row block per workgroup while that leaves CUs idle, else two, which
-  // read the weights half as often
+  // one row block per workgroup, or two where that gives each CU one workgroup and one
+  // would give it two (two read the weights half as often, but past that leave a second
+  // round of large workgroups on few CUs).  A step in us with one and with two: batch 4096
+  // 45.8 and 52.5, 4600 56.0 and 54.8, 8192 72.9 and 71.1, 10000 91.1 and 98.5, 16384 128
+  // and 128, 32768 239 and 243
+  const int blocks = (B + TRM - 1) / TRM;
   int ntiles = 0;
-  hipError_t e = B <= TRAIN_MB1_MAX ? train_rows<1>(x, t, n, order, off, B, th, o, s, &ntiles)
-                                    : train_rows<2>(x, t, n, order, off, B, th, o, s, &ntiles);
+  hipError_t e = blocks > TRAIN_CUS && blocks <= 2 * TRAIN_CUS
+                     ? train_rows<2>(x, t, n, order, off, B, th, o, s, &ntiles)
+                     : train_rows<1>(x, t, n, order, off, B, th, o, s, &ntiles);
   if (e != hipSuccess) return e;
   const double c1 = 1.0 - std::pow((double)b1, (double)step), c2 = 1.0 - std::pow((double)b2, (double)step);
   const AdamK ak{lr, b1, b2, eps, (float)c1, (float)c2};
