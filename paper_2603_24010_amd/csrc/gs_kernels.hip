@@ -2353,9 +2353,18 @@ __device__ __forceinline__ void push_tail_emit(PushShared<P, AC> &sh, int G, int
 // particles take 79 us shared and 71 split, 2e8 on 16384 cells 710 and 683).  What it
 // costs is balance.  An ion tile takes up to a quarter longer than an electron tile (its
 // absorbed ions are queued and emit), so the electrons' workgroups idle, in proportion to
-// their tiles: with 4.9e7 electrons to 1.1e8 ions on 16384 cells a step is 628 us split
-// and 613 shared, with 2.1e7 to 1.6e8 658 and 667; hence a quarter.  And some may have a
-// tile more: taken when none has, or a tile is little of what each has.
+// their tiles, when many ions are absorbed.  With 3e5 of them a step on 16384 cells and
+// 0.20, 0.28 and 0.38 electrons per ion: 576, 572 and 560 us a push split, 587, 562 and
+// 537 shared; hence a quarter.  (With few absorbed the split wins at any ratio: 2e8 ions,
+// 3.5e4 absorbed, 0.05, 0.2, 0.26, 0.5 and 1 electrons per ion, 610, 698, 730, 860 and
+// 1149 us split, 651, 729, 759, 888 and 1152 shared; on 4096 cells, 2e7 ions, 67.9, 74.4,
+// 76.2, 87.3 and 124.5, and 69.5, 77.0, 80.8, 91.0 and 126.7.)
+// And some may have a tile more than when shared: taken when none has, or a tile is little
+// of what each has.  Below eight tiles each a tile more gains where it is small (tiles of
+// 4096 on 16384 cells, 7 each: 58 us, 71 shared; of 6144 on 4096 cells 41.5 and 46.4) and
+// loses where it is not (of 16384 on 1024 cells, 2 and 4 each: 36.8 and 56.6, 33.3 and
+// 54.0 shared; of 24576 on 4096 cells, 3 each: 65 and 59); from eight on it gained in all
+// that was measured (12 each: 59.2 and 61.2 on 4096 cells, 71.6 and 78.2 on 16384).
 __device__ inline int rr_electrons(int te, int ti, int nwg) {
   const int m = (te + ti + nwg - 1) / nwg;  // tiles of the busiest when shared
   if (te == 0 || 4ll * te > ti || m < 2) return 0;
@@ -3319,8 +3328,10 @@ __global__ __launch_bounds__(IBS) void k_inject_run(DevPtrs p, int gap, int spec
   for (int j = tid; j < nn; j += IBS) acc[j] = 0ull;
   __syncthreads();
   const unsigned long long base = s_base;
-  // (the next particles' loads are out before these are placed: 2e7 ions on 4096 cells
-  // take 181 us, 191 without)
+  // (The next particles' loads go out together, before these are placed: 2e7 ions on 4096
+  // cells take 181 us, 191 with each pass's loads at its own start.  They are not hidden
+  // behind the placing: it reads the gap's constants from memory for each particle, and
+  // the first such wait is for these loads too.)
   double xs[IU], vs[IU];
 #pragma unroll
   for (int q = 0; q < IU; ++q) {
@@ -3367,8 +3378,10 @@ __global__ __launch_bounds__(IBS) void k_inject_run(DevPtrs p, int gap, int spec
 constexpr int RBS = 1024;  // k_phi and k_dt_read threads
 
 // phi_i = dx sum_{k >= i} E_{k+1/2}, phi_N = 0: thread t owns the reversed
-// positions [t ch, (t + 1) ch), counted from the ground.  A chain of loads: four are
-// in flight per round trip, and 1024 threads leave one round at 4096 cells.
+// positions [t ch, (t + 1) ch), counted from the ground.  A chain of loads, four in
+// flight per round trip (one round at 4096 cells), and in the second pass of stores to
+// phi, which is host memory: c.dx is read again behind each, so that a thread's nodes
+// cost a trip there apiece.
 __global__ __launch_bounds__(RBS) void k_phi(DevPtrs p, int gap, double *phi) {
   __shared__ double wsum[RBS / 64];
   const int tid = threadIdx.x;
